@@ -401,10 +401,14 @@ reff_status reff_batch_plans(const reff_pdn_desc* plans, int32_t n_plans,
  *            R(k,k) = 0, R(i,j) = R(j,i).
  *   stream   hipStream_t to run on; NULL => default stream.  The call
  *            returns after R_out is written.
- * The call allocates and frees its own device work memory: the weight table
- * ((M-1)(N-1) doubles), a cosine table (P (N-1) doubles), partial sums of
- * at most about 16.8M + P^2 doubles (134 MB + 8 P^2 bytes), and a P^2
- * staging array when R_out is a host pointer.
+ * The pairs come from a table of the double cosine sums over all coordinate
+ * differences and sums (two matrix products over the tier, whatever P), or,
+ * for few points on a very large tier, from direct products over the tier.
+ * The call allocates and frees its own device work memory: for the table two
+ * arrays of about (M+1)(N+1) doubles; for direct products the weights ((M-1)
+ * (N-1) doubles), a cosine table (P (N-1) doubles) and partial sums of at most
+ * about 16.8M + P^2 doubles (134 MB + 8 P^2 bytes); and a P^2 staging array
+ * when R_out is a host pointer.
  * Errors: INVALID_ARG (M, N < 1, r or s not finite and positive, P < 0 or
  * P > 65535, a point off the grid, NULL pointers with P > 0),
  * OUT_OF_MEMORY, DEVICE.
@@ -456,15 +460,16 @@ reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t ny, const do
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, results and errors as
  * reff_grid_pairs, which it shares its kernels with; its work memory (points,
- * weights, cosine table, partial Gram blocks, and the staging of R_out when
- * it is a host pointer) lives in one 64 MiB array per GPU that the library
+ * tables or weights and partial blocks, and the staging of R_out when it is a
+ * host pointer) lives in one 64 MiB array per GPU that the library
  * holds from the first call on that device until the process ends.  Inputs
  * whose work memory does not fit (one m segment of P^2 doubles plus 8 (M-1)
  * (N-1) + 8 P (N-1) + 8 P + (host output) 8 P^2 bytes, each part rounded up
  * to 256 bytes, above 64 MiB; for example P above about 2,800 points) are
- * rejected with REFF_ERR_INVALID_ARG before any device work.  When fewer m
- * segments fit than the allocating call uses, the partial sums are grouped
- * differently (results agree to rounding).  Calls on one GPU share the
+ * rejected with REFF_ERR_INVALID_ARG before any device work.  Calls whose
+ * cosine table does not fit take the direct products, and when fewer m segments
+ * of those fit than the allocating call uses, the partial sums are grouped
+ * differently (either way results agree to rounding).  Calls on one GPU share the
  * array: calls that overlap in time on the same GPU (two host threads, or
  * two streams) race and must be serialised by the caller.  The call
  * returns after R_out is written; it makes no hipMalloc or hipFree call.

@@ -3,7 +3,7 @@
 //
 //  1. intra-die resistances from the closed form of Eq. 3: TSV-TSV on every
 //     tier (d x p x p), bump-TSV on tier 0 (m x p), load-TSV on the last
-//     tier (n x p) -- one all-pairs evaluation per tier (grid_pairs.hip);
+//     tier (n x p) -- rectangles of one cosine table per tier (grid_pairs.hip);
 //  2. the reduced saddle-point system C x = b of size (p+1)(d-1): unknowns
 //     are the p TSV currents of each of the d-1 tier interfaces and the d-1
 //     supply-voltage differences.  With Atilde^i = -R^i_TT / 2 (TSV-TSV
@@ -409,14 +409,20 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   const int q = p - 1, nz = q * (d - 1), ne = (int)(m + n);
   const int ntile = (nz + TB - 1) / TB;
   Bufs bufs;
+  // the cosine tables of all tiers, or (few endpoints on a very large tier)
+  // direct products tier by tier through a P x P array
+  bool table = grid_use_table(nx, ny, std::max(P0, Pd));
+  const size_t npts = table ? (size_t)(p + m + n) : (size_t)std::max(P0, Pd);
   int32_t* dxy = nullptr;
+  double* drs = nullptr;
   double *dR = nullptr, *RT = nullptr, *rt = nullptr, *Rs1 = nullptr, *Rsd = nullptr;
   double *HZ = nullptr, *L = nullptr, *Linv = nullptr, *rhs = nullptr, *Y = nullptr;
   double *Icur = nullptr, *selfv = nullptr, *cA = nullptr, *cB = nullptr, *G = nullptr;
   double* dout = nullptr;
   int* bad = nullptr;
-  hipError_t e = bufs.get(&dxy, 2 * (size_t)std::max(P0, Pd));
-  if (e == hipSuccess) e = bufs.get(&dR, (size_t)std::max(P0, Pd) * std::max(P0, Pd));
+  hipError_t e = bufs.get(&dxy, 2 * npts);
+  if (e == hipSuccess) e = bufs.get(&drs, 2 * (size_t)d);
+  if (e == hipSuccess && !table) e = bufs.get(&dR, npts * npts);
   if (e == hipSuccess) e = bufs.get(&RT, (size_t)d * p * p);
   if (e == hipSuccess) e = bufs.get(&rt, (size_t)p * (d - 1));
   if (e == hipSuccess) e = bufs.get(&Rs1, (size_t)m * p);
@@ -438,10 +444,35 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   e = hipMemsetAsync(bad, 0, sizeof(int), st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(rt, tsv_r, sizeof(double) * p * (d - 1), hipMemcpyHostToDevice, st);
-  // 1. intra-die resistances, tier by tier: TSVs first, then the tier's
-  //    bumps (tier 0) or loads (last tier)
+  // 1. intra-die resistances: TSV-TSV of every tier, bump-TSV of tier 0,
+  //    load-TSV of the last tier
   std::vector<int32_t> pts;
-  for (int t = 0; t < d && e == hipSuccess; ++t) {
+  std::vector<double> rs;
+  if (table && e == hipSuccess) {
+    pts.assign(tsv_xy, tsv_xy + 2 * (size_t)p);
+    pts.insert(pts.end(), bump_xy, bump_xy + 2 * m);
+    pts.insert(pts.end(), load_xy, load_xy + 2 * n);
+    std::vector<GridRect> rects;
+    for (int t = 0; t < d; ++t) {
+      rs.push_back(r_t[t]);
+      rs.push_back(s_t[t]);
+      rects.push_back(GridRect{t, dxy, dxy, p, p, RT + (size_t)t * p * p});
+    }
+    rects.push_back(GridRect{0, dxy + 2 * (size_t)p, dxy, m, p, Rs1});
+    rects.push_back(GridRect{d - 1, dxy + 2 * (size_t)(p + m), dxy, n, p, Rsd});
+    e = hipMemcpyAsync(dxy, pts.data(), sizeof(int32_t) * pts.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(drs, rs.data(), sizeof(double) * rs.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+      e = grid_tiers_device(nx, ny, d, drs, rects.data(), (int)rects.size(), st);
+    if (e == hipErrorOutOfMemory) {  // no room for a tier's table
+      (void)hipGetLastError();
+      table = false;
+      e = hipStreamSynchronize(st);  // the staged points are refilled below
+      if (e == hipSuccess) e = bufs.get(&dR, (size_t)std::max(P0, Pd) * std::max(P0, Pd));
+    }
+  }
+  for (int t = 0; !table && t < d && e == hipSuccess; ++t) {
     pts.assign(tsv_xy, tsv_xy + 2 * (size_t)p);
     int64_t extra = 0;
     if (t == 0) pts.insert(pts.end(), bump_xy, bump_xy + 2 * m), extra = m;
