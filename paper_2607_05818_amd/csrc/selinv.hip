@@ -11,23 +11,23 @@
 // column-major block over [pivots, update set Q].  It is cleared, receives
 // the entries of G in its pivot columns, and the update matrices of its
 // children (extend-add, children of rank 0 then 1, so no two writers meet).
-// Its k pivot columns are then factored 64 at a time, right-looking:
-//   L_jj = chol(A_jj), L_Rj = A_Rj L_jj^-T, A_RR -= L_Rj L_Rj^T  (lower),
-// where R is every front row after the panel; after the last panel the
-// trailing Q x Q block is the update matrix passed to the parent.
+// Its k pivot columns are then eliminated 64 at a time, right-looking, as a
+// block LDL^T: with P the panel and R every front row after it,
+//   D_P = A_PP^-1 (in place of A_PP),  Lhat = A_RP D_P (kept transposed in
+//   the unused upper block P x R),     A_RR -= Lhat A_RP^T  (lower).
+// After the last panel the trailing Q x Q block is the update matrix passed
+// to the parent.  (D_P and Lhat are all that the inversion reads, so neither
+// a triangular factor of the panel nor its inverse is ever formed.)
 //
 // Selected inversion (roots first; Z = G^-1): a front first gathers Z_QQ
 // from its parent's finished block, then takes its panels last to first.
 // For a panel P with the rows R after it (the later pivots of the front and
 // Q, all of whose Z entries are known by then):
-//   Lhat = L_RP L_PP^-1,  Z_RP = -Z_RR Lhat,
-//   Z_PP = L_PP^-T L_PP^-1 - Lhat^T Z_RP,
-// the block form of the Takahashi identities (L^T Z = L^-1, whose upper
-// part is known and whose lower part is the identity's inverse on the
-// diagonal), written over Z_RP / Z_PR / Z_PP in place.  The dense front
-// makes the structure of every column the whole of R, so the supernodal
-// block form applies to any panel split.  diag(Z_PP) is R_i for the panel's
-// nodes.
+//   Z_RP = -Z_RR Lhat,   Z_PP = D_P - Lhat^T Z_RP,
+// the block form of the Takahashi identities, written over Lhat / A_RP / D_P
+// in place (Z_RP, its transpose Z_PR, Z_PP).  The dense front makes the
+// structure of every column the whole of R, so the supernodal block form
+// applies to any panel split.  diag(Z_PP) is R_i for the panel's nodes.
 //
 // The dense work is 64 x 64 output tiles on the float64 matrix cores
 // (v_mfma_f64_16x16x4); tiles of all fronts of a level share one launch
@@ -63,56 +63,76 @@ struct DFront {
   int64_t poff;  // parent's arena offset, -1 at a root
   int64_t rel;   // into rel[]: F - k parent positions of Q
   int64_t piv;   // into piv_node[]: k node ids
-  int64_t ybuf;  // offset of its F x 64 block in the level's Y buffer
-  int64_t part;  // offset of its nsplit x 64 x 64 partial products
-  int32_t F, k, pF, rank, nsplit, pad_;
+  int64_t ybuf;  // offset of its F x 64 block in a K part's Y buffer
+  int64_t part;  // offset of its row tiles' 64 x 64 partial products
+  int32_t F, k, pF, rank;
 };
 
 constexpr int KS = 32;  // K slice staged through LDS
 
-// C(i, j) = alpha sum_{kk in [kb, ke)} A(i, kk) B(kk, j) [+ beta C(i, j)] on the
-// 64 x 64 tile at (i0, j0) of an M x N column-major C (ldc).
-//   A(i, kk) = ta ? A[i lda + kk] : A[kk lda + i]
-//   B(kk, j) = tb ? B[kk ldb + j] : B[j ldb + kk]
-// With `lower`, entries above the diagonal are not written.  Four waves;
+// C(i, j) = alpha sum_{kk in [kb, ke)} A(i, kk) B(kk, j) [+ C(i, j) with ADD] on
+// the 64 x 64 tile at (i0, j0) of an M x N column-major C (ldc).
+//   A(i, kk) = TA ? A[i lda + kk] : A[kk lda + i]
+//   B(kk, j) = TB ? B[kk ldb + j] : B[j ldb + kk]
+//   C(i, j)  at TC ? C[i ldc + j] : C[j ldc + i]
+// With LOWER, entries above the diagonal are not written.  Four waves;
 // wave w owns tile rows 16 w .. 16 w + 15 as four 16 x 16 accumulators.
 // K goes through LDS 32 at a time, the next slice's loads in flight (in
-// registers) while the matrix cores work on the current one.  The whole K
-// range is read before the tile is written, so C may alias the rows of A
-// it covers.
+// registers) while the matrix cores work on the current one; with ADD the
+// tile of C is loaded before the products (a panel step has only two slices,
+// and the tile's latency would follow them otherwise).
+template <bool TA, bool TB, bool TC, bool LOWER, bool ADD>
 __device__ __forceinline__ void gemm_tile(int i0, int j0, int M, int N, int kb, int ke,
-                                          double alpha, const double* A, int64_t lda, bool ta,
-                                          const double* B, int64_t ldb, bool tb, double beta,
-                                          double* C, int64_t ldc, bool lower,
+                                          double alpha, const double* A, int64_t lda,
+                                          const double* B, int64_t ldb, double* C, int64_t ldc,
                                           double (*sA)[KS + 1], double (*sB)[PT + 1]) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int cc = lane & 15, kr = lane >> 4;
   d4v acc[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q] = d4v{0.0, 0.0, 0.0, 0.0};
+  // Loads go through the slice's scalar base and 32-bit byte offsets.  Rows,
+  // columns and K indices past the edge repeat the last one: entries past
+  // the edge of C are not written, and past the end of K A is zeroed.
+  const uint32_t la = 8u * (uint32_t)lda, lb = 8u * (uint32_t)ldb, lc = 8u * (uint32_t)ldc;
+  const int mr = M - 1 - i0, nr = N - 1 - j0;
   double ra[8], rb[8];
   auto load = [&](int k0) {
+    const char* pa = (const char*)(TA ? A + (int64_t)i0 * lda + k0 : A + (int64_t)k0 * lda + i0);
+    const char* pb = (const char*)(TB ? B + (int64_t)k0 * ldb + j0 : B + (int64_t)j0 * ldb + k0);
+    const int last = ke - 1 - k0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int idx = t + 256 * e;  // 0 .. 2047
-      const int ai = ta ? idx >> 5 : idx & 63, ak = ta ? idx & 31 : idx >> 6;
-      const int gi = i0 + ai, gk = k0 + ak;
-      ra[e] = (gi < M && gk < ke) ? (ta ? A[(int64_t)gi * lda + gk] : A[(int64_t)gk * lda + gi])
-                                  : 0.0;
-      const int bj = tb ? idx & 63 : idx >> 5, bk = tb ? idx >> 6 : idx & 31;
-      const int gj = j0 + bj, gk2 = k0 + bk;
-      rb[e] = (gj < N && gk2 < ke) ? (tb ? B[(int64_t)gk2 * ldb + gj] : B[(int64_t)gj * ldb + gk2])
-                                   : 0.0;
+      const int ai = min(TA ? (t >> 5) + 8 * e : t & 63, mr);
+      const int bj = min(TB ? t & 63 : (t >> 5) + 8 * e, nr);
+      const int ak = TA ? t & 31 : (t >> 6) + 4 * e, bk = TB ? (t >> 6) + 4 * e : t & 31;
+      const uint32_t ca = min(ak, last), cb = min(bk, last);
+      const double va =
+          *(const double*)(pa + (TA ? __umul24(ai, la) + 8u * ca : __umul24(ca, la) + 8u * ai));
+      rb[e] = *(const double*)(pb + (TB ? __umul24(cb, lb) + 8u * bj : __umul24(bj, lb) + 8u * cb));
+      ra[e] = ak <= last ? va : 0.0;
     }
   };
+  char* pc = (char*)(TC ? C + (int64_t)i0 * ldc + j0 : C + (int64_t)j0 * ldc + i0);
+  auto at = [&](int i, int j) -> double* {
+    return (double*)(pc + (TC ? __umul24(i, lc) + 8u * j : __umul24(j, lc) + 8u * i));
+  };
   if (kb < ke) load(kb);
+  double cv[4][4];
+  if (ADD) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        cv[q][r] = *at(min(16 * w + kr + 4 * r, mr), min(16 * q + cc, nr));
+  }
   for (int k0 = kb; k0 < ke; k0 += KS) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int idx = t + 256 * e;
-      sA[ta ? idx >> 5 : idx & 63][ta ? idx & 31 : idx >> 6] = ra[e];
-      sB[tb ? idx >> 6 : idx & 31][tb ? idx & 63 : idx >> 5] = rb[e];
+      sA[TA ? idx >> 5 : idx & 63][TA ? idx & 31 : idx >> 6] = ra[e];
+      sB[TB ? idx >> 6 : idx & 31][TB ? idx & 63 : idx >> 5] = rb[e];
     }
     __syncthreads();
     if (k0 + KS < ke) load(k0 + KS);
@@ -129,11 +149,9 @@ __device__ __forceinline__ void gemm_tile(int i0, int j0, int M, int N, int kb, 
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int gi = i0 + 16 * w + kr + 4 * r, gj = j0 + 16 * q + cc;
-      if (gi < M && gj < N && (!lower || gi >= gj)) {
-        double* c = &C[(int64_t)gj * ldc + gi];
-        *c = alpha * acc[q][r] + (beta != 0.0 ? beta * *c : 0.0);
-      }
+      const int i = 16 * w + kr + 4 * r, j = 16 * q + cc;
+      if (i <= mr && j <= nr && !(LOWER && i0 + i < j0 + j))
+        *at(i, j) = ADD ? cv[q][r] + alpha * acc[q][r] : alpha * acc[q][r];
     }
 }
 
@@ -193,109 +211,114 @@ __global__ __launch_bounds__(256) void k_gather(const DFront* __restrict__ fr,
   }
 }
 
-// Diagonal tile of panel jp of every front.  FACTOR: Cholesky of A_jj in
-// place (lower) and L_jj^-1 into Li; a pivot that is not positive sets
-// *bad.  Otherwise (selected inversion): L_jj^-1 into Li and
-// L_jj^-T L_jj^-1 into Z0.  Li, Z0: 64 x 64 column-major per list slot,
-// identity-padded past the panel width.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Inverse of the symmetric positive definite w x w matrix in T (64 x 64 in
+// LDS, identity-padded past w), in place, by Gauss-Jordan elimination in four
+// blocks of 16 columns; a pivot that is not positive sets *bad.
 //
-// The tile lives in registers: lane r of wave g holds row r of columns
-// g, g+4, .., g+60 (Cholesky), then column r of rows g, g+4, .. of the
-// inverse (forward elimination); one LDS tile holds L for the elimination
-// and then the inverse.  Each of the 64 steps publishes one
-// column (one row) through a double-buffered LDS vector, so a step costs
-// one barrier, a few LDS broadcasts and 16 fused multiply-adds per lane.
-template <bool FACTOR>
+// One wave eliminates a block's 16 columns on all 64 rows in registers (lane
+// r holds row r): the pivot row's entries are broadcast by v_readlane, so the
+// 16 dependent steps need neither LDS nor barriers.  That leaves the block
+// D = A_bb^-1 on its own rows and C = -A_ib D on the others, and the other
+// columns follow as one product on the matrix cores, A_ij += C_ib A_bj (and
+// A_bj = D A_bj), a 16-row strip per wave.
+// The tile's 64 steps are a serial chain, and every panel of every level
+// waits for one (98 panels at 4 x 512 x 512): a step costs about 36
+// independent register instructions here, against a barrier, LDS reads, a
+// square root and a division when the four waves shared each column.  Per
+// panel of the root of the 4 x 512 x 512 stack: 25 us, where Cholesky and the
+// triangular inverse took 101 us and their repetition in the inversion 60 us.
+__device__ __forceinline__ void invert_tile(double (*T)[PT + 1], double (*Cp)[17], int w, int* bad) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int cc = lane & 15, kr = lane >> 4;
+  for (int b = 0; 16 * b < w; ++b) {
+    if (wv == 0) {
+      double a[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) a[c] = T[lane][16 * b + c];
+      bool ok = true;
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int q = 16 * b + p;  // pivot row and column
+        const double piv = lane_value(a[p], q);
+        ok = ok && piv > 0.0 && std::isfinite(piv);
+        const double inv = 1.0 / piv;
+        // row q becomes inv * row q, row r loses (a_rp inv) * row q
+        const double mult = lane == q ? inv : -a[p] * inv;
+        const double keep = lane == q ? 0.0 : 1.0;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          if (c == p) continue;
+          const double s = lane_value(a[c], q);
+          a[c] = fma(mult, s, a[c] * keep);
+        }
+        a[p] = mult;
+      }
+      if (!ok && lane == 0) atomicOr(bad, 1);
+#pragma unroll
+      for (int c = 0; c < 16; ++c) Cp[lane][c] = a[c];
+    }
+    __syncthreads();
+    d4v acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j == b) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        acc[j][r] = wv == b ? 0.0 : T[16 * wv + kr + 4 * r][16 * j + cc];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+            Cp[16 * wv + cc][4 * ks + kr], T[16 * b + 4 * ks + kr][16 * j + cc], acc[j], 0, 0, 0);
+    }
+    __syncthreads();  // every strip has read row block b
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        T[16 * wv + kr + 4 * r][16 * j + cc] =
+            j == b ? Cp[16 * wv + kr + 4 * r][cc] : acc[j][r];
+    __syncthreads();
+  }
+}
+
+// D_P = A_PP^-1 of panel jp of every front, in place (full square).
 __global__ __launch_bounds__(256) void k_tile(const DFront* __restrict__ fr,
                                               const int32_t* __restrict__ list, int nf, int jp,
-                                              double* ar, double* __restrict__ Li,
-                                              double* __restrict__ Z0, int* bad) {
-  __shared__ double T[PT][PT + 1];  // the tile, then its inverse
-  __shared__ double buf[2][PT];
-  const int t = threadIdx.x, r = t & 63, g = t >> 6;
+                                              double* ar, int* bad) {
+  __shared__ double T[PT][PT + 1], Cp[PT][17];
+  const int t = threadIdx.x;
   for (int fi = blockIdx.x; fi < nf; fi += gridDim.x) {
     const DFront f = fr[list[fi]];
     const int j0 = PT * jp;
     if (f.k <= j0) continue;
     const int w = min(PT, f.k - j0);
     double* a = ar + f.off + (int64_t)j0 * f.F + j0;
-    double v[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int cc = g + 4 * j;
-      v[j] = (r < w && cc < w) ? (r >= cc ? a[(int64_t)cc * f.F + r] : 0.0) : (r == cc ? 1.0 : 0.0);
+    for (int e = t; e < PT * PT; e += 256) {
+      const int r = e & 63, c = e >> 6;
+      if (r < c) continue;
+      const double v = r < w ? a[(int64_t)c * f.F + r] : (r == c ? 1.0 : 0.0);
+      T[r][c] = v;
+      T[c][r] = v;
     }
-    __syncthreads();  // the previous front's LDS reads are done
-    if (FACTOR) {
-#pragma unroll
-      for (int c = 0; c < PT; ++c) {
-        if (c >= w) break;  // the rest of the tile is identity padding
-        double* bf = buf[c & 1];
-        if (g == (c & 3)) bf[r] = v[c >> 2];
-        __syncthreads();
-        const double piv = bf[c];
-        if (t == 0 && !(piv > 0.0 && std::isfinite(piv))) atomicOr(bad, 1);
-        const double sq = sqrt(fmax(piv, 1e-300)), inv = 1.0 / sq;
-        const double lr = bf[r] * inv;
-        if (g == (c & 3)) v[c >> 2] = r > c ? lr : (r == c ? sq : 0.0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int cc = g + 4 * j;
-          if (cc > c && r >= cc) v[j] -= lr * (bf[cc] * inv);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int cc = g + 4 * j;
-        if (r < w && cc < w && r >= cc) a[(int64_t)cc * f.F + r] = v[j];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j) T[r][g + 4 * j] = v[j];
     __syncthreads();
-    // X = L^-1: lane r holds column r of rows g + 4 j
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = (g + 4 * j == r) ? 1.0 : 0.0;
-#pragma unroll
-    for (int k = 0; k < PT; ++k) {
-      if (k >= w) break;  // rows past the panel width keep the identity
-      double* bk = buf[k & 1];
-      if (g == (k & 3)) {
-        v[k >> 2] /= T[k][k];
-        bk[r] = v[k >> 2];
-      }
-      __syncthreads();
-      const double xk = bk[r];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int i = g + 4 * j;
-        if (i > k) v[j] -= T[i][k] * xk;
-      }
+    invert_tile(T, Cp, w, bad);
+    for (int e = t; e < PT * PT; e += 256) {
+      const int r = e & 63, c = e >> 6;
+      if (r < w && c < w) a[(int64_t)c * f.F + r] = T[r][c];
     }
-    __syncthreads();  // every step's reads of L are done
-#pragma unroll
-    for (int j = 0; j < 16; ++j) T[g + 4 * j][r] = v[j];
-    __syncthreads();
-    double* li = Li + (size_t)fi * PT * PT;
-    for (int e = t; e < PT * PT; e += 256) li[e] = T[e & 63][e >> 6];
-    if (!FACTOR) {
-      // Z0(r, b) = sum_k X(k, r) X(k, b), b = g + 4 j
-      double z[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) z[j] = 0.0;
-      for (int k = 0; k < w; ++k) {  // the inverse is block diagonal past w
-        const double xr = T[k][r];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] += xr * T[k][g + 4 * j];
-      }
-      double* z0 = Z0 + (size_t)fi * PT * PT;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) z0[(g + 4 * j) * PT + r] = z[j];
-    }
+    __syncthreads();  // before the next front's loads
   }
 }
 
-enum GemmOp { OP_TRSM = 0, OP_SYRK = 1, OP_LHAT = 2, OP_Y = 3, OP_PART = 4 };
+enum GemmOp { OP_LHAT = 0, OP_UPDATE = 1, OP_Y = 2 };
 
 __device__ __forceinline__ void lower_tile(int t, int& ti, int& tj) {
   ti = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
@@ -305,16 +328,12 @@ __device__ __forceinline__ void lower_tile(int t, int& ti, int& tj) {
 }
 
 // The panel products of step jp for every front of a level (see the file
-// comment); blockIdx.x is the tile (or, for OP_PART, the K split).
+// comment); blockIdx.x is the tile (for OP_Y, with its part of the K range).
 template <int OP>
-__global__ __launch_bounds__(256) void k_front_gemm(const DFront* __restrict__ fr,
+__global__ __launch_bounds__(256, OP == OP_UPDATE ? 3 : 4) void k_front_gemm(const DFront* __restrict__ fr,
                                                     const int32_t* __restrict__ list, int nf,
-                                                    int jp, double* ar,
-                                                    const double* __restrict__ Li,
-                                                    double* __restrict__ Ybuf,
-                                                    double* __restrict__ part, int tiles,
-                                                    int ysplit, double* __restrict__ Ysp,
-                                                    int64_t ylev) {
+                                                    int jp, double* ar, int tiles, int ysplit,
+                                                    double* __restrict__ Ysp, int64_t ylev) {
   __shared__ double sA[PT][KS + 1], sB[KS][PT + 1];
   for (int fi = blockIdx.y; fi < nf; fi += gridDim.y) {
     const DFront f = fr[list[fi]];
@@ -323,82 +342,60 @@ __global__ __launch_bounds__(256) void k_front_gemm(const DFront* __restrict__ f
     const int w = min(PT, f.k - j0), r0 = j0 + w, m = f.F - r0;
     const int64_t F = f.F;
     double* base = ar + f.off;
-    const double* li = Li + (size_t)fi * PT * PT;
+    double* a_rp = base + (int64_t)j0 * F + r0;  // lower block, A[row][panel column]
+    double* lhat = base + (int64_t)r0 * F + j0;  // upper block: Lhat(i, p) at [i F + p]
     const int ntile = (m + PT - 1) / PT;
-    if (OP == OP_TRSM || OP == OP_LHAT) {
-      // rows R of the panel, in place: times L_jj^-T (factor) or L_jj^-1
+    if (OP == OP_LHAT) {
       if ((int)blockIdx.x >= ntile) continue;
-      double* c = base + (int64_t)j0 * F + r0;
-      gemm_tile(blockIdx.x * PT, 0, m, w, 0, w, 1.0, c, F, false, li, PT, OP == OP_TRSM, 0.0, c,
-                F, false, sA, sB);
-    } else if (OP == OP_SYRK) {
+      gemm_tile<false, false, true, false, false>(blockIdx.x * PT, 0, m, w, 0, w, 1.0, a_rp, F,
+                                                  base + (int64_t)j0 * F + j0, F, lhat, F, sA, sB);
+    } else if (OP == OP_UPDATE) {
       if ((int)blockIdx.x >= ntile * (ntile + 1) / 2) continue;
       int ti, tj;
       lower_tile(blockIdx.x, ti, tj);
-      const double* l = base + (int64_t)j0 * F + r0;
-      gemm_tile(ti * PT, tj * PT, m, m, 0, w, -1.0, l, F, false, l, F, true, 1.0,
-                base + (int64_t)r0 * F + r0, F, true, sA, sB);
-    } else if (OP == OP_Y) {
-      // Y = -Z_RR Lhat; with ysplit > 1, the K range in ysplit parts, each
-      // into its own copy of the level's Y buffer (summed by k_ysum)
+      gemm_tile<true, true, false, true, true>(ti * PT, tj * PT, m, m, 0, w, -1.0, lhat, F, a_rp,
+                                               F, base + (int64_t)r0 * F + r0, F, sA, sB);
+    } else {
+      // Y = -Z_RR Lhat over A_RP; with ysplit > 1, the K range in ysplit
+      // parts, each into its own Y buffer (summed by k_finish)
       const int tile = (int)blockIdx.x % tiles, sp = (int)blockIdx.x / tiles;
       if (tile >= ntile) continue;
       int kb = 0, ke = m;
-      double* y = Ybuf + f.ybuf;
+      double* y = a_rp;
       if (ysplit > 1) {
         const int ks = ((m + ysplit - 1) / ysplit + KS - 1) / KS * KS;
         kb = min(m, sp * ks);
         ke = min(m, kb + ks);
         y = Ysp + (size_t)sp * ylev + f.ybuf;
       }
-      gemm_tile(tile * PT, 0, m, w, kb, ke, -1.0, base + (int64_t)r0 * F + r0, F, false,
-                base + (int64_t)j0 * F + r0, F, false, 0.0, y, F, false, sA, sB);
-    } else {
-      // partial -Lhat^T Y over split blockIdx.x of the rows R
-      if ((int)blockIdx.x >= f.nsplit) continue;
-      const int ks = (m + f.nsplit - 1) / f.nsplit;
-      const int kb = min(m, (int)blockIdx.x * ks), ke = min(m, kb + ks);
-      gemm_tile(0, 0, w, w, kb, ke, -1.0, base + (int64_t)j0 * F + r0, F, true, Ybuf + f.ybuf, F,
-                false, 0.0, part + f.part + (size_t)blockIdx.x * PT * PT, PT, false, sA, sB);
+      gemm_tile<false, true, false, false, false>(tile * PT, 0, m, w, kb, ke, -1.0,
+                                                  base + (int64_t)r0 * F + r0, F, lhat, F, y, F, sA,
+                                                  sB);
     }
+    __syncthreads();
   }
 }
 
-// Y = sum of the ysplit partial products (rows of row tile blockIdx.x).
-__global__ __launch_bounds__(256) void k_ysum(const DFront* __restrict__ fr,
-                                              const int32_t* __restrict__ list, int nf, int jp,
-                                              int ysplit, const double* __restrict__ Ysp,
-                                              int64_t ylev, double* __restrict__ Ybuf) {
-  for (int fi = blockIdx.y; fi < nf; fi += gridDim.y) {
-    const DFront f = fr[list[fi]];
-    const int j0 = PT * jp;
-    if (f.k <= j0) continue;
-    const int w = min(PT, f.k - j0), m = f.F - j0 - w;
-    const int i0 = blockIdx.x * PT;
-    if (i0 >= m) continue;
-    for (int e = threadIdx.x; e < PT * PT; e += 256) {
-      const int c = e >> 6, i = i0 + (e & 63);
-      if (i >= m || c >= w) continue;
-      const int64_t o = f.ybuf + (int64_t)c * f.F + i;
-      double v = 0.0;
-      for (int s = 0; s < ysplit; ++s) v += Ysp[(size_t)s * ylev + o];
-      Ybuf[o] = v;
-    }
-  }
-}
-
-// End of a selected-inversion panel step: Z_PP = Z0 + sum of the partials
-// (blockIdx.x == 0, also writing diag(Z_PP) to Rfull), and Z_RP = Y,
-// Z_PR = Y^T (blockIdx.x = 1 + row tile).
-__global__ __launch_bounds__(256) void k_finish(const DFront* __restrict__ fr,
+// End of a selected-inversion panel step.  Per 64-row tile of R: sums the
+// K parts of Y, writes Z_RP = Y and Z_PR = Y^T (over Lhat^T, which only this
+// workgroup still reads) and forms -Lhat^T Y.  WHOLE: one workgroup takes all
+// row tiles of a front and finishes Z_PP = D_P - Lhat^T Y with diag(Z_PP) into
+// Rfull (levels with enough fronts to fill the chip); otherwise blockIdx.x
+// is the row tile and its product goes to `part` for k_zpp.  Bound by the
+// bytes of Y and Lhat; at the root panels of the 4 x 512 x 512 stack 22 us with
+// k_zpp, where separate launches for the sum of the K parts, the product and
+// the write-back took 107 us.
+template <bool WHOLE>
+__global__ __launch_bounds__(256, 2) void k_finish(const DFront* __restrict__ fr,
                                                 const int32_t* __restrict__ list, int nf, int jp,
-                                                double* ar, const double* __restrict__ Z0,
-                                                const double* __restrict__ Ybuf,
-                                                const double* __restrict__ part,
+                                                double* ar, int ysplit,
+                                                const double* __restrict__ Ysp, int64_t ylev,
+                                                double* __restrict__ part,
                                                 const int64_t* __restrict__ piv_node,
                                                 double* __restrict__ Rfull) {
-  __shared__ double Ts[PT][PT + 1];
-  const int t = threadIdx.x;
+  __shared__ double sL[PT][PT + 1], sY[PT][PT + 1];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int cc = lane & 15, kr = lane >> 4;
   for (int fi = blockIdx.y; fi < nf; fi += gridDim.y) {
     const DFront f = fr[list[fi]];
     const int j0 = PT * jp;
@@ -406,36 +403,105 @@ __global__ __launch_bounds__(256) void k_finish(const DFront* __restrict__ fr,
     const int w = min(PT, f.k - j0), r0 = j0 + w, m = f.F - r0;
     const int64_t F = f.F;
     double* base = ar + f.off;
-    if (blockIdx.x == 0) {
-      const double* z0 = Z0 + (size_t)fi * PT * PT;
-      const int ns = m > 0 ? f.nsplit : 0;
-      for (int e = t; e < PT * PT; e += 256) {
-        const int c = e >> 6, r = e & 63;
-        if (r >= w || c >= w) continue;
-        double v = z0[e];
-        for (int s = 0; s < ns; ++s) v += part[f.part + (size_t)s * PT * PT + e];
-        base[(int64_t)(j0 + c) * F + j0 + r] = v;
-        if (r == c) Rfull[piv_node[f.piv + j0 + r]] = v;
+    const int ntile = (m + PT - 1) / PT;
+    d4v acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = d4v{0.0, 0.0, 0.0, 0.0};
+    const int rt0 = WHOLE ? 0 : (int)blockIdx.x, rt1 = WHOLE ? ntile : min(rt0 + 1, ntile);
+    for (int rt = rt0; rt < rt1; ++rt) {
+      const int i0 = rt * PT, rows = min(PT, m - i0);
+      char* y_rp = (char*)(base + (int64_t)j0 * F + r0 + i0);  // (row, p) at [p F + row]
+      char* z_pr = (char*)(base + (int64_t)(r0 + i0) * F + j0);  // (p, row) at [row F + p]
+      // Y: lane = row, wv + 4 e = panel column; Lhat: the reverse.  Byte
+      // offsets from the scalar bases, clamped to the tile's edge.
+      const uint32_t f8 = 8u * (uint32_t)F;
+      auto oy = [&](int e) { return __umul24(min(wv + 4 * e, w - 1), f8) + 8u * min(lane, rows - 1); };
+      auto ol = [&](int e) { return __umul24(min(wv + 4 * e, rows - 1), f8) + 8u * min(lane, w - 1); };
+      double v[16];
+      if (ysplit > 1) {
+        const char* src = (const char*)(Ysp + f.ybuf + i0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = 0.0;
+        for (int s = 0; s < ysplit; ++s, src += 8 * ylev)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) v[e] += *(const double*)(src + oy(e));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = *(const double*)(y_rp + oy(e));
       }
-      continue;
-    }
-    const int rt = (int)blockIdx.x - 1;
-    if (rt * PT >= m) continue;
-    const int rows = min(PT, m - rt * PT);
-    const double* y = Ybuf + f.ybuf + rt * PT;
-    __syncthreads();
-    for (int e = t; e < PT * PT; e += 256) {
-      const int c = e >> 6, r = e & 63;
-      if (r < rows && c < w) {
-        const double v = y[(int64_t)c * F + r];
-        base[(int64_t)(j0 + c) * F + r0 + rt * PT + r] = v;  // Z_RP
-        Ts[c][r] = v;
+      __syncthreads();  // the previous tile's LDS reads are done
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        sY[lane][wv + 4 * e] = lane < rows ? v[e] : 0.0;
+        if (ysplit > 1 && lane < rows && wv + 4 * e < w) *(double*)(y_rp + oy(e)) = v[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = *(const double*)(z_pr + ol(e));
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sL[wv + 4 * e][lane] = v[e];
+      __syncthreads();
+      // entries past w repeat the last column and are not written
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (wv + 4 * e < rows && lane < w) *(double*)(z_pr + ol(e)) = sY[wv + 4 * e][lane];
+#pragma unroll 4
+      for (int ks = 0; ks < PT / 4; ++ks) {
+        const double av = sL[4 * ks + kr][16 * wv + cc];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sY[4 * ks + kr][16 * q + cc], acc[q],
+                                                        0, 0, 0);
       }
     }
+    if (WHOLE) {
+      double* z = base + (int64_t)j0 * F + j0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * wv + kr + 4 * r, j = 16 * q + cc;
+          if (i >= w || j >= w) continue;
+          const double v = z[(int64_t)j * F + i] - acc[q][r];
+          z[(int64_t)j * F + i] = v;
+          if (i == j) Rfull[piv_node[f.piv + j0 + i]] = v;
+        }
+    } else if (rt0 < ntile) {
+      double* pp = part + f.part + (int64_t)rt0 * PT * PT;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pp[(16 * q + cc) * PT + 16 * wv + kr + 4 * r] = acc[q][r];
+    }
     __syncthreads();
-    for (int e = t; e < PT * PT; e += 256) {
-      const int r = e >> 6, c = e & 63;
-      if (r < rows && c < w) base[(int64_t)(r0 + rt * PT + r) * F + j0 + c] = Ts[c][r];  // Z_PR
+  }
+}
+
+// Z_PP = D_P - the row tiles' products, in order (blockIdx.x: a 1024-entry
+// quarter of the tile), diag(Z_PP) into Rfull.
+__global__ __launch_bounds__(256) void k_zpp(const DFront* __restrict__ fr,
+                                             const int32_t* __restrict__ list, int nf, int jp,
+                                             double* ar, const double* __restrict__ part,
+                                             const int64_t* __restrict__ piv_node,
+                                             double* __restrict__ Rfull) {
+  for (int fi = blockIdx.y; fi < nf; fi += gridDim.y) {
+    const DFront f = fr[list[fi]];
+    const int j0 = PT * jp;
+    if (f.k <= j0) continue;
+    const int w = min(PT, f.k - j0), m = f.F - j0 - w, ntile = (m + PT - 1) / PT;
+    double* z = ar + f.off + (int64_t)j0 * f.F + j0;
+    const double* pp = part + f.part + blockIdx.x * 1024 + threadIdx.x;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < ntile; ++s, pp += PT * PT)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += pp[256 * e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int idx = blockIdx.x * 1024 + threadIdx.x + 256 * e, j = idx >> 6, i = idx & 63;
+      if (i >= w || j >= w) continue;
+      const double x = z[(int64_t)j * f.F + i] - v[e];
+      z[(int64_t)j * f.F + i] = x;
+      if (i == j) Rfull[piv_node[f.piv + j0 + i]] = x;
     }
   }
 }
@@ -473,8 +539,8 @@ hipError_t put(Bufs& b, T** out, const std::vector<T>& v, hipStream_t st) {
 }
 
 // The fronts of a level are launched in groups of at most GROUP fronts, so
-// that the per-front scratch of a panel step (tile inverses, Y blocks,
-// partial products) is sized by a group, not by a level of a large forest.
+// that the per-front scratch of a panel step (Y parts, partial products) is
+// sized by a group, not by a level of a large forest.
 constexpr size_t GROUP = 16384;
 
 // One launch group: a contiguous range of a level's front list.
@@ -483,10 +549,11 @@ struct GroupDev {
   int nf = 0;
   int max_panels = 0;
   int ysplit = 1;        // K parts of the Y product
-  int64_t ylev = 0;      // doubles of the group's Y buffer
-  int64_t part = 0;      // doubles of its partial products
+  int64_t ylev = 0;      // doubles of one K part's Y buffer
+  bool whole = true;     // k_finish<true>: one workgroup per front
+  int64_t part = 0;      // doubles of the row tiles' partial products (else)
   int64_t maxq = 0;      // largest update set
-  std::vector<int> mt, ms;  // per panel: row tiles after it, K parts of its partials
+  std::vector<int> mt;   // per panel: row tiles after it
 };
 
 struct LevelDev {
@@ -537,7 +604,16 @@ int group_ysplit(const SelinvPlan& P, const int32_t* fronts, size_t nf, int64_t 
   return (int)std::max<int64_t>(1, sp);
 }
 
-int front_nsplit(const SnFront& f) { return std::min(16, std::max(1, (f.F + 255) / 256)); }
+// Row tiles after a front's first panel.
+int64_t front_tiles(const SnFront& f) {
+  return f.k > 0 ? (f.F - std::min(PT, f.k) + PT - 1) / PT : 0;
+}
+
+// One workgroup finishes a whole front's panel where a launch has a
+// workgroup for every CU that way or the fronts have at most two row tiles (a
+// second launch would cost more than the tiles side by side save).
+constexpr int WHOLE_FRONTS = 512;
+constexpr int WHOLE_TILES = 2;
 
 // The launch groups of every level, with their scratch sizes.
 std::vector<std::vector<GroupDev>> plan_groups(const SelinvPlan& P) {
@@ -552,20 +628,20 @@ std::vector<std::vector<GroupDev>> plan_groups(const SelinvPlan& P) {
         const SnFront& f = P.fronts[(size_t)L.fronts[b + (size_t)j]];
         g.max_panels = std::max(g.max_panels, (f.k + PT - 1) / PT);
         g.ylev += (int64_t)f.F * PT;
-        g.part += (int64_t)front_nsplit(f) * PT * PT;
+        g.part += front_tiles(f) * PT * PT;
         g.maxq = std::max<int64_t>(g.maxq, (int64_t)(f.F - f.k));
       }
       g.mt.assign((size_t)g.max_panels, 0);
-      g.ms.assign((size_t)g.max_panels, 0);
       for (int j = 0; j < g.nf; ++j) {
         const SnFront& f = P.fronts[(size_t)L.fronts[b + (size_t)j]];
         for (int jp = 0; PT * jp < f.k; ++jp) {
           const int m = f.F - PT * jp - std::min(PT, f.k - PT * jp);
           g.mt[(size_t)jp] = std::max(g.mt[(size_t)jp], (m + PT - 1) / PT);
-          g.ms[(size_t)jp] = std::max(g.ms[(size_t)jp], front_nsplit(f));
         }
       }
       g.ysplit = group_ysplit(P, L.fronts.data() + b, (size_t)g.nf, g.ylev);
+      g.whole = g.nf >= WHOLE_FRONTS || g.max_panels == 0 || g.mt[0] <= WHOLE_TILES;
+      if (g.whole) g.part = 0;
       out[d].push_back(std::move(g));
     }
   }
@@ -574,7 +650,7 @@ std::vector<std::vector<GroupDev>> plan_groups(const SelinvPlan& P) {
 
 // Scratch sizes of a plan on the device, in doubles / bytes.
 struct SelinvSizes {
-  int64_t tiles = 0, ybuf = 0, part = 0, ysp = 0;
+  int64_t part = 0, ysp = 0;
   int64_t bytes = 0;
 };
 
@@ -582,14 +658,12 @@ SelinvSizes selinv_sizes(const SelinvPlan& P) {
   SelinvSizes z;
   for (const auto& lev : plan_groups(P))
     for (const GroupDev& g : lev) {
-      z.tiles = std::max<int64_t>(z.tiles, (int64_t)g.nf * PT * PT);
-      z.ybuf = std::max(z.ybuf, g.ylev);
       z.part = std::max(z.part, g.part);
       if (g.ysplit > 1) z.ysp = std::max(z.ysp, g.ysplit * g.ylev);
     }
   int64_t ent = 0;
   for (const SelinvLevel& L : P.levels) ent += (int64_t)L.ent_idx.size();
-  z.bytes = 8 * (P.arena + 2 * z.tiles + z.ybuf + z.part + z.ysp + P.n) + 16 * ent +
+  z.bytes = 8 * (P.arena + z.part + z.ysp + P.n) + 16 * ent +
             (int64_t)sizeof(DFront) * (int64_t)P.fronts.size() + 4 * (int64_t)P.rel.size() +
             8 * (int64_t)P.piv_node.size();
   return z;
@@ -616,8 +690,7 @@ size_t aligned(size_t b) { return (std::max<size_t>(b, 1) + ALIGN - 1) / ALIGN *
 struct SelinvDevice {
   std::vector<LevelDev> lv;
   SelinvSizes sz;
-  double *ar = nullptr, *Li = nullptr, *Z0 = nullptr, *Yb = nullptr, *part = nullptr;
-  double *Ysp = nullptr, *Rfull = nullptr, *vals = nullptr;
+  double *ar = nullptr, *part = nullptr, *Ysp = nullptr, *Rfull = nullptr, *vals = nullptr;
   int64_t *idx = nullptr, *piv = nullptr;
   int32_t *rel = nullptr, *dl = nullptr;
   DFront* dF = nullptr;
@@ -718,12 +791,10 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
         x.k = f.k;
         x.pF = f.parent >= 0 ? P.fronts[(size_t)f.parent].F : 0;
         x.rank = f.rank;
-        x.nsplit = front_nsplit(f);
-        x.pad_ = 0;
         x.ybuf = yb;
         x.part = pa;
         yb += (int64_t)f.F * PT;
-        pa += (int64_t)x.nsplit * PT * PT;
+        pa += front_tiles(f) * PT * PT;
       }
       g.list_off += lbase;
     }
@@ -733,8 +804,7 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
   hipError_t e = hipSuccess;
   if (use_cache) {
     const SelinvSizes& z = D->sz;
-    const size_t total = aligned(8 * (size_t)P.arena) + 2 * aligned(8 * (size_t)z.tiles) +
-                         aligned(8 * (size_t)z.ybuf) + aligned(8 * (size_t)z.part) +
+    const size_t total = aligned(8 * (size_t)P.arena) + aligned(8 * (size_t)z.part) +
                          aligned(8 * (size_t)z.ysp) + aligned(8 * (size_t)P.n) + aligned(4) +
                          2 * aligned(8 * (size_t)n_ent) + aligned(8 * P.piv_node.size()) +
                          aligned(4 * P.rel.size()) + aligned(4 * lists.size()) +
@@ -743,9 +813,6 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
     e = D->reserve(total, cached);
   }
   if (e == hipSuccess) e = D->get(&D->ar, (size_t)P.arena);
-  if (e == hipSuccess) e = D->get(&D->Li, (size_t)D->sz.tiles);
-  if (e == hipSuccess) e = D->get(&D->Z0, (size_t)D->sz.tiles);
-  if (e == hipSuccess) e = D->get(&D->Yb, (size_t)D->sz.ybuf);
   if (e == hipSuccess) e = D->get(&D->part, (size_t)D->sz.part);
   if (e == hipSuccess) e = D->get(&D->Ysp, (size_t)D->sz.ysp);
   if (e == hipSuccess) e = D->get(&D->Rfull, (size_t)P.n);
@@ -791,7 +858,7 @@ std::shared_ptr<SelinvDevice> selinv_device_of(reff_pdn_t* p, const SelinvPlan& 
 reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t st_,
                        std::chrono::steady_clock::time_point& t_fact,
                        const std::vector<uint8_t>* need = nullptr) {
-  double *ar = D.ar, *Li = D.Li, *Z0 = D.Z0, *Yb = D.Yb, *part = D.part, *Ysp = D.Ysp;
+  double *ar = D.ar, *part = D.part, *Ysp = D.Ysp;
   double* Rfull = D.Rfull;
   const int32_t *rel = D.rel, *dl = D.dl;
   const DFront* dF = D.dF;
@@ -821,15 +888,13 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
     for (const GroupDev& G : V.groups) {
       const int32_t* l = dl + G.list_off;
       for (int jp = 0; jp < G.max_panels; ++jp) {
-        hipLaunchKernelGGL(k_tile<true>, dim3(gy(G.nf)), dim3(256), 0, st_, dF, l, G.nf, jp, ar,
-                           Li, Z0, bad);
+        hipLaunchKernelGGL(k_tile, dim3(gy(G.nf)), dim3(256), 0, st_, dF, l, G.nf, jp, ar, bad);
         const int mt = G.mt[(size_t)jp];
         if (mt == 0) continue;
-        hipLaunchKernelGGL(k_front_gemm<OP_TRSM>, dim3((unsigned)mt, gy(G.nf)), dim3(256), 0,
-                           st_, dF, l, G.nf, jp, ar, Li, Yb, part, mt, 1, Ysp, (int64_t)0);
-        hipLaunchKernelGGL(k_front_gemm<OP_SYRK>, dim3((unsigned)(mt * (mt + 1) / 2), gy(G.nf)),
-                           dim3(256), 0, st_, dF, l, G.nf, jp, ar, Li, Yb, part, mt, 1, Ysp,
-                           (int64_t)0);
+        hipLaunchKernelGGL(k_front_gemm<OP_LHAT>, dim3((unsigned)mt, gy(G.nf)), dim3(256), 0,
+                           st_, dF, l, G.nf, jp, ar, mt, 1, Ysp, (int64_t)0);
+        hipLaunchKernelGGL(k_front_gemm<OP_UPDATE>, dim3((unsigned)(mt * (mt + 1) / 2), gy(G.nf)),
+                           dim3(256), 0, st_, dF, l, G.nf, jp, ar, mt, 1, Ysp, (int64_t)0);
       }
     }
     e = hipGetLastError();
@@ -838,7 +903,7 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
   if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st_);
   if (e == hipSuccess) e = hipStreamSynchronize(st_);
   if (e != hipSuccess) return dev_status(e, "selected inversion: factorisation");
-  if (hbad) return host_fail(REFF_ERR_DEVICE, "sparse Cholesky: a pivot was not positive");
+  if (hbad) return host_fail(REFF_ERR_DEVICE, "sparse factorisation: a pivot was not positive");
   t_fact = std::chrono::steady_clock::now();
   // With a request, the selected inversion visits only the needed fronts:
   // each launch group runs over the compacted list of its needed fronts
@@ -881,23 +946,21 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
         hipLaunchKernelGGL(k_gather, dim3(gx, gy(nfa)), dim3(256), 0, st_, dF, l, nfa, rel, ar);
       }
       for (int jp = G.max_panels - 1; jp >= 0; --jp) {
-        const int mt = G.mt[(size_t)jp], ms = G.ms[(size_t)jp];
-        hipLaunchKernelGGL(k_tile<false>, dim3(gy(nfa)), dim3(256), 0, st_, dF, l, nfa, jp, ar,
-                           Li, Z0, bad);
-        if (mt > 0) {
-          hipLaunchKernelGGL(k_front_gemm<OP_LHAT>, dim3((unsigned)mt, gy(nfa)), dim3(256), 0,
-                             st_, dF, l, nfa, jp, ar, Li, Yb, part, mt, 1, Ysp, (int64_t)0);
+        const int mt = G.mt[(size_t)jp];
+        if (mt > 0)
           hipLaunchKernelGGL(k_front_gemm<OP_Y>, dim3((unsigned)(mt * G.ysplit), gy(nfa)),
-                             dim3(256), 0, st_, dF, l, nfa, jp, ar, Li, Yb, part, mt, G.ysplit,
-                             Ysp, G.ylev);
-          if (G.ysplit > 1)
-            hipLaunchKernelGGL(k_ysum, dim3((unsigned)mt, gy(nfa)), dim3(256), 0, st_, dF, l,
-                               nfa, jp, G.ysplit, (const double*)Ysp, G.ylev, Yb);
-          hipLaunchKernelGGL(k_front_gemm<OP_PART>, dim3((unsigned)ms, gy(nfa)), dim3(256), 0,
-                             st_, dF, l, nfa, jp, ar, Li, Yb, part, mt, 1, Ysp, (int64_t)0);
+                             dim3(256), 0, st_, dF, l, nfa, jp, ar, mt, G.ysplit, Ysp, G.ylev);
+        if (G.whole) {
+          hipLaunchKernelGGL(k_finish<true>, dim3(1, gy(nfa)), dim3(256), 0, st_, dF, l, nfa, jp, ar,
+                             G.ysplit, (const double*)Ysp, G.ylev, part, D.piv, Rfull);
+        } else {
+          if (mt > 0)
+            hipLaunchKernelGGL(k_finish<false>, dim3((unsigned)mt, gy(nfa)), dim3(256), 0, st_, dF,
+                               l, nfa, jp, ar, G.ysplit, (const double*)Ysp, G.ylev, part, D.piv,
+                               Rfull);
+          hipLaunchKernelGGL(k_zpp, dim3(4, gy(nfa)), dim3(256), 0, st_, dF, l, nfa, jp, ar,
+                             (const double*)part, D.piv, Rfull);
         }
-        hipLaunchKernelGGL(k_finish, dim3((unsigned)(1 + mt), gy(nfa)), dim3(256), 0, st_, dF,
-                           l, nfa, jp, ar, Z0, Yb, part, D.piv, Rfull);
       }
     }
     e = hipGetLastError();
