@@ -76,7 +76,10 @@ constexpr int KS = 32;  // K slice staged through LDS
 //   B(kk, j) = TB ? B[kk ldb + j] : B[j ldb + kk]
 //   C(i, j)  at TC ? C[i ldc + j] : C[j ldc + i]
 // With LOWER, entries above the diagonal are not written.  Four waves;
-// wave w owns tile rows 16 w .. 16 w + 15 as four 16 x 16 accumulators.
+// wave w owns tile rows 16 w .. 16 w + 15 as four 16 x 16 accumulators, each
+// held with the lanes along C's contiguous index (for !TC the product is
+// formed transposed): a load or store of C then covers whole 128-byte lines,
+// four columns at a time, instead of 32 bytes in each of sixteen columns.
 // K goes through LDS 32 at a time, the next slice's loads in flight (in
 // registers) while the matrix cores work on the current one; with ADD the
 // tile of C is loaded before the products (a panel step has only two slices,
@@ -117,6 +120,9 @@ __device__ __forceinline__ void gemm_tile(int i0, int j0, int M, int N, int kb, 
   auto at = [&](int i, int j) -> double* {
     return (double*)(pc + (TC ? __umul24(i, lc) + 8u * j : __umul24(j, lc) + 8u * i));
   };
+  // entry r of accumulator q within the tile
+  auto row = [&](int r) { return 16 * w + (TC ? kr + 4 * r : cc); };
+  auto col = [&](int q, int r) { return 16 * q + (TC ? cc : kr + 4 * r); };
   if (kb < ke) load(kb);
   double cv[4][4];
   if (ADD) {
@@ -124,7 +130,7 @@ __device__ __forceinline__ void gemm_tile(int i0, int j0, int M, int N, int kb, 
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        cv[q][r] = *at(min(16 * w + kr + 4 * r, mr), min(16 * q + cc, nr));
+        cv[q][r] = *at(min(row(r), mr), min(col(q, r), nr));
   }
   for (int k0 = kb; k0 < ke; k0 += KS) {
     __syncthreads();
@@ -140,16 +146,17 @@ __device__ __forceinline__ void gemm_tile(int i0, int j0, int M, int N, int kb, 
     for (int ks = 0; ks < KS / 4; ++ks) {
       const double av = sA[16 * w + cc][4 * ks + kr];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sB[4 * ks + kr][16 * q + cc], acc[q],
-                                                      0, 0, 0);
+      for (int q = 0; q < 4; ++q) {
+        const double bv = sB[4 * ks + kr][16 * q + cc];
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(TC ? av : bv, TC ? bv : av, acc[q], 0, 0, 0);
+      }
     }
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = 16 * w + kr + 4 * r, j = 16 * q + cc;
+      const int i = row(r), j = col(q, r);
       if (i <= mr && j <= nr && !(LOWER && i0 + i < j0 + j))
         *at(i, j) = ADD ? cv[q][r] + alpha * acc[q][r] : alpha * acc[q][r];
     }
