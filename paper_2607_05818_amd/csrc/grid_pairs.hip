@@ -487,17 +487,24 @@ bool grid_use_table(int M, int N, int64_t P) {
   return table <= DIRECT_COST * direct;
 }
 
-hipError_t grid_tiers_device(int M, int N, int nt, const double* drs, const GridRect* rects,
-                             int nrect, hipStream_t st) {
-  // as many tiers at once as 8 GiB of tables hold
+// Tiers that share one launch: as many as 8 GiB of tables hold.
+static int grid_tier_group(int M, int N, int nt) {
   const size_t nf = (size_t)(M + 1) * (N + 1);
-  const int ng = (int)std::min<size_t>(nt, std::max<size_t>(1, ((size_t)8 << 30) / (16 * nf)));
-  char* base = nullptr;
-  hipError_t e = hipMalloc((void**)&base, grid_table_bytes(M, N, ng));
-  if (e != hipSuccess) return e;
+  return (int)std::min<size_t>(nt, std::max<size_t>(1, ((size_t)8 << 30) / (16 * nf)));
+}
+
+size_t grid_tiers_bytes(int M, int N, int nt) {
+  return grid_table_bytes(M, N, grid_tier_group(M, N, nt));
+}
+
+hipError_t grid_tiers_launch(int M, int N, int nt, const double* drs, const GridRect* rects,
+                             int nrect, char* work, hipStream_t st) {
+  const size_t nf = (size_t)(M + 1) * (N + 1);
+  const int ng = grid_tier_group(M, N, nt);
+  hipError_t e = hipSuccess;
   for (int t0 = 0; t0 < nt && e == hipSuccess; t0 += ng) {
     const int cnt = std::min(ng, nt - t0);
-    const GridTables g = grid_table_carve(base, M, N, cnt);
+    const GridTables g = grid_table_carve(work, M, N, cnt);
     e = grid_table_launch(M, N, cnt, drs + 2 * t0, g, st);
     for (int k = 0; k < nrect && e == hipSuccess; ++k) {
       const GridRect& q = rects[k];
@@ -506,9 +513,7 @@ hipError_t grid_tiers_device(int M, int N, int nt, const double* drs, const Grid
                            g.F + (q.tier - t0) * nf, q.out, st);
     }
   }
-  const hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(base);
-  return e == hipSuccess ? e2 : e;
+  return e;
 }
 
 // All-pairs Eq. 3 resistances of P points already in device memory, by the

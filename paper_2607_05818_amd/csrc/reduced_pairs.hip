@@ -25,15 +25,15 @@
 // The factorisation works on that subspace (null-space method): per
 // interface the last TSV's current is eliminated, I^a = Z u^a + g_a e_p with
 // Z = [I_{p-1}; -1^T], so H_Z = Z^T H Z ((p-1)(d-1) square, symmetric
-// positive definite) takes a Cholesky factorisation, u = H_Z^-1 Z^T
+// positive definite) takes a block LDL^T factorisation, u = H_Z^-1 Z^T
 // (f - H E g), and the voltage differences follow from the last row of each
 // interface, y_a = f_(a,p-1) - (H I)_(a,p-1).  The paper decomposes C by LU
 // (its Sec. IV); the answer is the same, the symmetric positive definite
 // form needs no pivoting.
 //
-// The dense float64 work (Cholesky, triangular solves with many right-hand
-// sides, the cross-term product) runs as 64 x 64 tiles on the float64
-// matrix cores (v_mfma_f64_16x16x4).
+// The dense float64 work (factorisation with the forward elimination of every
+// right-hand side, back substitution, the cross-term product) runs as 64 x 64
+// tiles on the float64 matrix cores (v_mfma_f64_16x16x4).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -43,6 +43,7 @@
 #include <vector>
 
 #include "reff_internal.h"
+#include "tile_inverse.h"
 
 namespace reff {
 namespace {
@@ -51,20 +52,14 @@ constexpr int TB = 64;  // tile edge of the dense kernels
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-// C[M x N] = alpha op(A) op(B) + beta C (float64, row-major, leading
-// dimensions lda / ldb / ldc); op(A)(i, k) = ta ? A[k lda + i] : A[i lda + k],
-// op(B)(k, j) = tb ? B[j ldb + k] : B[k ldb + j].  With `lower`, only tiles
-// whose first row is at or below their first column are computed (the lower
-// triangle of a square update).  One workgroup (four waves) per 64 x 64 tile
-// of C; wave w owns rows 16 w .. 16 w + 15, as four 16 x 16 matrix-core
-// accumulators; the K range is staged through LDS 16 at a time.
-__global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, double alpha,
-                                                const double* __restrict__ A, int64_t lda, int ta,
-                                                const double* __restrict__ B, int64_t ldb, int tb,
-                                                double beta, double* __restrict__ Cm, int64_t ldc,
-                                                int lower) {
+// C[M x N] = A B^T (float64, row-major, leading dimensions lda / ldb / ldc).
+// One workgroup (four waves) per 64 x 64 tile of C; wave w owns rows 16 w ..
+// 16 w + 15, as four 16 x 16 matrix-core accumulators; the K range is staged
+// through LDS 16 at a time.
+__global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, const double* __restrict__ A,
+                                                int64_t lda, const double* __restrict__ B,
+                                                int64_t ldb, double* __restrict__ Cm, int64_t ldc) {
   const int i0 = blockIdx.y * TB, j0 = blockIdx.x * TB;
-  if (lower && i0 + TB - 1 < j0) return;
   __shared__ double sA[TB][17], sB[16][TB + 1];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int cc = lane & 15, kr = lane >> 4;
@@ -75,19 +70,10 @@ __global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, double alph
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int idx = t + 256 * e;   // 0 .. 1023
-      // A tile: 64 rows x 16 k (k fastest for the row-major case)
-      const int ar = ta ? idx % TB : idx / 16, ak = ta ? idx / TB : idx % 16;
-      const int gi = i0 + ar, gk = k0 + ak;
-      double va = 0.0;
-      if (gi < M && gk < K) va = ta ? A[(int64_t)gk * lda + gi] : A[(int64_t)gi * lda + gk];
-      sA[ar][ak] = va;
-      // B tile: 16 k x 64 columns
-      const int bk = tb ? idx % 16 : idx / TB, bc = tb ? idx / 16 : idx % TB;
-      const int gj = j0 + bc, gk2 = k0 + bk;
-      double vb = 0.0;
-      if (gj < N && gk2 < K) vb = tb ? B[(int64_t)gj * ldb + gk2] : B[(int64_t)gk2 * ldb + gj];
-      sB[bk][bc] = vb;
+      const int idx = t + 256 * e;  // 0 .. 1023: 64 rows x 16 k, k fastest
+      const int r = idx / 16, k = idx % 16, gk = k0 + k;
+      sA[r][k] = i0 + r < M && gk < K ? A[(int64_t)(i0 + r) * lda + gk] : 0.0;
+      sB[k][r] = j0 + r < N && gk < K ? B[(int64_t)(j0 + r) * ldb + gk] : 0.0;
     }
     __syncthreads();
 #pragma unroll
@@ -104,62 +90,174 @@ __global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, double alph
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int gi = i0 + 16 * w + kr + 4 * r, gj = j0 + 16 * q + cc;
-      if (gi < M && gj < N) {
-        double* c = &Cm[(int64_t)gi * ldc + gj];
-        *c = alpha * acc[q][r] + (beta != 0.0 ? beta * *c : 0.0);
-      }
+      if (gi < M && gj < N) Cm[(int64_t)gi * ldc + gj] = acc[q][r];
     }
 }
 
-// Cholesky factor of the diagonal tile kt of A (n x n, row-major, lda), in
-// LDS: L_kk (written into L, zero above the diagonal) and its inverse
-// (Linv[kt][64][64]).  Rows and columns past n are padded with the
-// identity.  A pivot that is not positive sets *bad.
-__global__ __launch_bounds__(256) void k_potrf_tile(int n, int kt, const double* __restrict__ A,
-                                                    int64_t lda, double* __restrict__ L,
-                                                    double* __restrict__ Linv, int* bad) {
-  __shared__ double T[TB][TB + 1], X[TB][TB + 1];
-  const int t = threadIdx.x, o = kt * TB;
-  const int nb = min(TB, n - o);
-  for (int e = t; e < TB * TB; e += 256) {
-    const int i = e / TB, j = e % TB;
-    T[i][j] = (i < nb && j < nb) ? A[(int64_t)(o + i) * lda + (o + j)] : (i == j ? 1.0 : 0.0);
+// ---- H_Z u = rhs for all right-hand sides, 64-row panels.
+//
+// With D_P = A_PP^-1 of panel P (after the panels before it), eliminating P
+// subtracts A_iP D_P [A_jP^T, b_P] from the trailing blocks A_ij and from the
+// right-hand sides b_i, and u_P = D_P (b_P - sum_{R after P} A_RP^T u_R): the
+// unscaled A_RP stays in place, and no factor is formed.  A panel is one
+// launch each way.  A workgroup recomputes its 64 x 64 operand D_P X (twice
+// the products of a kept one, against a launch per panel and a pass over it),
+// and the one that updates the next diagonal tile inverts it on the spot: the
+// serial chain is one tile inverse and two tile products per panel.  4 x 512
+// x 512 with 512 TSVs (1533 unknowns, 2176 right-hand sides): 7.2 ms as 164
+// launches of Cholesky, panel and update steps before.
+
+// Loads the 64 x 64 tile at (i0, j0) of a row-major matrix (rows < M, columns
+// < N; zero outside) into LDS, transposed with TR.
+template <bool TR>
+__device__ __forceinline__ void stage_tile(const double* __restrict__ A, int64_t lda, int i0,
+                                           int j0, int M, int N, double (*T)[TB + 1]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double v[16];
+  const bool cok = j0 + lane < N;
+  const double* a = A + (int64_t)i0 * lda + j0 + (cok ? lane : 0);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = wv + 4 * e;
+    v[e] = cok && i0 + r < M ? a[(int64_t)r * lda] : 0.0;
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = wv + 4 * e;
+    if (TR)
+      T[lane][r] = v[e];
+    else
+      T[r][lane] = v[e];
+  }
+}
+
+// acc = L R of two tiles in LDS (64 x 64 x 64); wave w: rows 16 w .. 16 w + 15.
+__device__ __forceinline__ void tile_product(const double (*L)[TB + 1], const double (*R)[TB + 1],
+                                             d4v* acc) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = d4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < TB / 4; ++ks) {
+    const double a = L[16 * w + cc][4 * ks + kr];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, R[4 * ks + kr][16 * q + cc], acc[q], 0, 0, 0);
+  }
+}
+
+// Inverts the diagonal tile at row o held in T (identity beyond nb rows)
+// into D[kt].
+__device__ __forceinline__ void finish_diagonal(double (*T)[TB + 1], double (*Cp)[17], int nb,
+                                                double* __restrict__ D, int* bad) {
+  invert_tile(T, Cp, nb, bad);
+  for (int e = threadIdx.x; e < TB * TB; e += 256) D[e] = T[e >> 6][e & 63];
+}
+
+// D[0] = A_00^-1.
+__global__ __launch_bounds__(256) void k_ldl_first(int n, const double* __restrict__ A,
+                                                   double* __restrict__ D, int* bad) {
+  __shared__ double T[TB][TB + 1], Cp[TB][17];
+  const int nb = min(TB, n);
+  for (int e = threadIdx.x; e < TB * TB; e += 256) {
+    const int i = e >> 6, j = e & 63;
+    T[i][j] = i < nb && j < nb ? A[(int64_t)i * n + j] : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
-  for (int j = 0; j < TB; ++j) {
-    const double piv = T[j][j];
-    __syncthreads();
-    if (t == 0) {
-      if (!(piv > 0.0) || !std::isfinite(piv)) atomicOr(bad, 1);
-      T[j][j] = sqrt(fmax(piv, 1e-300));
-    }
-    __syncthreads();
-    const double djj = T[j][j];
-    for (int i = j + 1 + t; i < TB; i += 256) T[i][j] /= djj;
-    __syncthreads();
-    for (int e = t; e < TB * TB; e += 256) {
-      const int i = e / TB, k = e % TB;
-      if (k > j && i >= k) T[i][k] -= T[i][j] * T[k][j];
-    }
-    __syncthreads();
-  }
-  // inverse of the lower-triangular factor, one column per thread:
-  // forward substitution L X = I
-  if (t < TB) {
-    const int c = t;
-    for (int i = 0; i < TB; ++i) {
-      double v = (i == c) ? 1.0 : 0.0;
-      for (int k = c; k < i; ++k) v -= T[i][k] * X[k][c];
-      X[i][c] = (i < c) ? 0.0 : v / T[i][i];
-    }
-  }
+  finish_diagonal(T, Cp, nb, D, bad);
+}
+
+// Eliminates panel kt (a full one: there are rows after it).  blockIdx.y =
+// row tile after the panel; blockIdx.x = column tile after the panel (lower
+// tiles only) or, past those, tile of the right-hand sides.
+__global__ __launch_bounds__(256, 2) void k_ldl_step(int n, int kt, int ntile, double* __restrict__ A,
+                                                     double* __restrict__ D, int ne,
+                                                     double* __restrict__ rhs, int* bad) {
+  __shared__ double S0[TB][TB + 1], S1[TB][TB + 1], Cp[TB][17];
+  const int rest = ntile - 1 - kt, ti = kt + 1 + blockIdx.y;
+  const bool mat = (int)blockIdx.x < rest;
+  if (mat && blockIdx.x > blockIdx.y) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
+  const int p0 = kt * TB, i0 = ti * TB;
+  const int j0 = mat ? (kt + 1 + (int)blockIdx.x) * TB : ((int)blockIdx.x - rest) * TB;
+  const int N = mat ? n : ne;
+  double* C = mat ? A : rhs;
+  // D_P X, X = A_jP^T or b_P
+  stage_tile<false>(D + (size_t)kt * TB * TB, TB, 0, 0, TB, TB, S0);
+  if (mat)
+    stage_tile<true>(A, n, j0, p0, n, n, S1);
+  else
+    stage_tile<false>(rhs, ne, p0, j0, n, ne, S1);
   __syncthreads();
-  double* Li = Linv + (size_t)kt * TB * TB;
-  for (int e = t; e < TB * TB; e += 256) {
-    const int i = e / TB, j = e % TB;
-    Li[e] = X[i][j];
-    if (i < nb && j < nb) L[(int64_t)(o + i) * lda + (o + j)] = (j <= i) ? T[i][j] : 0.0;
+  d4v acc[4];
+  tile_product(S0, S1, acc);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) S1[16 * w + kr + 4 * r][16 * q + cc] = acc[q][r];
+  stage_tile<false>(A, n, i0, p0, n, n, S0);  // A_iP
+  __syncthreads();
+  tile_product(S0, S1, acc);
+  const bool next = mat && blockIdx.x == 0 && blockIdx.y == 0;
+  if (next) __syncthreads();  // S0 becomes the next diagonal tile
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * w + kr + 4 * r, j = 16 * q + cc;
+      const bool ok = i0 + i < n && j0 + j < N;
+      double v = i == j ? 1.0 : 0.0;
+      if (ok) {
+        double* c = &C[(int64_t)(i0 + i) * N + j0 + j];
+        v = *c - acc[q][r];
+        *c = v;
+      }
+      if (next) S0[i][j] = v;
+    }
+  if (next) {
+    __syncthreads();
+    finish_diagonal(S0, Cp, min(TB, n - i0), D + (size_t)(kt + 1) * TB * TB, bad);
   }
+}
+
+// Back substitution of panel kt: u_P = D_P b_P (blockIdx.y == kt, into U),
+// b_i -= A_Pi^T u_P for the row tiles i before it; blockIdx.x = tile of the
+// right-hand sides.
+__global__ __launch_bounds__(256, 2) void k_ldl_back(int n, int kt, const double* __restrict__ A,
+                                                     const double* __restrict__ D, int ne,
+                                                     double* __restrict__ rhs,
+                                                     double* __restrict__ U) {
+  __shared__ double S0[TB][TB + 1], S1[TB][TB + 1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
+  const int p0 = kt * TB, i0 = (int)blockIdx.y * TB, j0 = (int)blockIdx.x * TB;
+  const bool own = (int)blockIdx.y == kt;
+  stage_tile<false>(D + (size_t)kt * TB * TB, TB, 0, 0, TB, TB, S0);
+  stage_tile<false>(rhs, ne, p0, j0, n, ne, S1);
+  __syncthreads();
+  d4v acc[4];
+  tile_product(S0, S1, acc);
+  if (!own) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) S1[16 * w + kr + 4 * r][16 * q + cc] = acc[q][r];
+    stage_tile<true>(A, n, p0, i0, n, n, S0);  // A_Pi^T
+    __syncthreads();
+    tile_product(S0, S1, acc);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 16 * w + kr + 4 * r, j = j0 + 16 * q + cc;
+      if (i >= n || j >= ne) continue;
+      if (own)
+        U[(int64_t)i * ne + j] = acc[q][r];
+      else
+        rhs[(int64_t)i * ne + j] -= acc[q][r];
+    }
 }
 
 // H entry between TSV k of interface b and TSV j of interface a (0-based
@@ -334,28 +432,33 @@ __global__ __launch_bounds__(256) void k_reduced_finish(int m, int n,
 
 dim3 rgrid(int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)); }
 
-hipError_t gemm(hipStream_t st, int M, int N, int K, double alpha, const double* A, int64_t lda,
-                int ta, const double* B, int64_t ldb, int tb, double beta, double* C, int64_t ldc,
-                int lower = 0) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gemm64, dim3((unsigned)((N + TB - 1) / TB), (unsigned)((M + TB - 1) / TB)),
-                     dim3(256), 0, st, M, N, K, alpha, A, lda, ta, B, ldb, tb, beta, C, ldc, lower);
-  return hipGetLastError();
-}
-
-// Device buffers of one call, released together.
-struct Bufs {
-  std::vector<void*> ptrs;
-  ~Bufs() {
-    for (void* p : ptrs) (void)hipFree(p);
-  }
+// Device memory of one call: the arrays are named first, then carved from
+// one allocation.
+struct Carve {
+  struct Part {
+    void** p;
+    size_t bytes;
+  };
+  std::vector<Part> parts;
+  char* base = nullptr;
   template <typename T>
-  hipError_t get(T** out, size_t count) {
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
-    if (e == hipSuccess) ptrs.push_back(p);
-    *out = (T*)p;
-    return e;
+  void add(T** out, size_t count) {
+    parts.push_back(Part{(void**)out, (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256});
+  }
+  hipError_t alloc() {
+    size_t total = 0;
+    for (const Part& q : parts) total += q.bytes;
+    const hipError_t e = hipMalloc((void**)&base, total);
+    if (e != hipSuccess) return e;
+    char* at = base;
+    for (const Part& q : parts) {
+      *q.p = at;
+      at += q.bytes;
+    }
+    return hipSuccess;
+  }
+  ~Carve() {
+    if (base) (void)hipFree(base);
   }
 };
 
@@ -408,39 +511,54 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   };
   const int q = p - 1, nz = q * (d - 1), ne = (int)(m + n);
   const int ntile = (nz + TB - 1) / TB;
-  Bufs bufs;
-  // the cosine tables of all tiers, or (few endpoints on a very large tier)
-  // direct products tier by tier through a P x P array
-  bool table = grid_use_table(nx, ny, std::max(P0, Pd));
-  const size_t npts = table ? (size_t)(p + m + n) : (size_t)std::max(P0, Pd);
+  // the cosine tables of all tiers, or (few endpoints on a very large tier, or
+  // no room for the tables) direct products tier by tier through a P x P array
+  const size_t Pm = (size_t)std::max(P0, Pd);
   int32_t* dxy = nullptr;
   double* drs = nullptr;
+  char* tab = nullptr;
   double *dR = nullptr, *RT = nullptr, *rt = nullptr, *Rs1 = nullptr, *Rsd = nullptr;
-  double *HZ = nullptr, *L = nullptr, *Linv = nullptr, *rhs = nullptr, *Y = nullptr;
+  double *HZ = nullptr, *D = nullptr, *rhs = nullptr, *U = nullptr;
   double *Icur = nullptr, *selfv = nullptr, *cA = nullptr, *cB = nullptr, *G = nullptr;
   double* dout = nullptr;
   int* bad = nullptr;
-  hipError_t e = bufs.get(&dxy, 2 * npts);
-  if (e == hipSuccess) e = bufs.get(&drs, 2 * (size_t)d);
-  if (e == hipSuccess && !table) e = bufs.get(&dR, npts * npts);
-  if (e == hipSuccess) e = bufs.get(&RT, (size_t)d * p * p);
-  if (e == hipSuccess) e = bufs.get(&rt, (size_t)p * (d - 1));
-  if (e == hipSuccess) e = bufs.get(&Rs1, (size_t)m * p);
-  if (e == hipSuccess) e = bufs.get(&Rsd, (size_t)n * p);
-  if (e == hipSuccess) e = bufs.get(&HZ, (size_t)nz * nz);
-  if (e == hipSuccess) e = bufs.get(&L, (size_t)nz * nz);
-  if (e == hipSuccess) e = bufs.get(&Linv, (size_t)ntile * TB * TB);
-  if (e == hipSuccess) e = bufs.get(&rhs, (size_t)nz * ne);
-  if (e == hipSuccess) e = bufs.get(&Y, (size_t)nz * ne);
-  if (e == hipSuccess) e = bufs.get(&Icur, (size_t)ne * p * (d - 1));
-  if (e == hipSuccess) e = bufs.get(&selfv, (size_t)ne);
-  if (e == hipSuccess) e = bufs.get(&cA, (size_t)m * 2 * p);
-  if (e == hipSuccess) e = bufs.get(&cB, (size_t)n * 2 * p);
-  if (e == hipSuccess) e = bufs.get(&G, (size_t)m * n);
-  if (e == hipSuccess) e = bufs.get(&bad, 1);
-  if (e == hipSuccess && !out_on_device) e = bufs.get(&dout, (size_t)m * n);
+  Carve mem;
+  auto arrays = [&](bool with_table) {
+    mem.parts.clear();
+    mem.add(&dxy, 2 * (size_t)(p + m + n));
+    mem.add(&drs, 2 * (size_t)d);
+    if (with_table)
+      mem.add(&tab, grid_tiers_bytes(nx, ny, d));
+    else
+      mem.add(&dR, Pm * Pm);
+    mem.add(&RT, (size_t)d * p * p);
+    mem.add(&rt, (size_t)p * (d - 1));
+    mem.add(&Rs1, (size_t)m * p);
+    mem.add(&Rsd, (size_t)n * p);
+    mem.add(&HZ, (size_t)nz * nz);
+    mem.add(&D, (size_t)ntile * TB * TB);
+    mem.add(&rhs, (size_t)nz * ne);
+    mem.add(&U, (size_t)nz * ne);
+    mem.add(&Icur, (size_t)ne * p * (d - 1));
+    mem.add(&selfv, (size_t)ne);
+    mem.add(&cA, (size_t)m * 2 * p);
+    mem.add(&cB, (size_t)n * 2 * p);
+    mem.add(&G, (size_t)m * n);
+    mem.add(&bad, 1);
+    if (!out_on_device) mem.add(&dout, (size_t)m * n);
+  };
+  bool table = grid_use_table(nx, ny, (int64_t)Pm);
+  arrays(table);
+  hipError_t e = mem.alloc();
+  if (e == hipErrorOutOfMemory && table) {
+    (void)hipGetLastError();
+    table = false;
+    arrays(false);
+    e = mem.alloc();
+  }
   if (e != hipSuccess) return dev_fail(e, "hipMalloc");
   double* out = out_on_device ? R_out : dout;
+  // (a fill kernel of the runtime; the call is never captured, it synchronises)
   e = hipMemsetAsync(bad, 0, sizeof(int), st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(rt, tsv_r, sizeof(double) * p * (d - 1), hipMemcpyHostToDevice, st);
@@ -464,13 +582,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
     if (e == hipSuccess)
       e = hipMemcpyAsync(drs, rs.data(), sizeof(double) * rs.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
-      e = grid_tiers_device(nx, ny, d, drs, rects.data(), (int)rects.size(), st);
-    if (e == hipErrorOutOfMemory) {  // no room for a tier's table
-      (void)hipGetLastError();
-      table = false;
-      e = hipStreamSynchronize(st);  // the staged points are refilled below
-      if (e == hipSuccess) e = bufs.get(&dR, (size_t)std::max(P0, Pd) * std::max(P0, Pd));
-    }
+      e = grid_tiers_launch(nx, ny, d, drs, rects.data(), (int)rects.size(), tab, st);
   }
   for (int t = 0; !table && t < d && e == hipSuccess; ++t) {
     pts.assign(tsv_xy, tsv_xy + 2 * (size_t)p);
@@ -502,48 +614,36 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
                          (const double*)Rsd, rhs);
       e = hipGetLastError();
     }
-    for (int kt = 0; kt < ntile && e == hipSuccess; ++kt) {
-      const int o = kt * TB, nb = std::min(TB, nz - o), rest = nz - o - nb;
-      hipLaunchKernelGGL(k_potrf_tile, dim3(1), dim3(256), 0, st, nz, kt, (const double*)HZ,
-                         (int64_t)nz, L, Linv, bad);
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(k_ldl_first, dim3(1), dim3(256), 0, st, nz, (const double*)HZ, D, bad);
       e = hipGetLastError();
-      // panel: L(rest, k) = A(rest, k) L_kk^-T
-      if (e == hipSuccess && rest > 0)
-        e = gemm(st, rest, nb, nb, 1.0, HZ + (size_t)(o + nb) * nz + o, nz, 0,
-                 Linv + (size_t)kt * TB * TB, TB, 1, 0.0, L + (size_t)(o + nb) * nz + o, nz);
-      // trailing update (lower tiles): A(rest, rest) -= L(rest, k) L(rest, k)^T
-      if (e == hipSuccess && rest > 0)
-        e = gemm(st, rest, rest, nb, -1.0, L + (size_t)(o + nb) * nz + o, nz, 0,
-                 L + (size_t)(o + nb) * nz + o, nz, 1, 1.0, HZ + (size_t)(o + nb) * nz + o + nb, nz,
-                 1);
     }
-    // forward: L Y = rhs (rhs is consumed), tile row by tile row
-    for (int kt = 0; kt < ntile && e == hipSuccess; ++kt) {
-      const int o = kt * TB, nb = std::min(TB, nz - o), rest = nz - o - nb;
-      e = gemm(st, nb, ne, nb, 1.0, Linv + (size_t)kt * TB * TB, TB, 0, rhs + (size_t)o * ne, ne,
-               0, 0.0, Y + (size_t)o * ne, ne);
-      if (e == hipSuccess && rest > 0)
-        e = gemm(st, rest, ne, nb, -1.0, L + (size_t)(o + nb) * nz + o, nz, 0,
-                 Y + (size_t)o * ne, ne, 0, 1.0, rhs + (size_t)(o + nb) * ne, ne);
+    const unsigned et = (unsigned)((ne + TB - 1) / TB);
+    for (int kt = 0; kt + 1 < ntile && e == hipSuccess; ++kt) {
+      const unsigned rest = (unsigned)(ntile - 1 - kt);
+      hipLaunchKernelGGL(k_ldl_step, dim3(rest + et, rest), dim3(256), 0, st, nz, kt, ntile, HZ, D,
+                         ne, rhs, bad);
+      e = hipGetLastError();
     }
-    // backward: L^T U = Y (U written into rhs), last tile row first
     for (int kt = ntile - 1; kt >= 0 && e == hipSuccess; --kt) {
-      const int o = kt * TB, nb = std::min(TB, nz - o);
-      e = gemm(st, nb, ne, nb, 1.0, Linv + (size_t)kt * TB * TB, TB, 1, Y + (size_t)o * ne, ne, 0,
-               0.0, rhs + (size_t)o * ne, ne);
-      if (e == hipSuccess && o > 0)
-        e = gemm(st, o, ne, nb, -1.0, L + (size_t)o * nz, nz, 1, rhs + (size_t)o * ne, ne, 0, 1.0,
-                 Y, ne);
+      hipLaunchKernelGGL(k_ldl_back, dim3(et, (unsigned)(kt + 1)), dim3(256), 0, st, nz, kt,
+                         (const double*)HZ, (const double*)D, ne, rhs, U);
+      e = hipGetLastError();
     }
   }
   // 4. currents, voltage differences, self terms, cross-term operands
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_reduced_post, dim3((unsigned)ne), dim3(256), 0, st, d, p, (int)m, ne,
                        (const double*)RT, (const double*)rt, (const double*)Rs1,
-                       (const double*)Rsd, (const double*)rhs, Icur, selfv, cA, cB);
+                       (const double*)Rsd, (const double*)U, Icur, selfv, cA, cB);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) e = gemm(st, (int)m, (int)n, 2 * p, 1.0, cA, 2 * p, 0, cB, 2 * p, 1, 0.0, G, n);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_gemm64, dim3((unsigned)((n + TB - 1) / TB), (unsigned)((m + TB - 1) / TB)),
+                       dim3(256), 0, st, (int)m, (int)n, 2 * p, (const double*)cA, (int64_t)(2 * p),
+                       (const double*)cB, (int64_t)(2 * p), G, (int64_t)n);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_reduced_finish, rgrid(m * n), dim3(256), 0, st, (int)m, (int)n,
                        (const double*)selfv, (const double*)G, out);
@@ -557,6 +657,6 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   if (e != hipSuccess) return dev_fail(e, "reduced pairs");
   if (hbad)
     return host_fail(REFF_ERR_DEVICE,
-                     "reduced system: a Cholesky pivot of Z^T H Z was not positive");
+                     "reduced system: a pivot of Z^T H Z was not positive");
   return REFF_OK;
 }

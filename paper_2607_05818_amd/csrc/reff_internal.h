@@ -21,7 +21,7 @@ reff_status host_fail(reff_status s, const std::string& msg);
 // The stack validation every entry point performs before device work.
 reff_status host_validate_desc(const reff_pdn_desc* d);
 // Eq. 3 on uniform M x N tiers (grid_pairs.hip).  Whether P points are served
-// by the cosine table of the tier (grid_tiers_device) or by direct products
+// by the cosine table of the tier (grid_tiers_launch) or by direct products
 // (grid_pairs_device).
 bool grid_use_table(int M, int N, int64_t P);
 // Resistances of row points x column points of one tier: out[nr * nc].
@@ -31,11 +31,13 @@ struct GridRect {
   int64_t nr, nc;
   double* out;
 };
-// The rectangles of nt tiers of one size; drs[2 t], drs[2 t + 1] are tier
-// t's edge resistances along x and y.  Pointers are device memory (rects is
-// host); returns once the stream has run the kernels.
-hipError_t grid_tiers_device(int M, int N, int nt, const double* drs, const GridRect* rects,
-                             int nrect, hipStream_t st);
+// Launches the rectangles of nt tiers of one size on `st`; drs[2 t], drs[2 t
+// + 1] are tier t's edge resistances along x and y.  Pointers are device
+// memory (rects is host), `work` grid_tiers_bytes of it, in use until the
+// stream has run the kernels.
+size_t grid_tiers_bytes(int M, int N, int nt);
+hipError_t grid_tiers_launch(int M, int N, int nt, const double* drs, const GridRect* rects,
+                             int nrect, char* work, hipStream_t st);
 // Every pair of P points (device xy) into device out[P * P]; returns once the
 // stream has run the kernels.
 hipError_t grid_pairs_device(int M, int N, double r, double s, const int32_t* dxy, int64_t P,
