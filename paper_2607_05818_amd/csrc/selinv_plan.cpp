@@ -3,6 +3,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <system_error>
+#include <mutex>
+#include <exception>
 #include <functional>
 #include <thread>
 
@@ -407,13 +410,29 @@ void selinv_parallel_for(size_t count, const std::function<void(size_t)>& body) 
     for (size_t i = 0; i < count; ++i) body(i);
     return;
   }
+  // The calling thread works too; where threads cannot be had it works alone.
+  // An exception of the body ends the loop and is passed on to the caller.
   std::atomic<size_t> next{0};
-  std::vector<std::thread> pool;
-  for (size_t t = 0; t < nthr; ++t)
-    pool.emplace_back([&]() {
+  std::exception_ptr failed;
+  std::mutex mu;
+  auto work = [&]() {
+    try {
       for (size_t i = next++; i < count; i = next++) body(i);
-    });
+    } catch (...) {
+      next = count;
+      std::lock_guard<std::mutex> lk(mu);
+      failed = std::current_exception();
+    }
+  };
+  std::vector<std::thread> pool;
+  pool.reserve(nthr - 1);
+  try {
+    for (size_t t = 0; t + 1 < nthr; ++t) pool.emplace_back(work);
+  } catch (const std::system_error&) {
+  }
+  work();
   for (auto& th : pool) th.join();
+  if (failed) std::rethrow_exception(failed);
 }
 
 }  // namespace reff

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "reff_internal.h"
+#include "selinv_plan.h"
 #include "surrogate_internal.h"
 
 using namespace reffsg;
@@ -54,21 +55,22 @@ struct Layer {
   int cin, cout, k;
   bool relu;
   int64_t w_off, b_off;  // into the parameter vector
-  uint16_t* wb = nullptr;  // bf16 W [k*k*cin][gcout]
-  uint16_t* wt = nullptr;  // bf16 flipped transpose [k*k*gcout][cin]
+  uint16_t* wb = nullptr;  // bf16 W [gcout][k*k*cin], rows padded (conv_row)
+  uint16_t* wt = nullptr;  // bf16 flipped transpose [cin][k*k*gcout], rows padded
   int gcout() const { return up ? 4 * cout : cout; }
   int64_t nw() const { return (int64_t)k * k * cin * gcout(); }
+  int64_t nwb() const { return gcout() * conv_row((int64_t)k * k * cin); }
+  int64_t nwt() const { return cin * conv_row((int64_t)k * k * gcout()); }
 };
 
 // Activation (and gradient) buffers of one batch capacity.
 struct Acts {
   int cap = 0;
-  uint16_t *x0, *e1a, *cat1, *p1, *e2a, *cat2, *p2, *e3a, *cat3, *p3, *b1, *b2, *s3, *d3a, *d3b,
-      *s2, *d2a, *d2b, *s1, *d1a, *d1b;
+  uint16_t *x0, *e1a, *cat1, *p1, *e2a, *cat2, *p2, *e3a, *cat3, *p3, *b1, *b2, *d3a, *d3b, *d2a,
+      *d2b, *d1a, *d1b;
   float* out;
   uint16_t *ge1a, *gcat1, *gp1, *ge2a, *gcat2, *gp2, *ge3a, *gcat3, *gp3, *gb1, *gb2, *gs3, *gd3a,
       *gd3b, *gs2, *gd2a, *gd2b, *gs1, *gd1a, *gd1b, *gout;
-  uint16_t* col;
   uint8_t* padm;
   double* R;
   std::vector<void*> owned;
@@ -90,6 +92,8 @@ struct reff_surrogate_t {
   double* lpart = nullptr;  // loss partials
   LabelRec* lab = nullptr;
   size_t lab_cap = 0;
+  void* stage = nullptr;  // pinned staging of a batch's features and pad masks
+  size_t stage_bytes = 0;
   Acts a;
 };
 
@@ -124,18 +128,14 @@ reff_status ensure_acts(reff_surrogate_t* s, int B) {
       {&a.x0, P1 * s->cin0}, {&a.e1a, P1 * C},     {&a.cat1, P1 * 2 * C}, {&a.p1, P2 * C},
       {&a.e2a, P2 * 2 * C},  {&a.cat2, P2 * 4 * C}, {&a.p2, P3 * 2 * C},  {&a.e3a, P3 * 4 * C},
       {&a.cat3, P3 * 8 * C}, {&a.p3, P4 * 4 * C},   {&a.b1, P4 * 8 * C},  {&a.b2, P4 * 8 * C},
-      {&a.s3, P4 * 16 * C},  {&a.d3a, P3 * 4 * C},  {&a.d3b, P3 * 4 * C}, {&a.s2, P3 * 8 * C},
-      {&a.d2a, P2 * 2 * C},  {&a.d2b, P2 * 2 * C},  {&a.s1, P2 * 4 * C},  {&a.d1a, P1 * C},
-      {&a.d1b, P1 * C},
+      {&a.d3a, P3 * 4 * C},  {&a.d3b, P3 * 4 * C},  {&a.d2a, P2 * 2 * C}, {&a.d2b, P2 * 2 * C},
+      {&a.d1a, P1 * C},      {&a.d1b, P1 * C},
       {&a.ge1a, P1 * C},     {&a.gcat1, P1 * 2 * C}, {&a.gp1, P2 * C},     {&a.ge2a, P2 * 2 * C},
       {&a.gcat2, P2 * 4 * C}, {&a.gp2, P3 * 2 * C}, {&a.ge3a, P3 * 4 * C}, {&a.gcat3, P3 * 8 * C},
       {&a.gp3, P4 * 4 * C},  {&a.gb1, P4 * 8 * C},  {&a.gb2, P4 * 8 * C}, {&a.gs3, P4 * 16 * C},
       {&a.gd3a, P3 * 4 * C}, {&a.gd3b, P3 * 4 * C}, {&a.gs2, P3 * 8 * C}, {&a.gd2a, P2 * 2 * C},
       {&a.gd2b, P2 * 2 * C}, {&a.gs1, P2 * 4 * C},  {&a.gd1a, P1 * C},    {&a.gd1b, P1 * C},
       {&a.gout, P1 * s->nt},
-      // im2col: at most 9 x (2C input channels) per pixel at full resolution
-      // (every level has 9 x 16 C / 4^l <= 18 C per full-resolution pixel).
-      {&a.col, P1 * 18 * C},
   };
   for (const Req& r : reqs) SGRET(dmalloc((void**)r.p, (size_t)r.n * 2, a.owned));
   SGRET(dmalloc((void**)&a.out, (size_t)P1 * s->nt * 4, a.owned));
@@ -199,14 +199,15 @@ reff_status alloc_model(reff_surrogate_t* s) {
   SGCHK(hipMemset(s->m, 0, np * 4));
   SGCHK(hipMemset(s->v, 0, np * 4));
   int64_t nw = 0;
-  for (const Layer& l : s->L) nw += 2 * l.nw();
+  for (const Layer& l : s->L) nw += l.nwb() + l.nwt();
   SGCHK(hipMalloc((void**)&s->wbuf, (size_t)nw * 2));
+  SGCHK(hipMemset(s->wbuf, 0, (size_t)nw * 2));  // the rows' padding
   int64_t o = 0;
   for (Layer& l : s->L) {
     l.wb = s->wbuf + o;
-    o += l.nw();
+    o += l.nwb();
     l.wt = s->wbuf + o;
-    o += l.nw();
+    o += l.nwt();
   }
   s->part_floats = PART_FLOATS;
   SGCHK(hipMalloc((void**)&s->part, s->part_floats * 4));
@@ -220,43 +221,58 @@ void free_model(reff_surrogate_t* s) {
   for (void* q : {(void*)s->p, (void*)s->g, (void*)s->m, (void*)s->v, (void*)s->wbuf,
                   (void*)s->part, (void*)s->lpart, (void*)s->lab})
     if (q) (void)hipFree(q);
+  if (s->stage) (void)hipHostFree(s->stage);
   free_acts(s->a);
   delete s;
 }
 
-// Input channels of one plan (see the header), bf16, [ny][nx][cin0], and its
-// tier-0 pad mask [ny][nx].
-void plan_features(const reff_surrogate_t* s, const reff_pdn_desc* d, uint16_t* f, uint8_t* pad) {
+// Input channels of rows [y0, y1) of one plan (see the header), bf16,
+// [ny][nx][cin0], and its tier-0 pad mask [ny][nx].
+void plan_features(const reff_surrogate_t* s, const reff_pdn_desc* d, int y0, int y1, uint16_t* f,
+                   uint8_t* pad) {
   const int nt = s->nt, nx = s->nx, ny = s->ny, ci = s->cin0;
-  std::vector<float> x((size_t)nx * ny * ci, 0.f);
-  for (int t = 0; t < nt; ++t)
-    for (int y = 0; y < ny; ++y)
-      for (int xx = 0; xx < nx; ++xx) {
-        float* px = &x[((size_t)y * nx + xx) * ci];
-        if (xx + 1 < nx) px[t] = (float)std::log(d->gx[((size_t)t * ny + y) * (nx - 1) + xx]);
-        if (y + 1 < ny) px[nt + t] = (float)std::log(d->gy[((size_t)t * (ny - 1) + y) * nx + xx]);
-      }
+  std::vector<float> row((size_t)nx * ci);
+  for (int y = y0; y < y1; ++y) {
+    std::fill(row.begin(), row.end(), 0.f);
+    for (int t = 0; t < nt; ++t) {
+      const double* gx = d->gx + ((size_t)t * ny + y) * (nx - 1);
+      for (int x = 0; x + 1 < nx; ++x) row[(size_t)x * ci + t] = (float)std::log(gx[x]);
+      if (y + 1 == ny) continue;
+      const double* gy = d->gy + ((size_t)t * (ny - 1) + y) * nx;
+      for (int x = 0; x < nx; ++x) row[(size_t)x * ci + nt + t] = (float)std::log(gy[x]);
+    }
+    uint16_t* o = f + (size_t)y * nx * ci;
+    for (size_t i = 0; i < row.size(); ++i) o[i] = host_f2bf(row[i]);
+  }
+  std::memset(pad + (size_t)y0 * nx, 0, (size_t)(y1 - y0) * nx);
   for (int j = 0; j < d->n_tsv; ++j) {
     const int xx = d->tsv_xy[2 * j], y = d->tsv_xy[2 * j + 1];
+    if (y < y0 || y >= y1) continue;
     double mean = 0.0;
     for (int t = 0; t + 1 < nt; ++t) mean += d->tsv_g[(size_t)j * (nt - 1) + t];
     mean = nt > 1 ? mean / (nt - 1) : 0.0;
-    x[((size_t)y * nx + xx) * ci + 2 * nt] = (float)std::log1p(mean);
+    f[((size_t)y * nx + xx) * ci + 2 * nt] = host_f2bf((float)std::log1p(mean));
   }
-  std::memset(pad, 0, (size_t)nx * ny);
   for (int j = 0; j < d->n_pads; ++j) {
     const int xx = d->pad_xy[2 * j], y = d->pad_xy[2 * j + 1];
-    x[((size_t)y * nx + xx) * ci + 2 * nt + 1] = 1.f;
+    if (y < y0 || y >= y1) continue;
+    f[((size_t)y * nx + xx) * ci + 2 * nt + 1] = host_f2bf(1.f);
     pad[(size_t)y * nx + xx] = 1;
   }
-  for (size_t i = 0; i < x.size(); ++i) f[i] = host_f2bf(x[i]);
 }
 
+// Descriptors are validated on host threads; the first bad plan is reported.
 reff_status check_plans(const reff_surrogate_t* s, const reff_pdn_desc* plans, int32_t n) {
   if (n < 0) return host_fail(REFF_ERR_INVALID_ARG, "n_plans < 0");
   if (n > 0 && !plans) return host_fail(REFF_ERR_INVALID_ARG, "plans is NULL");
+  std::vector<reff_status> vs((size_t)n, REFF_OK);
+  std::vector<std::string> vm((size_t)n);
+  reff::selinv_parallel_for((size_t)n, [&](size_t i) {
+    vs[i] = reff::host_validate_desc(&plans[i]);
+    if (vs[i] != REFF_OK) vm[i] = reff_last_error();  // this thread's message
+  });
   for (int32_t i = 0; i < n; ++i) {
-    SGRET(reff::host_validate_desc(&plans[i]));
+    if (vs[(size_t)i] != REFF_OK) return host_fail(vs[(size_t)i], vm[(size_t)i]);
     if (plans[i].n_tiers != s->nt || plans[i].nx != s->nx || plans[i].ny != s->ny)
       return host_fail(REFF_ERR_INVALID_ARG,
                        "plan " + std::to_string(i) + " does not match the model geometry");
@@ -264,48 +280,58 @@ reff_status check_plans(const reff_surrogate_t* s, const reff_pdn_desc* plans, i
   return REFF_OK;
 }
 
-// Upload the features and pad masks of plans idx[0..B) into the batch input.
+// Upload the features and pad masks of plans idx[0..B) into the batch input:
+// formed on host threads in bands of rows, straight into pinned memory that
+// the model keeps (the copy is drained before the call returns).
 reff_status load_inputs(reff_surrogate_t* s, const reff_pdn_desc* plans, const int32_t* idx,
                         int B, hipStream_t st) {
-  const size_t hw = (size_t)s->nx * s->ny;
-  std::vector<uint16_t> f(hw * s->cin0 * B);
-  std::vector<uint8_t> pad(hw * B);
-  for (int b = 0; b < B; ++b)
-    plan_features(s, &plans[idx[b]], f.data() + hw * s->cin0 * b, pad.data() + hw * b);
-  SGCHK(hipMemcpyAsync(s->a.x0, f.data(), f.size() * 2, hipMemcpyHostToDevice, st));
-  SGCHK(hipMemcpyAsync(s->a.padm, pad.data(), pad.size(), hipMemcpyHostToDevice, st));
+  const size_t hw = (size_t)s->nx * s->ny, fb = hw * s->cin0 * B * 2;
+  if (fb + hw * B > s->stage_bytes) {
+    if (s->stage) (void)hipHostFree(s->stage);
+    s->stage = nullptr;
+    s->stage_bytes = 0;
+    SGCHK(hipHostMalloc(&s->stage, fb + hw * B, hipHostMallocDefault));
+    s->stage_bytes = fb + hw * B;
+  }
+  uint16_t* f = (uint16_t*)s->stage;
+  uint8_t* pad = (uint8_t*)s->stage + fb;
+  constexpr int BAND = 32;  // rows: about 0.1 ms of logarithms at 3 x 128 columns
+  const size_t bands = (size_t)(s->ny + BAND - 1) / BAND;
+  reff::selinv_parallel_for(bands * B, [&](size_t i) {
+    const size_t b = i / bands;
+    const int y0 = (int)(i % bands) * BAND;
+    plan_features(s, &plans[idx[b]], y0, std::min(y0 + BAND, s->ny), f + hw * s->cin0 * b,
+                  pad + hw * b);
+  });
+  SGCHK(hipMemcpyAsync(s->a.x0, f, fb, hipMemcpyHostToDevice, st));
+  SGCHK(hipMemcpyAsync(s->a.padm, pad, hw * B, hipMemcpyHostToDevice, st));
   SGCHK(hipStreamSynchronize(st));
   return REFF_OK;
 }
 
 // ---- layer sequencing
 
+// A transposed convolution (l.up) stores its rows depth-to-space.
 reff_status conv_fwd(reff_surrogate_t* s, const Layer& l, const uint16_t* X, int64_t ldx, int B,
                      int H, int W, void* Y, int64_t ldy, bool y_fp32, hipStream_t st) {
-  const int64_t P = (int64_t)B * H * W;
-  GemmArgs g{};
-  if (l.k == 1) {
-    g.A = X;
-    g.sAm = ldx;
-    g.K = l.cin;
-  } else {
-    SGCHK(im2col(X, ldx, l.cin, B, H, W, l.k, s->a.col, st));
-    g.A = s->a.col;
-    g.sAm = (int64_t)l.k * l.k * l.cin;
-    g.K = l.k * l.k * l.cin;
-  }
-  g.sAk = 1;
-  g.B = l.wb;
-  g.sBk = l.gcout();
-  g.M = (int)P;
+  ConvArgs g{};
+  g.X = X;
+  g.ldx = ldx;
+  g.cin = l.cin;
+  g.taps = l.k * l.k;
+  g.P = B * H * W;
+  g.H = H;
+  g.W = W;
+  g.Wn = l.wb;
   g.N = l.gcout();
+  g.K = g.taps * l.cin;
   g.bias = s->p + l.b_off;
   g.relu = l.relu ? 1 : 0;
   g.C = Y;
   g.ldc = ldy;
   g.c_fp32 = y_fp32 ? 1 : 0;
-  g.kchunk = (g.K + 31) / 32 * 32;
-  SGCHK(gemm(g, 1, st));
+  g.up = l.up ? l.cout : 0;
+  SGCHK(conv(g, st));
   return REFF_OK;
 }
 
@@ -321,66 +347,36 @@ reff_status conv_bwd(reff_surrogate_t* s, const Layer& l, const uint16_t* X, int
   // bias gradient
   const int nblk = (int)std::min<int64_t>(256, std::max<int64_t>(1, P / 256));
   SGCHK(colsum(dY, lddy, co, P, s->part, nblk, s->g + l.b_off, st));
-  // weight gradient: dW = im2col(X)^T dY, K dimension = pixels, split
-  GemmArgs g{};
-  const int kdim = l.k * l.k * l.cin;
-  if (l.k == 1) {
-    g.A = X;
-    g.sAm = 1;
-    g.sAk = ldx;
-  } else {
-    SGCHK(im2col(X, ldx, l.cin, B, H, W, l.k, s->a.col, st));
-    g.A = s->a.col;
-    g.sAm = 1;
-    g.sAk = kdim;
-  }
-  g.B = dY;
-  g.sBk = lddy;
-  g.M = kdim;
+  // weight gradient
+  WgradArgs g{};
+  g.X = X;
+  g.ldx = ldx;
+  g.cin = l.cin;
+  g.taps = l.k * l.k;
+  g.P = (int)P;
+  g.H = H;
+  g.W = W;
+  g.dY = dY;
+  g.ldy = lddy;
   g.N = co;
-  g.K = (int)P;
-  g.relu = 0;
-  g.bias = nullptr;
-  g.ldc = co;
-  g.c_fp32 = 1;
-  const int64_t mn = (int64_t)kdim * co;
-  int64_t nsplit = std::min<int64_t>({(P + 4095) / 4096, 64, (int64_t)s->part_floats / mn});
-  nsplit = std::max<int64_t>(1, nsplit);
-  g.kchunk = (int)(((P + nsplit - 1) / nsplit + 31) / 32 * 32);
-  nsplit = (P + g.kchunk - 1) / g.kchunk;
-  if (nsplit > 1) {
-    g.C = s->part;
-    SGCHK(gemm(g, (int)nsplit, st));
-    SGCHK(splitk_reduce(s->part, (int)nsplit, mn, s->g + l.w_off, 0, st));
-  } else {
-    g.C = s->g + l.w_off;
-    SGCHK(gemm(g, 1, st));
-  }
+  g.part = s->part;
+  SGCHK(wgrad(g, s->g + l.w_off, (int64_t)s->part_floats, st));
   if (!dX) return REFF_OK;
-  // input gradient: dX = im2col(dY) Wt
-  GemmArgs h{};
-  if (l.k == 1) {
-    h.A = dY;
-    h.sAm = lddy;
-    h.K = co;
-  } else {
-    SGCHK(im2col(dY, lddy, co, B, H, W, l.k, s->a.col, st));
-    h.A = s->a.col;
-    h.sAm = (int64_t)l.k * l.k * co;
-    h.K = l.k * l.k * co;
-  }
-  h.sAk = 1;
-  h.B = l.wt;
-  h.sBk = l.cin;
-  h.M = (int)P;
+  // input gradient: the convolution of dY with the flipped taps
+  ConvArgs h{};
+  h.X = dY;
+  h.ldx = lddy;
+  h.cin = co;
+  h.taps = l.k * l.k;
+  h.P = (int)P;
+  h.H = H;
+  h.W = W;
+  h.Wn = l.wt;
   h.N = l.cin;
-  h.bias = nullptr;
-  h.relu = 0;
+  h.K = h.taps * co;
   h.C = dX;
   h.ldc = lddx;
-  h.c_fp32 = 0;
-  h.kchunk = (h.K + 31) / 32 * 32;
-  SGCHK(gemm(h, 1, st));
+  SGCHK(conv(h, st));
   return REFF_OK;
 }
 
@@ -399,16 +395,13 @@ reff_status forward(reff_surrogate_t* s, int B, hipStream_t st) {
   SGCHK(pool_fwd(a.cat3 + 4 * C, 8 * C, 4 * C, B, H / 4, W / 4, a.p3, st));
   SGRET(conv_fwd(s, L[6], a.p3, 4 * C, B, H / 8, W / 8, a.b1, 8 * C, false, st));
   SGRET(conv_fwd(s, L[7], a.b1, 8 * C, B, H / 8, W / 8, a.b2, 8 * C, false, st));
-  SGRET(conv_fwd(s, L[8], a.b2, 8 * C, B, H / 8, W / 8, a.s3, 16 * C, false, st));
-  SGCHK(d2s(a.s3, 4 * C, B, H / 8, W / 8, a.cat3, 8 * C, st));
+  SGRET(conv_fwd(s, L[8], a.b2, 8 * C, B, H / 8, W / 8, a.cat3, 8 * C, false, st));
   SGRET(conv_fwd(s, L[9], a.cat3, 8 * C, B, H / 4, W / 4, a.d3a, 4 * C, false, st));
   SGRET(conv_fwd(s, L[10], a.d3a, 4 * C, B, H / 4, W / 4, a.d3b, 4 * C, false, st));
-  SGRET(conv_fwd(s, L[11], a.d3b, 4 * C, B, H / 4, W / 4, a.s2, 8 * C, false, st));
-  SGCHK(d2s(a.s2, 2 * C, B, H / 4, W / 4, a.cat2, 4 * C, st));
+  SGRET(conv_fwd(s, L[11], a.d3b, 4 * C, B, H / 4, W / 4, a.cat2, 4 * C, false, st));
   SGRET(conv_fwd(s, L[12], a.cat2, 4 * C, B, H / 2, W / 2, a.d2a, 2 * C, false, st));
   SGRET(conv_fwd(s, L[13], a.d2a, 2 * C, B, H / 2, W / 2, a.d2b, 2 * C, false, st));
-  SGRET(conv_fwd(s, L[14], a.d2b, 2 * C, B, H / 2, W / 2, a.s1, 4 * C, false, st));
-  SGCHK(d2s(a.s1, C, B, H / 2, W / 2, a.cat1, 2 * C, st));
+  SGRET(conv_fwd(s, L[14], a.d2b, 2 * C, B, H / 2, W / 2, a.cat1, 2 * C, false, st));
   SGRET(conv_fwd(s, L[15], a.cat1, 2 * C, B, H, W, a.d1a, C, false, st));
   SGRET(conv_fwd(s, L[16], a.d1a, C, B, H, W, a.d1b, C, false, st));
   SGRET(conv_fwd(s, L[17], a.d1b, C, B, H, W, a.out, s->nt, true, st));
@@ -734,8 +727,8 @@ reff_status reff_surrogate_predict(reff_surrogate s, const reff_pdn_desc* plans,
     SGRET(ensure_acts(s, B));
     SGRET(reffsg::predict_device(s, plans + b0, B, s->a.R, nullptr));
     for (int b = 0; b < B; ++b)
-      SGCHK(hipMemcpy(R_out[b0 + b], s->a.R + b * per, (size_t)per * 8,
-                      out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost));
+      SGCHK(hipMemcpyAsync(R_out[b0 + b], s->a.R + b * per, (size_t)per * 8,
+                           out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, nullptr));
   }
   SGCHK(hipDeviceSynchronize());
   return REFF_OK;

@@ -16,24 +16,39 @@ bool geometry_matches(reff_surrogate s, const reff_pdn_desc* d);
 reff_status predict_device(reff_surrogate s, const reff_pdn_desc* plans, int32_t n, double* R,
                            hipStream_t st);
 
-// C(m, n) = sum_k A(m, k) B(k, n) on the matrix cores (BF16 inputs, FP32
-// accumulation), A(m, k) = A[m*sAm + k*sAk] (sAm == 1 or sAk == 1),
-// B(k, n) = B[k*sBk + n].  With kchunk < K the K range is split over
-// gridDim.z slices of kchunk (a multiple of 32) and slice z writes its FP32
-// partial to (float*)C + z*M*ldc (no bias, no ReLU); otherwise
-//   C(m, n) = relu?(acc + bias[n]) stored as FP32 or BF16 at C[m*ldc + n].
-struct GemmArgs {
-  const uint16_t* A;
-  int64_t sAm, sAk;
-  const uint16_t* B;
-  int64_t sBk;
-  int M, N, K;
+// A 3x3 (taps 9, zero padding) or 1x1 (taps 1) convolution over P = B H W
+// pixels as a product on the matrix cores (BF16 inputs, FP32 accumulation):
+//   C(p, n) = relu?(sum over k = tap cin + c < K of X[p + tap][c] Wn[n][k] + bias[n])
+// stored as FP32 or BF16 at C[p ldc + n]; with up = c > 0 (a 2x2 transposed
+// convolution of c channels, N = 4 c) column (a 2 + b) c + ch of pixel (y, x)
+// is stored at channel ch of pixel (2 y + a, 2 x + b).  Rows of Wn hold
+// conv_row(K) values, zero past K.
+struct ConvArgs {
+  const uint16_t* X;
+  int64_t ldx;
+  int cin, taps, P, H, W;
+  const uint16_t* Wn;
+  int N, K;
   const float* bias;
   int relu;
   void* C;
   int64_t ldc;
-  int c_fp32;
-  int kchunk;
+  int c_fp32, up;
+  int magic;  // set by conv
+};
+constexpr int64_t conv_row(int64_t K) { return (K + 31) / 32 * 32; }
+
+// Weight gradient of such a convolution: out[m][n] = sum_p X[p + tap][c]
+// dY[p][n], m = tap cin + c (`part`: room for the partial sums).
+struct WgradArgs {
+  const uint16_t* X;
+  int64_t ldx;
+  int cin, taps, P, H, W;
+  const uint16_t* dY;
+  int64_t ldy;
+  int N;
+  float* part;
+  int chunk, magic;  // set by wgrad
 };
 
 // One labelled node of a training batch: pixel (b*H + y)*W + x of the
@@ -45,23 +60,15 @@ struct LabelRec {
   float pad_;
 };
 
-hipError_t gemm(const GemmArgs& g, int nsplit, hipStream_t st);
-// out[i] (=|+=) sum over z < nsplit of part[z*len + i]
-hipError_t splitk_reduce(const float* part, int nsplit, int64_t len, float* out, int accumulate,
-                         hipStream_t st);
-// col[p][(kh*K + kw)*C + c] = X[p shifted by (kh - (K-1)/2, kw - (K-1)/2)][c]
-// (0 outside the image); X has row stride ldx.
-hipError_t im2col(const uint16_t* X, int64_t ldx, int C, int B, int H, int W, int K,
-                  uint16_t* col, hipStream_t st);
+hipError_t conv(ConvArgs g, hipStream_t st);
+hipError_t wgrad(WgradArgs g, float* out, int64_t part_floats, hipStream_t st);
 hipError_t pool_fwd(const uint16_t* X, int64_t ldx, int C, int B, int H, int W, uint16_t* Y,
                     hipStream_t st);
 // dX (row stride ldx) += dY routed to the first maximum of each 2x2 window
 hipError_t pool_bwd(const uint16_t* X, int64_t ldx, const uint16_t* dY, int C, int B, int H,
                     int W, uint16_t* dX, hipStream_t st);
-// depth-to-space: Y[(b, 2y+a, 2x+c)][ch] = S[(b, y, x)][(a*2+c)*C + ch]; H, W
-// are the low-resolution sizes.  s2d is its adjoint (a gather).
-hipError_t d2s(const uint16_t* S, int C, int B, int H, int W, uint16_t* Y, int64_t ldy,
-               hipStream_t st);
+// space-to-depth: S[(b, y, x)][(a*2+c)*C + ch] = Y[(b, 2y+a, 2x+c)][ch]; H, W
+// are the low-resolution sizes
 hipError_t s2d(const uint16_t* Y, int64_t ldy, int C, int B, int H, int W, uint16_t* S,
                hipStream_t st);
 // dY *= (Y > 0) over P rows of C channels
@@ -70,8 +77,9 @@ hipError_t relu_bwd(uint16_t* dY, int64_t lddy, const uint16_t* Y, int64_t ldy, 
 // db[c] = sum over P rows of dY[p][c]; part holds nblk*C floats
 hipError_t colsum(const uint16_t* dY, int64_t ld, int C, int64_t P, float* part, int nblk,
                   float* db, hipStream_t st);
-// Wb = bf16(W), Wt = bf16 of the flipped transpose used by the input gradient:
-// Wt[(kh*K + kw)*Cout + co][ci] = W[((K-1-kh)*K + (K-1-kw))*Cin + ci][co]
+// BF16 copies of W [(kh*K + kw)*Cin + ci][co] for the products: Wb[co][(kh*K +
+// kw)*Cin + ci] and, for the input gradient, the flipped taps Wt[ci][((K-1-kh)*K
+// + (K-1-kw))*Cout + co]; rows of conv_row values
 hipError_t weight_copies(const float* W, int Cin, int Cout, int K, uint16_t* Wb, uint16_t* Wt,
                          hipStream_t st);
 // dpred[pix][t] = 2 (pred - logR) / n for each label (dpred zeroed first);

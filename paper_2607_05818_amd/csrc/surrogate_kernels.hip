@@ -1,10 +1,13 @@
-// gfx950 kernels of the screening model: one BF16 matrix-core GEMM that
-// carries every convolution (im2col + GEMM; the 2x2 transposed convolution
-// is a 1x1 GEMM into a space-to-depth layout), plus the pooling, layout,
-// loss and optimiser kernels around it.  Activations are NHWC BF16 (stored
-// as uint16_t), accumulation is FP32.
+// gfx950 kernels of the screening model: BF16 matrix-core products that carry
+// every convolution (implicit GEMMs: the 3x3 neighbourhoods are read where
+// they lie; the 2x2 transposed convolution is a 1x1 product whose rows are
+// stored depth-to-space), plus the pooling, layout, loss and optimiser kernels
+// around them.  Activations are NHWC BF16 (stored as uint16_t), accumulation
+// is FP32.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <algorithm>
 
 #include "surrogate_internal.h"
 
@@ -19,223 +22,341 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 
-typedef short s4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
-
-constexpr int BM = 64, BN = 64, BK = 32, LDT = BK + 8;
-
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+typedef __bf16 b8v __attribute__((ext_vector_type(8)));
 
-// Eight consecutive bf16 of one tile row, from global memory: one 16-byte
-// load when the run is in range and 16-byte aligned, element loads (zero
-// outside [0, lim)) otherwise.
-__device__ __forceinline__ u4v load8(const uint16_t* __restrict__ base, int64_t first,
-                                     int64_t stride, int idx0, int lim, bool vec_ok) {
-  if (vec_ok && idx0 + 8 <= lim) return *reinterpret_cast<const u4v*>(base + first);
-  uint16_t h[8];
+constexpr int BK = 32;       // K step of the convolution product
+constexpr int LDT = BK + 8;  // LDS row pitch: 16 rows of 16 bytes on 64 banks
+
+// K index -> tap without a division (magic = 2^20 / cin + 1): k / cin while k
+// cin < 2^20, which holds for every layer whose channels are no multiple of 8
+// (at most 254) and for the first 32 k of the others.
+__device__ __forceinline__ int tap_of(int k, int magic) { return (int)(((int64_t)k * magic) >> 20); }
+
+// C(p, n) = sum over taps and channels of X[p shifted by the tap][c] W[n][k],
+// k = tap cin + c: the convolution as a product over K = taps x cin whose A
+// rows are formed by the loads (taps outside the image are zero).  A workgroup
+// of four waves makes 64 MR pixels x NT channels, a wave 16 MR x NT of them
+// as MR x NT / 16 tiles of v_mfma_f32_16x16x32_bf16, K ascending in steps of
+// 32 (the instruction adds its k in order: the sums are those of the 16-wide
+// form bit for bit).  A thread moves eight consecutive k (one tap, for cin a
+// multiple of 8) of MR rows and of one row of W per step with 16-byte loads;
+// the next step's are in flight while the current products run, and the LDS
+// tiles are double-buffered, so one barrier per step suffices.
+// Bound by LDS reads (MR + NT / 16 per MR NT / 16 products); MR = 4 where that
+// leaves at least two workgroups per CU, else MR = 1.
+// At 16 plans of 3 x 128 x 128 (C = 32) the kernels of a forward pass take 575
+// us; with im2col copies, 64 x 64 tiles of the 16-wide instruction and a
+// depth-to-space pass they took 1,250 us.
+template <int MR, int NT>
+__global__ __launch_bounds__(256) void k_conv(ConvArgs g) {
+  constexpr int ROWS = 64 * MR, NQ = NT / 16;
+  __shared__ __align__(16) uint16_t sA[2][ROWS][LDT];
+  __shared__ __align__(16) uint16_t sB[2][NT][LDT];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int p0 = blockIdx.x * ROWS, n0 = blockIdx.y * NT;
+  const int row = t >> 2, kg = 8 * (t & 3);  // this thread's rows are row + 64 i
+  const bool vec = g.cin % 8 == 0 && g.ldx % 8 == 0 && ((uintptr_t)g.X & 15) == 0;
+  int px[MR], py[MR];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = idx0 + e < lim ? base[first + e * stride] : (uint16_t)0;
-  return u4v{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
-             (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
+  for (int i = 0; i < MR; ++i) {
+    const int p = p0 + row + 64 * i;
+    px[i] = p % g.W;
+    py[i] = p < g.P ? (p / g.W) % g.H : -4;  // rows past the end: no tap is inside
+  }
+  const int kp = (g.K + BK - 1) / BK * BK;  // rows of W are zero from K to kp
+  int tap = tap_of(kg, g.magic), ci = kg - tap * g.cin;
+  u4v va[MR], vb;
+  auto load_step = [&](int k0) {
+    if (vec) {
+      const int dy = g.taps == 9 ? ((tap * 11) >> 5) - 1 : 0;
+      const int dx = g.taps == 9 ? tap - 3 * (dy + 1) - 1 : 0;
+#pragma unroll
+      for (int i = 0; i < MR; ++i) {
+        const int y = py[i] + dy, x = px[i] + dx;
+        const int64_t p = p0 + row + 64 * i + dy * g.W + dx;
+        va[i] = tap < g.taps && y >= 0 && y < g.H && x >= 0 && x < g.W
+                    ? *reinterpret_cast<const u4v*>(g.X + p * g.ldx + ci)
+                    : u4v{0u, 0u, 0u, 0u};
+      }
+      ci += BK;
+      while (ci >= g.cin) ci -= g.cin, ++tap;
+    } else {
+#pragma unroll
+      for (int i = 0; i < MR; ++i) {
+        uint16_t h[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = k0 + kg + e, tp = tap_of(k, g.magic), c = k - tp * g.cin;
+          const int dy = g.taps == 9 ? ((tp * 11) >> 5) - 1 : 0;
+          const int dx = g.taps == 9 ? tp - 3 * (dy + 1) - 1 : 0;
+          const int y = py[i] + dy, x = px[i] + dx;
+          const int64_t p = p0 + row + 64 * i + dy * g.W + dx;
+          h[e] = k < g.K && y >= 0 && y < g.H && x >= 0 && x < g.W ? g.X[p * g.ldx + c] : (uint16_t)0;
+        }
+        va[i] = u4v{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
+                    (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
+      }
+    }
+    if (row < NT)
+      vb = n0 + row < g.N ? *reinterpret_cast<const u4v*>(g.Wn + (int64_t)(n0 + row) * kp + k0 + kg)
+                          : u4v{0u, 0u, 0u, 0u};
+  };
+  auto store_step = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < MR; ++i) *reinterpret_cast<u4v*>(&sA[buf][row + 64 * i][kg]) = va[i];
+    if (row < NT) *reinterpret_cast<u4v*>(&sB[buf][row][kg]) = vb;
+  };
+  f4v acc[MR][NQ];
+#pragma unroll
+  for (int i = 0; i < MR; ++i)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+  load_step(0);
+  store_step(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < kp; k0 += BK) {
+    const bool more = k0 + BK < kp;
+    if (more) load_step(k0 + BK);
+    const int kc = 8 * (lane >> 4), r = lane & 15;
+    b8v bf[NQ];
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) bf[j] = *reinterpret_cast<const b8v*>(&sB[buf][16 * j + r][kc]);
+#pragma unroll
+    for (int i = 0; i < MR; ++i) {
+      const b8v af = *reinterpret_cast<const b8v*>(&sA[buf][16 * (MR * w + i) + r][kc]);
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[j], acc[i][j], 0, 0, 0);
+    }
+    if (more) store_step(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int i = 0; i < MR; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int p = p0 + 16 * (MR * w + i) + 4 * (lane >> 4) + r;
+      if (p >= g.P) continue;
+      const int x = g.up ? p % g.W : 0, yb = g.up ? p / g.W : 0;  // yb = b H + y
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) {
+        const int n = n0 + 16 * j + (lane & 15);
+        if (n >= g.N) continue;
+        float v = acc[i][j][r];
+        if (g.bias) v += g.bias[n];
+        if (g.relu) v = fmaxf(v, 0.f);
+        int64_t at = (int64_t)p * g.ldc + n;
+        if (g.up) {  // channel (a 2 + c) up + ch of pixel (y, x) goes to (2 y + a, 2 x + c)
+          const int q = n / g.up;
+          at = ((int64_t)(2 * yb + (q >> 1)) * (2 * g.W) + 2 * x + (q & 1)) * g.ldc + n - q * g.up;
+        }
+        if (g.c_fp32)
+          ((float*)g.C)[at] = v;
+        else
+          ((uint16_t*)g.C)[at] = f2bf(v);
+      }
+    }
 }
 
-// 64 x 64 output tile (blockIdx.x along M, blockIdx.y along N, blockIdx.z
-// the K slice) per 256-thread workgroup; wave w owns the 32 x 32
-// quarter (w / 2, w % 2) as 2 x 2 tiles of v_mfma_f32_16x16x16bf16 (A lane
-// l holds A[l%16][4(l/16) .. +3], B lane l holds B[4(l/16) .. +3][l%16],
-// result row 4(l/16) + r, column l%16 in register r).  Every thread moves
-// eight consecutive bf16 of A and of B per 32-wide K step with one 16-byte
-// global load each; the next step's loads are in flight while the current
-// step's products run, and the LDS tiles are double-buffered, so one
-// barrier per step suffices.  A with unit K stride (im2col rows) lands in
-// LDS as one 16-byte store; the K-strided A (weight gradients) and B are
-// scattered into the transposed [n][k] layout the matrix-core operands read.
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __align__(16) uint16_t sA[2][BM][LDT];
-  __shared__ __align__(16) uint16_t sB[2][BN][LDT];  // transposed: sB[n][k]
+hipError_t conv(ConvArgs g, hipStream_t st) {
+  if (g.P <= 0 || g.N <= 0) return hipSuccess;
+  g.magic = (1 << 20) / g.cin + 1;
+  const int nt = g.N <= 32 ? 32 : 64;
+  auto blocks = [&](int rows, int n) { return dim3((g.P + rows - 1) / rows, (g.N + n - 1) / n); };
+  const dim3 big = blocks(256, nt);
+  if ((int64_t)big.x * big.y >= 512) {
+    if (nt == 32)
+      hipLaunchKernelGGL((k_conv<4, 32>), big, dim3(256), 0, st, g);
+    else
+      hipLaunchKernelGGL((k_conv<4, 64>), big, dim3(256), 0, st, g);
+    return hipGetLastError();
+  }
+  const dim3 sm = blocks(64, 64);
+  if (nt == 64 && (int64_t)sm.x * sm.y >= 512)
+    hipLaunchKernelGGL((k_conv<1, 64>), sm, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL((k_conv<1, 32>), blocks(64, 32), dim3(256), 0, st, g);
+  return hipGetLastError();
+}
+
+// Weight gradient: part[z][m][n] = sum over the pixels p of slice z of
+// X[p shifted by the tap of m][channel of m] dY[p][n], m = tap cin + c.  The
+// K index of the product is the pixel, along which neither operand is
+// contiguous: a thread loads eight channels (16 bytes) of four consecutive
+// pixels and stores them transposed, 8 bytes (four pixels) per channel, into
+// the [channel][pixel] tiles that the matrix cores read.  64 x 64 tiles of
+// (m, n), 64 pixels per step, wave w the quarter (w / 2, w % 2).
+// Replaces an im2col copy and 2-byte LDS stores: at 16 plans of 3 x 128 x 128
+// all kernels of a training step take 2.7 ms (this one 0.82), 7.4 ms before.
+constexpr int GP = 64;       // pixels per step
+constexpr int LGP = GP + 8;  // LDS pitch
+
+__global__ __launch_bounds__(256) void k_wgrad(WgradArgs g) {
+  __shared__ __align__(16) uint16_t sX[2][64][LGP], sD[2][64][LGP];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-  const int kbeg = blockIdx.z * g.kchunk;
-  const int kend = min(g.K, kbeg + g.kchunk);
+  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+  const int pbeg = blockIdx.z * g.chunk, pend = min(g.P, pbeg + g.chunk);
+  const bool isx = t < 128;
+  const int pg = 4 * (t & 15), cg = 8 * ((t & 127) >> 4);  // pixel and channel group
+  // operand of this thread: X at (tap, c) of m, or dY at column n
+  const int m = m0 + cg, n = n0 + cg;
+  const int K = g.taps * g.cin;
+  const int64_t ld = isx ? g.ldx : g.ldy;
+  const bool vec = isx ? g.cin % 8 == 0 && g.ldx % 8 == 0 && ((uintptr_t)g.X & 15) == 0
+                       : g.ldy % 8 == 0 && ((uintptr_t)g.dY & 15) == 0 && n + 8 <= g.N;
+  const int tap0 = isx ? min(m, K) / g.cin : 0;
+  const int wy = 64 / g.W, wx = 64 % g.W;  // one step further, in rows and columns
+  int x = (pbeg + pg) % g.W, y = ((pbeg + pg) / g.W) % g.H;
+  u4v v[4];
+  auto load_step = [&](int p0) {
+    int xx = x, yy = y;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int p = p0 + pg + j;
+      v[j] = u4v{0u, 0u, 0u, 0u};
+      if (p < pend) {
+        if (vec) {
+          const int dy = g.taps == 9 && isx ? ((tap0 * 11) >> 5) - 1 : 0;
+          const int dx = g.taps == 9 && isx ? tap0 - 3 * (dy + 1) - 1 : 0;
+          const bool in = isx ? m < K && yy + dy >= 0 && yy + dy < g.H && xx + dx >= 0 && xx + dx < g.W
+                              : true;
+          const uint16_t* src = isx ? g.X + ((int64_t)p + dy * g.W + dx) * ld + (m - tap0 * g.cin)
+                                    : g.dY + (int64_t)p * ld + n;
+          if (in) v[j] = *reinterpret_cast<const u4v*>(src);
+        } else {
+          uint16_t h[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            h[e] = 0;
+            if (isx && m + e < K) {
+              const int tp = tap_of(m + e, g.magic), c = m + e - tp * g.cin;
+              const int dy = g.taps == 9 ? ((tp * 11) >> 5) - 1 : 0;
+              const int dx = g.taps == 9 ? tp - 3 * (dy + 1) - 1 : 0;
+              if (yy + dy >= 0 && yy + dy < g.H && xx + dx >= 0 && xx + dx < g.W)
+                h[e] = g.X[((int64_t)p + dy * g.W + dx) * ld + c];
+            } else if (!isx && n + e < g.N) {
+              h[e] = g.dY[(int64_t)p * ld + n + e];
+            }
+          }
+          v[j] = u4v{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
+                     (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
+        }
+      }
+      if (++xx == g.W) {
+        xx = 0;
+        if (++yy == g.H) yy = 0;
+      }
+    }
+    x += wx;
+    y += wy;
+    if (x >= g.W) x -= g.W, ++y;
+    while (y >= g.H) y -= g.H;
+  };
+  auto store_step = [&](int buf) {
+    uint16_t(*T)[LGP] = isx ? sX[buf] : sD[buf];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {  // channels 2 e and 2 e + 1
+      const uint32_t a = v[0][e], b = v[1][e], c = v[2][e], d = v[3][e];
+      *reinterpret_cast<uint64_t*>(&T[cg + 2 * e][pg]) =
+          (uint64_t)((a & 0xffffu) | (b << 16)) | ((uint64_t)((c & 0xffffu) | (d << 16)) << 32);
+      *reinterpret_cast<uint64_t*>(&T[cg + 2 * e + 1][pg]) =
+          (uint64_t)((a >> 16) | (b & 0xffff0000u)) | ((uint64_t)((c >> 16) | (d & 0xffff0000u)) << 32);
+    }
+  };
   const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  const bool arow = g.sAk == 1;
-  // this thread's slice of a K step: A row-major: row t/4, k (t%4)*8;
-  // A K-strided: k t/8, rows (t%8)*8; B: k t/8, columns (t%8)*8
-  const int ar = arow ? t >> 2 : (t & 7) * 8, ak = arow ? (t & 3) * 8 : t >> 3;
-  const int bk = t >> 3, bn = (t & 7) * 8;
-  const bool a_vec = arow ? (g.sAm % 8 == 0 && ((uintptr_t)g.A & 15) == 0)
-                          : (g.sAm == 1 && g.sAk % 8 == 0 && ((uintptr_t)g.A & 15) == 0);
-  const bool b_vec = g.sBk % 8 == 0 && ((uintptr_t)g.B & 15) == 0;
-  auto load_step = [&](int k0, u4v& va, u4v& vb) {
-    if (arow) {
-      const int gm = m0 + ar;
-      va = gm < g.M ? load8(g.A, (int64_t)gm * g.sAm + k0 + ak, 1, k0 + ak, kend, a_vec)
-                    : u4v{0u, 0u, 0u, 0u};
-    } else {
-      const int gk = k0 + ak;
-      va = gk < kend ? load8(g.A, (int64_t)(m0 + ar) * g.sAm + (int64_t)gk * g.sAk, g.sAm, m0 + ar,
-                             g.M, a_vec)
-                     : u4v{0u, 0u, 0u, 0u};
-    }
-    const int gk = k0 + bk;
-    vb = gk < kend ? load8(g.B, (int64_t)gk * g.sBk + n0 + bn, 1, n0 + bn, g.N, b_vec)
-                   : u4v{0u, 0u, 0u, 0u};
-  };
-  auto store_step = [&](int buf, const u4v& va, const u4v& vb) {
-    if (arow) {
-      *reinterpret_cast<u4v*>(&sA[buf][ar][ak]) = va;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sA[buf][ar + e][ak] = (uint16_t)(va[e >> 1] >> (16 * (e & 1)));
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sB[buf][bn + e][bk] = (uint16_t)(vb[e >> 1] >> (16 * (e & 1)));
-  };
   f4v acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
-  u4v va, vb;
-  if (kbeg < kend) {
-    load_step(kbeg, va, vb);
-    store_step(0, va, vb);
+  if (pbeg < pend) {
+    load_step(pbeg);
+    store_step(0);
   }
   __syncthreads();
   int buf = 0;
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    const bool more = k0 + BK < kend;
-    if (more) load_step(k0 + BK, va, vb);
+  for (int p0 = pbeg; p0 < pend; p0 += GP) {
+    const bool more = p0 + GP < pend;
+    if (more) load_step(p0 + GP);
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      s4v af[2], bfr[2];
-      const int kc = kk + 4 * (lane >> 4);
+    for (int kk = 0; kk < GP; kk += 32) {
+      const int kc = kk + 8 * (lane >> 4), r = lane & 15;
+      b8v af[2], bf[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        af[i] = *reinterpret_cast<const s4v*>(&sA[buf][wm + 16 * i + (lane & 15)][kc]);
-        bfr[i] = *reinterpret_cast<const s4v*>(&sB[buf][wn + 16 * i + (lane & 15)][kc]);
+        af[i] = *reinterpret_cast<const b8v*>(&sX[buf][wm + 16 * i + r][kc]);
+        bf[i] = *reinterpret_cast<const b8v*>(&sD[buf][wn + 16 * i + r][kc]);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bfr[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
     }
-    if (more) store_step(buf ^ 1, va, vb);
+    if (more) store_step(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
-  const bool split = gridDim.z > 1;
+  float* C = g.part + (int64_t)blockIdx.z * K * g.N;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + 16 * j + (lane & 15);
-        if (m >= g.M || n >= g.N) continue;
-        float v = acc[i][j][r];
-        if (split) {
-          ((float*)g.C)[(int64_t)blockIdx.z * g.M * g.ldc + (int64_t)m * g.ldc + n] = v;
-          continue;
-        }
-        if (g.bias) v += g.bias[n];
-        if (g.relu) v = fmaxf(v, 0.f);
-        if (g.c_fp32)
-          ((float*)g.C)[(int64_t)m * g.ldc + n] = v;
-        else
-          ((uint16_t*)g.C)[(int64_t)m * g.ldc + n] = f2bf(v);
+        const int mm = m0 + wm + 16 * i + 4 * (lane >> 4) + r, nn = n0 + wn + 16 * j + (lane & 15);
+        if (mm < K && nn < g.N) C[(int64_t)mm * g.N + nn] = acc[i][j][r];
       }
 }
 
-hipError_t gemm(const GemmArgs& g, int nsplit, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  const dim3 grid((g.M + BM - 1) / BM, (g.N + BN - 1) / BN, nsplit);
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, g);
+// out[i] = sum over z < nsplit of part[z len + i]: 64 entries per workgroup,
+// its four waves each a quarter of the slices.
+__global__ __launch_bounds__(256) void k_sum_slices(const float* __restrict__ part, int nsplit,
+                                                    int64_t len, float* __restrict__ out) {
+  __shared__ float red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  float s = 0.f;
+  if (i < len)
+#pragma unroll 4
+    for (int z = w; z < nsplit; z += 4) s += part[z * len + i];
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && i < len) out[i] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+hipError_t sum_slices(const float* part, int nsplit, int64_t len, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((len + 63) / 64)), dim3(256), 0, st, part, nsplit,
+                     len, out);
   return hipGetLastError();
 }
 
-__global__ void k_splitk_reduce(const float* part, int nsplit, int64_t len, float* out,
-                                int accumulate) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int z = 0; z < nsplit; ++z) s += part[(int64_t)z * len + i];
-    out[i] = accumulate ? out[i] + s : s;
-  }
+// Pixels of a step's slice: enough workgroups to fill the chip twice, slices
+// of at least 512 pixels, and partials within part_floats.
+hipError_t wgrad(WgradArgs g, float* out, int64_t part_floats, hipStream_t st) {
+  const int K = g.taps * g.cin;
+  const int64_t len = (int64_t)K * g.N;
+  const int64_t tiles = (int64_t)((K + 63) / 64) * ((g.N + 63) / 64);
+  int64_t nz = std::max<int64_t>(1, std::min<int64_t>({(1024 + tiles - 1) / tiles, g.P / 512,
+                                                       part_floats / len}));
+  g.chunk = (int)(((g.P + nz - 1) / nz + GP - 1) / GP * GP);
+  nz = (g.P + g.chunk - 1) / g.chunk;
+  g.magic = (1 << 20) / g.cin + 1;
+  float* part = g.part;
+  if (nz == 1) g.part = out;
+  hipLaunchKernelGGL(k_wgrad, dim3((K + 63) / 64, (g.N + 63) / 64, (unsigned)nz), dim3(256), 0, st, g);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && nz > 1) e = sum_slices(part, (int)nz, len, out, st);
+  return e;
 }
 
 static int blocks_for(int64_t n, int per = 256, int cap = 16384) {
   const int64_t b = (n + per - 1) / per;
   return (int)(b < 1 ? 1 : (b > cap ? cap : b));
-}
-
-hipError_t splitk_reduce(const float* part, int nsplit, int64_t len, float* out, int accumulate,
-                         hipStream_t st) {
-  hipLaunchKernelGGL(k_splitk_reduce, dim3(blocks_for(len)), dim3(256), 0, st, part, nsplit, len,
-                     out, accumulate);
-  return hipGetLastError();
-}
-
-__global__ void k_im2col(const uint16_t* X, int64_t ldx, int C, int B, int H, int W, int K,
-                         uint16_t* col) {
-  const int KK = K * K;
-  const int64_t total = (int64_t)B * H * W * KK * C;
-  const int h = (K - 1) / 2;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % C);
-    const int64_t q = e / C;
-    const int kk = (int)(q % KK);
-    const int64_t p = q / KK;
-    const int x = (int)(p % W);
-    const int y = (int)((p / W) % H);
-    const int64_t b = p / ((int64_t)W * H);
-    const int sy = y + kk / K - h, sx = x + kk % K - h;
-    uint16_t v = 0;
-    if (sy >= 0 && sy < H && sx >= 0 && sx < W) v = X[((b * H + sy) * W + sx) * ldx + c];
-    col[e] = v;
-  }
-}
-
-// The same with eight channels (16 bytes) per thread and 32-bit index
-// arithmetic: for C and ldx multiples of 8, 16-byte aligned buffers and
-// fewer than 2^31 groups.
-__global__ void k_im2col8(const uint16_t* __restrict__ X, int ldx, int C8, int B, int H, int W,
-                          int K, uint16_t* __restrict__ col) {
-  const int KK = K * K;
-  const int total = B * H * W * KK * C8;
-  const int h = (K - 1) / 2;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int cg = e % C8;
-    const int q = e / C8;
-    const int kk = q % KK;
-    const int p = q / KK;
-    const int x = p % W;
-    const int py = p / W;
-    const int y = py % H;
-    const int b = py / H;
-    const int sy = y + kk / K - h, sx = x + kk % K - h;
-    u4v v = u4v{0u, 0u, 0u, 0u};
-    if (sy >= 0 && sy < H && sx >= 0 && sx < W)
-      v = *reinterpret_cast<const u4v*>(X + ((int64_t)(b * H + sy) * W + sx) * ldx + cg * 8);
-    *reinterpret_cast<u4v*>(col + (int64_t)e * 8) = v;
-  }
-}
-
-hipError_t im2col(const uint16_t* X, int64_t ldx, int C, int B, int H, int W, int K,
-                  uint16_t* col, hipStream_t st) {
-  const int64_t total = (int64_t)B * H * W * K * K * C;
-  if (C % 8 == 0 && ldx % 8 == 0 && ldx < ((int64_t)1 << 30) && total / 8 < ((int64_t)1 << 31) &&
-      ((uintptr_t)X & 15) == 0 && ((uintptr_t)col & 15) == 0) {
-    hipLaunchKernelGGL(k_im2col8, dim3(blocks_for(total / 8)), dim3(256), 0, st, X, (int)ldx,
-                       C / 8, B, H, W, K, col);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_im2col, dim3(blocks_for(total)), dim3(256), 0, st, X, ldx, C, B, H, W, K,
-                     col);
-  return hipGetLastError();
 }
 
 __global__ void k_pool_fwd(const uint16_t* X, int64_t ldx, int C, int B, int H, int W,
@@ -302,43 +423,37 @@ hipError_t pool_bwd(const uint16_t* X, int64_t ldx, const uint16_t* dY, int C, i
   return hipGetLastError();
 }
 
-// One element per (low-res pixel, a, c, channel); forward gathers from S and
-// scatters to Y, the adjoint does the reverse.
-template <bool TO_Y>
-__global__ void k_d2s(const uint16_t* src, uint16_t* dst, int C, int B, int H, int W,
-                      int64_t ldy) {
-  const int64_t total = (int64_t)B * H * W * 4 * C;
+// Space-to-depth, the adjoint of the transposed convolution's stores: one
+// element, or eight (C and ldy multiples of 8, 16-byte aligned), per (low-res
+// pixel, a, c, channel group).
+template <int V>
+__global__ void k_s2d(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int C, int B,
+                      int H, int W, int64_t ldy) {
+  const int CV = C / V;
+  const int64_t total = (int64_t)B * H * W * 4 * CV;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
-    const int ch = (int)(e % C);
-    const int64_t q = e / C;
-    const int ac = (int)(q % 4);
-    const int64_t p = q / 4;
-    const int x = (int)(p % W);
-    const int y = (int)((p / W) % H);
-    const int64_t b = p / ((int64_t)W * H);
-    const int a = ac >> 1, c = ac & 1;
-    const int64_t py = (b * 2 * H + 2 * y + a) * (2 * W) + 2 * x + c;
-    if (TO_Y)
-      dst[py * ldy + ch] = src[e];
+    const int ch = (int)(e % CV) * V;
+    const int64_t q = e / CV;
+    const int ac = (int)(q & 3);
+    const uint32_t p = (uint32_t)(q >> 2);  // < 2^28 pixels
+    const uint32_t yb = p / W, x = p - yb * W;
+    const int64_t py = (int64_t)(2 * yb + (ac >> 1)) * (2 * W) + 2 * x + (ac & 1);
+    if (V == 8)
+      *reinterpret_cast<u4v*>(dst + e * 8) = *reinterpret_cast<const u4v*>(src + py * ldy + ch);
     else
       dst[e] = src[py * ldy + ch];
   }
 }
 
-hipError_t d2s(const uint16_t* S, int C, int B, int H, int W, uint16_t* Y, int64_t ldy,
-               hipStream_t st) {
-  const int64_t total = (int64_t)B * H * W * 4 * C;
-  hipLaunchKernelGGL(k_d2s<true>, dim3(blocks_for(total)), dim3(256), 0, st, S, Y, C, B, H, W,
-                     ldy);
-  return hipGetLastError();
-}
-
 hipError_t s2d(const uint16_t* Y, int64_t ldy, int C, int B, int H, int W, uint16_t* S,
                hipStream_t st) {
   const int64_t total = (int64_t)B * H * W * 4 * C;
-  hipLaunchKernelGGL(k_d2s<false>, dim3(blocks_for(total)), dim3(256), 0, st, Y, S, C, B, H, W,
-                     ldy);
+  if (C % 8 == 0 && ldy % 8 == 0 && (((uintptr_t)Y | (uintptr_t)S) & 15) == 0)
+    hipLaunchKernelGGL(k_s2d<8>, dim3(blocks_for(total / 8)), dim3(256), 0, st, Y, S, C, B, H, W,
+                       ldy);
+  else
+    hipLaunchKernelGGL(k_s2d<1>, dim3(blocks_for(total)), dim3(256), 0, st, Y, S, C, B, H, W, ldy);
   return hipGetLastError();
 }
 
@@ -360,22 +475,43 @@ hipError_t relu_bwd(uint16_t* dY, int64_t lddy, const uint16_t* Y, int64_t ldy, 
   return hipGetLastError();
 }
 
-// Block (cx, r): channels 64 cx .. +63, rows r, r + nblk, ... ; 4 row
-// groups of 64 lanes, combined in LDS.
-__global__ __launch_bounds__(256) void k_colsum(const uint16_t* dY, int64_t ld, int C, int64_t P,
-                                                float* part) {
-  __shared__ float red[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int grp = threadIdx.x >> 6;
-  float s = 0.f;
-  if (c < C)
-    for (int64_t p = (int64_t)blockIdx.y * 4 + grp; p < P; p += (int64_t)gridDim.y * 4)
-      s += bf2f(dY[p * ld + c]);
-  red[grp][threadIdx.x & 63] = s;
+// Column sums of P rows: block (cx, r) takes channels 64 cx .. +63 of rows r
+// 32 + .., its thread eight channels (one 16-byte load per row where the rows
+// allow it) of every 32 nblk-th row; combined in LDS.
+__global__ __launch_bounds__(256) void k_colsum(const uint16_t* __restrict__ dY, int64_t ld, int C,
+                                                int64_t P, float* __restrict__ part) {
+  __shared__ float red[32][64];
+  const int c8 = 8 * (threadIdx.x & 7), r = threadIdx.x >> 3;
+  const int c = blockIdx.x * 64 + c8;
+  const bool vec = c + 8 <= C && ld % 8 == 0 && ((uintptr_t)dY & 15) == 0;
+  float s[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s[e] = 0.f;
+  if (vec) {
+#pragma unroll 4
+    for (int64_t p = (int64_t)blockIdx.y * 32 + r; p < P; p += (int64_t)gridDim.y * 32) {
+      const u4v v = *reinterpret_cast<const u4v*>(dY + p * ld + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s[2 * e] += __uint_as_float(v[e] << 16);
+        s[2 * e + 1] += __uint_as_float(v[e] & 0xffff0000u);
+      }
+    }
+  } else if (c < C) {
+    for (int64_t p = (int64_t)blockIdx.y * 32 + r; p < P; p += (int64_t)gridDim.y * 32)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (c + e < C) s[e] += bf2f(dY[p * ld + c + e]);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[r][c8 + e] = s[e];
   __syncthreads();
-  if (grp == 0 && c < C)
-    part[(int64_t)blockIdx.y * C + c] = red[0][threadIdx.x] + red[1][threadIdx.x] +
-                                        red[2][threadIdx.x] + red[3][threadIdx.x];
+  if (threadIdx.x < 64 && blockIdx.x * 64 + threadIdx.x < C) {
+    float v = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < 32; ++k) v += red[k][threadIdx.x];
+    part[(int64_t)blockIdx.y * C + blockIdx.x * 64 + threadIdx.x] = v;
+  }
 }
 
 hipError_t colsum(const uint16_t* dY, int64_t ld, int C, int64_t P, float* part, int nblk,
@@ -383,13 +519,16 @@ hipError_t colsum(const uint16_t* dY, int64_t ld, int C, int64_t P, float* part,
   hipLaunchKernelGGL(k_colsum, dim3((C + 63) / 64, nblk), dim3(256), 0, st, dY, ld, C, P, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return splitk_reduce(part, nblk, C, db, 0, st);
+  return sum_slices(part, nblk, C, db, st);
 }
 
-__global__ void k_weight_copies(const float* W, int Cin, int Cout, int K, uint16_t* Wb,
-                                uint16_t* Wt) {
+// Rows of Wb and Wt are padded to multiples of 32 (the padding is zeroed when
+// the model is made).
+__global__ void k_weight_copies(const float* __restrict__ W, int Cin, int Cout, int K,
+                                uint16_t* __restrict__ Wb, uint16_t* __restrict__ Wt) {
   const int KK = K * K;
   const int64_t total = (int64_t)KK * Cin * Cout;
+  const int64_t ldb = conv_row(KK * Cin), ldt = conv_row(KK * Cout);
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int co = (int)(e % Cout);
@@ -397,10 +536,10 @@ __global__ void k_weight_copies(const float* W, int Cin, int Cout, int K, uint16
     const int ci = (int)(q % Cin);
     const int kk = (int)(q / Cin);
     const uint16_t v = f2bf(W[e]);
-    Wb[e] = v;
+    Wb[co * ldb + q] = v;
     const int kh = kk / K, kw = kk % K;
     const int kf = (K - 1 - kh) * K + (K - 1 - kw);
-    Wt[((int64_t)kf * Cout + co) * Cin + ci] = v;
+    Wt[ci * ldt + (int64_t)kf * Cout + co] = v;
   }
 }
 
