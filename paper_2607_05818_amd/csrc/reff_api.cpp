@@ -993,6 +993,9 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
       b.TA = triples ? ws.TA.p : nullptr;  // no three-step passes without them
       b.TB = triples ? ws.TB.p : nullptr;
       b.max_tsv_slots = max_slots;
+      int64_t most = 0;
+      for (const PlanDesc& pd : plans) most = std::max(most, pd.n);
+      if (most <= resident_nodes(fp32)) b.resident = (int)most;
     }
 
     HIPCHK(launch_init_blocks(fp32, o.indep, coef, b, o.stream));

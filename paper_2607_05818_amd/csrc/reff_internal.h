@@ -243,7 +243,13 @@ struct SolveBuffers {
   void* TA = nullptr;
   void* TB = nullptr;
   int max_tsv_slots = 0;
+  // > 0: every block's stack has at most this many nodes, and this many fit
+  // the one-launch Chebyshev application (resident_nodes)
+  int resident = 0;
 };
+
+// Most nodes of a stack whose Chebyshev iterate a workgroup holds on chip.
+constexpr int resident_nodes(bool fp32) { return fp32 ? 8192 : 4096; }
 
 int grid_for(int64_t n);
 

@@ -1469,6 +1469,87 @@ __global__ __launch_bounds__(WG, sizeof(T) == 4 ? 4 : 2) void k_cheb2_strip(Coef
   for (int s = 0; s < st.nrows; ++s) row(s, std::true_type{});
 }
 
+// Every Chebyshev step of an application in one launch, for stacks whose
+// iterate fits on chip: one workgroup per column of a block holds the whole
+// stack's z_j in LDS (two buffers), its nodes' coefficients, R and z_{j-1} in
+// registers, and steps with one barrier between steps.  Node values come from
+// cheb_node as everywhere, so they are those of the strip passes bit for bit.
+// A column is strided in memory (64 right-hand sides per node); workgroups of
+// one XCD take eight adjacent columns, whose 64-byte pieces then meet in its
+// L2.
+// A strip pass costs about 15 us however small the stack (prologue of dependent
+// loads, a handful of workgroups, side-buffer launches), nine of them an
+// application at degree 19; this is one launch of 24 us (2 x 32 x 32,
+// float64).  NPT nodes per thread: float64 up to 4, float32 up to 8 (registers
+// and 128 KB of LDS), which bounds the stack (resident_nodes).
+constexpr int RES_THREADS = 1024;
+struct ChebSteps {
+  double a1[MAX_CHEB], a2[MAX_CHEB];
+};
+
+template <typename T, int NPT>
+__global__ __launch_bounds__(RES_THREADS) void k_cheb_resident(Coef<T> c, Work wk,
+                                                               const int32_t* __restrict__ act,
+                                                               const T* __restrict__ R,
+                                                               T* __restrict__ Z, int degree,
+                                                               ChebSteps cs_, T ith) {
+  __shared__ T z[2][RES_THREADS * NPT];
+  if ((int)blockIdx.y >= wk.cnt[2]) return;
+  const PlanDesc pd = wk.plans[act[blockIdx.y]];
+  const int col = (blockIdx.x & 7) * (S / 8) + (blockIdx.x >> 3);
+  const int n = (int)pd.n, nx = pd.nx, plane = (int)pd.plane, ny = plane / nx;
+  T d[NPT], di[NPT], ce[NPT], cw[NPT], cn[NPT], cs[NPT], r[NPT], u[NPT], up[NPT];
+  int slot[NPT], at[NPT];  // at: bits 0..3 = has east, west, north, south neighbour
+#pragma unroll
+  for (int i = 0; i < NPT; ++i) {
+    const int v = min((int)threadIdx.x + RES_THREADS * i, n - 1);
+    const int64_t ci = pd.cbase + v;
+    const int rem = v % plane, x = rem % nx, y = rem / nx;
+    at[i] = (x + 1 < nx ? 1 : 0) | (x > 0 ? 2 : 0) | (y + 1 < ny ? 4 : 0) | (y > 0 ? 8 : 0);
+    d[i] = c.d[ci];
+    di[i] = c.dinv[ci];
+    ce[i] = c.cE[ci];
+    cw[i] = x > 0 ? c.cE[ci - 1] : T(0);
+    cn[i] = c.cN[ci];
+    cs[i] = y > 0 ? c.cN[ci - nx] : T(0);
+    slot[i] = c.slot[ci];
+    r[i] = R[(pd.vbase + v) * S + col];
+    u[i] = di[i] * r[i] * ith;  // z_1, in the order of cheb_z1
+    up[i] = T(0);
+    if ((int)threadIdx.x + RES_THREADS * i < n) z[0][v] = u[i];
+  }
+  __syncthreads();
+  for (int j = 1; j < degree; ++j) {
+    const T* zc = z[(j & 1) ^ 1];
+    T* zn = z[j & 1];
+    const T a1 = (T)cs_.a1[j], a2 = (T)cs_.a2[j];
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int v = (int)threadIdx.x + RES_THREADS * i;
+      if (v >= n) break;
+      T gu = T(0), gd = T(0), yu = T(0), yd = T(0);
+      if (slot[i] >= 0) {
+        gu = c.up[slot[i]];
+        gd = c.dn[slot[i]];
+        yu = zc[gu != T(0) ? v + plane : v];
+        yd = zc[gd != T(0) ? v - plane : v];
+      }
+      const T znew = cheb_node(u[i], at[i] & 1 ? zc[v + 1] : T(0), at[i] & 2 ? zc[v - 1] : T(0),
+                               at[i] & 4 ? zc[v + nx] : T(0), at[i] & 8 ? zc[v - nx] : T(0), yu, yd,
+                               d[i], ce[i], cw[i], cn[i], cs[i], gu, gd, up[i], r[i], di[i], a1, a2);
+      up[i] = u[i];
+      u[i] = znew;
+      zn[v] = znew;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < NPT; ++i) {
+    const int v = (int)threadIdx.x + RES_THREADS * i;
+    if (v < n) Z[(pd.vbase + v) * S + col] = u[i];
+  }
+}
+
 // TSV side buffers of a three-step pass (z_{j+1}, z_{j+2}, z_{j+3} from z_j,
 // z_{j-1}): the strip kernel's level 2 and level 3 need z_{j+1} and z_{j+2}
 // at the TSV partners of their nodes, in tiers other workgroups own.  Slot q
@@ -2549,7 +2630,10 @@ __global__ void k_scale_units(Coef<T> c, Work wk, const T* __restrict__ R, T* __
 // 0 .. nb-1 in order, a block staying active until every column met the
 // tolerance (all_conv); its units and strips follow it.  One workgroup;
 // 256 blocks per round, placed by block-wide exclusive scans of the active
-// flag and of the unit and strip counts.
+// flag and of the unit and strip counts.  Blocks only leave between resets of
+// the lists, so an unchanged count means unchanged lists: the usual iteration,
+// in which no block converges, ends there (two blocks of 1024 units each: 69
+// -> 5 us).
 __global__ __launch_bounds__(256) void k_compact(const PlanDesc* __restrict__ plans, int nb,
                                                  const BlockState* __restrict__ st,
                                                  int32_t* __restrict__ act,
@@ -2558,6 +2642,10 @@ __global__ __launch_bounds__(256) void k_compact(const PlanDesc* __restrict__ pl
                                                  int32_t* __restrict__ cnt) {
   __shared__ int sa[256], su[256], ss[256];
   const int t = threadIdx.x;
+  int n_on = 0;
+  for (int base = 0; base < nb; base += 256)
+    n_on += __syncthreads_count(base + t < nb && st[base + t].all_conv == 0);
+  if (n_on == cnt[2]) return;
   int ta = 0, tu = 0, ts = 0;  // totals of the rounds before
   for (int base = 0; base < nb; base += 256) {
     const int p = base + t;
@@ -2612,7 +2700,29 @@ static void reduce(const SolveBuffers& b, int m0, int nmat, int len, hipStream_t
 // that forms z_1 from R itself, so that no kernel writes z_1.
 template <typename T>
 static bool cheb_folds_z1(const SolveBuffers& b) {
-  return sizeof(T) == 4 && b.cheb_k > 3 && b.TA != nullptr;
+  return b.resident > 0 || (sizeof(T) == 4 && b.cheb_k > 3 && b.TA != nullptr);
+}
+
+// All steps in one launch (k_cheb_resident; b.resident: nodes of the group's
+// largest stack).
+template <typename T>
+static T* cheb_resident(const Coef<T>& c, const SolveBuffers& b, hipStream_t st, T* last) {
+  ChebSteps s;
+  for (int j = 0; j < MAX_CHEB; ++j) s.a1[j] = b.cheb_a1[j], s.a2[j] = b.cheb_a2[j];
+  T* out = last ? last : (T*)b.Za;
+  const dim3 g(S, b.n_act), blk(RES_THREADS);
+  const T ith = (T)b.cheb_invtheta;
+  const T* R = (const T*)b.R;
+  const int per = (b.resident + RES_THREADS - 1) / RES_THREADS;
+  if (per <= 1)
+    hipLaunchKernelGGL((k_cheb_resident<T, 1>), g, blk, 0, st, c, b.work, b.act, R, out, b.cheb_k, s, ith);
+  else if (per <= 2)
+    hipLaunchKernelGGL((k_cheb_resident<T, 2>), g, blk, 0, st, c, b.work, b.act, R, out, b.cheb_k, s, ith);
+  else if (per <= 4)
+    hipLaunchKernelGGL((k_cheb_resident<T, 4>), g, blk, 0, st, c, b.work, b.act, R, out, b.cheb_k, s, ith);
+  else if constexpr (sizeof(T) == 4)
+    hipLaunchKernelGGL((k_cheb_resident<T, 8>), g, blk, 0, st, c, b.work, b.act, R, out, b.cheb_k, s, ith);
+  return out;
 }
 
 // Chebyshev steps j = 1 .. cheb_k - 1 from z_1: three per pass while three
@@ -2624,6 +2734,7 @@ static bool cheb_folds_z1(const SolveBuffers& b) {
 // Returns the array that holds Z.
 template <typename T>
 static T* cheb_steps(const Coef<T>& c, const SolveBuffers& b, hipStream_t st, T* last) {
+  if (b.resident > 0) return cheb_resident<T>(c, b, st, last);
   const dim3 g(b.n_strips), blk(WG);
   T* buf[4] = {(T*)b.Za, (T*)b.Zb, (T*)b.Zc, (T*)b.Zd};
   const T* R = (const T*)b.R;
