@@ -33,11 +33,10 @@ S = 64
 def cheb_passes(cheb, fp32=True):
     """The Chebyshev passes of one preconditioner application, in order:
     (steps, has z_{j-1}) per pass.  Steps run three per pass while three
-    remain (float32; two in float64), then two, then one."""
+    remain, then two, then one."""
     left, first, out = cheb - 1, True, []
-    top = 3 if fp32 else 2
     while left > 0:
-        k = min(top, left)
+        k = min(3, left)
         out.append((k, not first))
         left -= k
         first = False
@@ -47,7 +46,7 @@ def cheb_passes(cheb, fp32=True):
 def cheb_folds_z1(cheb, fp32=True):
     """The first pass is a three-step pass that forms z_1 = D^-1 R / theta
     from R itself (nothing writes z_1)."""
-    return fp32 and cheb > 3
+    return cheb > 3
 
 
 def cheb_words(cheb, fp32=True):

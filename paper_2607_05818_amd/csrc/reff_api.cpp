@@ -598,10 +598,10 @@ void make_units(const std::vector<PlanDesc>& in, std::vector<PlanDesc>& plans,
 
 // Most rows of one strip for the three-step Chebyshev pass, which addresses
 // a strip's rows through unsigned 32-bit byte offsets from a base three rows
-// before it: (rows + 8) x nx x S floats stay below 2^31 bytes.  0 when even
+// before it: (rows + 8) x nx x S words stay below 2^31 bytes.  0 when even
 // one row does not fit (the pass is then not used).
-int64_t max_strip_rows(int64_t nx) {
-  return std::max<int64_t>(0, (int64_t(1) << 31) / (nx * S * (int64_t)sizeof(float)) - 8);
+int64_t max_strip_rows(int64_t nx, size_t word) {
+  return std::max<int64_t>(0, (int64_t(1) << 31) / (nx * S * (int64_t)word) - 8);
 }
 
 // Strips for the stencil kernel of a group (float32 block variant): every
@@ -610,7 +610,7 @@ int64_t max_strip_rows(int64_t nx) {
 // more than max_strip_rows rows each); at least `floor` per block while the
 // segments keep 64 rows or more (as for work units).
 void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
-                 int target = TARGET_UNITS, int floor = 0) {
+                 size_t word, int target = TARGET_UNITS, int floor = 0) {
   int64_t rows = 0;
   for (const PlanDesc& p : plans) rows += p.n;
   if (floor > 0) {
@@ -631,7 +631,7 @@ void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
     int64_t want = std::max<int64_t>(1, (target * p.n + rows - 1) / std::max<int64_t>(rows, 1));
     want = std::max<int64_t>(want, std::min<int64_t>(floor, nt * nsx * std::max<int64_t>(1, ny / 64)));
     const int64_t ysegs = std::min<int64_t>(ny, std::max<int64_t>(1, (want + nt * nsx - 1) / (nt * nsx)));
-    const int64_t hcap = max_strip_rows(nx);
+    const int64_t hcap = max_strip_rows(nx, word);
     const int64_t H = std::min<int64_t>((ny + ysegs - 1) / ysegs, std::max<int64_t>(hcap, 1));
     p.strip_begin = (int32_t)strips.size();
     for (int64_t t = 0; t < nt; ++t)
@@ -860,7 +860,7 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     nu = (int)units.size();
     strips.clear();
     const bool cheb = !o.indep && o.cheb > 1;
-    if ((fp32 || cheb) && !o.indep) make_strips(plans, strips, tc.strips, floor);
+    if ((fp32 || cheb) && !o.indep) make_strips(plans, strips, tsz, tc.strips, floor);
     ns = (int)strips.size();
     // ---- buffers
     reff_status rs;
@@ -876,7 +876,7 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     if (cheb && o.cheb > 2 && (rs = ensure(ws.Zc, vec)) != REFF_OK) return rs;
     if (cheb && o.cheb > 2 && (rs = ensure(ws.Zd, vec)) != REFF_OK) return rs;
     bool triples = cheb && o.cheb > 3;
-    for (const PlanDesc& p : plans) triples = triples && max_strip_rows(p.nx) >= 1;
+    for (const PlanDesc& p : plans) triples = triples && max_strip_rows(p.nx, tsz) >= 1;
     if (triples && (rs = ensure(ws.TA, (size_t)slot_rows * 5 * S * tsz)) != REFF_OK) return rs;
     if (triples && (rs = ensure(ws.TB, (size_t)slot_rows * S * tsz)) != REFF_OK) return rs;
     if ((rs = ensure(ws.part, (size_t)std::max(nu, ns) * NGRAM * S * S * sizeof(double))) != REFF_OK)

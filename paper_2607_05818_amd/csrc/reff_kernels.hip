@@ -1634,7 +1634,7 @@ __global__ __launch_bounds__(64 * TSV_WAVES) void k_cheb_tsv_b(
   }
 }
 
-// Three Chebyshev steps in one pass over a strip (float32, block variant):
+// Three Chebyshev steps in one pass over a strip (block variant):
 //   z_{j+1} = step(z_j, z_{j-1}; a1, a2), z_{j+2} = step(z_{j+1}, z_j; b1, b2),
 //   z_{j+3} = step(z_{j+2}, z_{j+1}; c1, c2)
 // (z_{j-1} = 0 without HAS_PREV).  Three levels one row apart: level 1 forms
@@ -1652,21 +1652,26 @@ __global__ __launch_bounds__(64 * TSV_WAVES) void k_cheb_tsv_b(
 // Writes z_{j+2} to outa (null for the last pass: nothing reads it) and
 // z_{j+3} to outb (the next pass's z_{j-1} and z_j); neither may alias an
 // input.
+// Float32: 74 KB of LDS and 123 VGPRs, two workgroups per CU.  Float64: 144 KB
+// and one workgroup per CU; against the two-step pass (133 KB, three barriers
+// per row) an application reads and writes 28 words per node instead of 44 at
+// degree 19, a pass of three steps taking the time of one of two: 204 -> 194 us
+// at 4 x 256 x 256 (one block), 177 -> 166 us at four blocks of 3 x 128 x 128.
 constexpr int WG3 = 512;
 constexpr int NPW3 = CH / (WG3 / 64);  // 4
 
-template <bool HAS_PREV>
-__global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
-                                                        const float* __restrict__ zin,
-                                                        const float* __restrict__ zprev,
-                                                        const float* __restrict__ R,
-                                                        const float* __restrict__ TA,
-                                                        const float* __restrict__ TB,
-                                                        float* __restrict__ outa,
-                                                        float* __restrict__ outb, float a1,
-                                                        float a2, float b1, float b2, float c1,
-                                                        float c2, float ith) {
-  using T = float;
+// The TSV slot among a node's coefficient words (float32: its bits).
+__device__ __forceinline__ float slot_word(int s, float) { return __int_as_float(s); }
+__device__ __forceinline__ double slot_word(int s, double) { return (double)s; }
+__device__ __forceinline__ int word_slot(float v) { return __float_as_int(v); }
+__device__ __forceinline__ int word_slot(double v) { return (int)v; }
+
+template <typename T, bool HAS_PREV>
+__global__ __launch_bounds__(WG3, sizeof(T) == 4 ? 4 : 2) void k_cheb3_strip(
+    Coef<T> c, Work wk, const T* __restrict__ zin, const T* __restrict__ zprev,
+    const T* __restrict__ R, const T* __restrict__ TA, const T* __restrict__ TB,
+    T* __restrict__ outa, T* __restrict__ outb, T a1, T a2, T b1, T b2, T c1, T c2, T ith) {
+  typedef T v4 __attribute__((ext_vector_type(4)));
   constexpr int NPW = NPW3;
   constexpr int N1 = CH + 4;  // coefficient columns -2 .. CH + 1, index c + 2
   // East / west neighbour rows, slot (s + 4) & 1 read in iteration s: z_j
@@ -1676,15 +1681,15 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
   __shared__ T h2[2][CH + 4][S];
   __shared__ T h3[2][CH + 2][S];
   // Everything a node's step reads besides the iterates, per row and column,
-  // in two 16-byte entries: cfa = {d, Dinv, cE (east coupling), cN (north
+  // in two entries of four words: cfa = {d, Dinv, cE (east coupling), cN (north
   // coupling)}, cfb = {cW (west coupling, cE of column c - 1), cS (south
   // coupling, cN of the row below), TSV slot (int bits), 0}.  Row yy is in
   // ring slot (yy - y0 + 4) & 7 and again 8 slots on, so that the rows y - 1
   // .. y + 2 read in iteration s sit in the consecutive slots b .. b + 3,
   // b = (s + 3) & 7: one address per node column and row, the rest fixed
   // offsets.
-  __shared__ f4v cfa[16][N1];
-  __shared__ f4v cfb[16][N1];
+  __shared__ v4 cfa[16][N1];
+  __shared__ v4 cfb[16][N1];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int ls = active_item(wk, 1);
@@ -1707,11 +1712,11 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
   // The strip's own rows are read and written through unsigned 32-bit byte
   // offsets from per-strip base pointers placed three rows and three columns
   // before its first node, so that every offset is non-negative (the host
-  // keeps (nrows + 8) nx S sizeof(float) below 2^31); TSV partners, a tier
+  // keeps (nrows + 8) nx S sizeof(T) below 2^31); TSV partners, a tier
   // away, use 64-bit indices.
   const int64_t r0off = (pd.vbase + st.lrow0) * S;
   const int64_t bias = (3 * (int64_t)nx + 3) * S;
-  const uint32_t lane4 = (uint32_t)lane * 4u;
+  const uint32_t lane4 = (uint32_t)(lane * sizeof(T));
   auto boff = [&](int yy, int cc) -> uint32_t {
     yy = min(max(yy, 0), ny - 1);
     cc = min(max(cc, -x0), nx - 1 - x0);
@@ -1790,12 +1795,12 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
   auto load_coef = [&](int yy, T& val) {
     if (has_c) {
       const int64_t ci = vidx(kf == 5 ? yy - 1 : yy, kc_src) + cofs;  // cS: the row below
-      val = kf == 6 ? __int_as_float(c.slot[ci]) : csrc[ci];
+      val = kf == 6 ? slot_word(c.slot[ci], T(0)) : csrc[ci];
     }
   };
   auto store_coef = [&](int k, T val) {
     if (has_c) {
-      const T v = kf == 6 ? (kc_ok ? val : __int_as_float(-1)) : (kc_ok ? val : T(0));
+      const T v = kf == 6 ? (kc_ok ? val : slot_word(-1, T(0))) : (kc_ok ? val : T(0));
       T* e = kf < 4 ? (T*)&cfa[k][kcol + 2] + kf : (T*)&cfb[k][kcol + 2] + (kf - 4);
       e[0] = v;
       e[8 * N1 * 4] = v;  // the copy 8 slots on
@@ -1854,7 +1859,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
 #pragma unroll
       for (int i = 0; i <= NPW; ++i) {
         sl[i] = (i < NPW || has_h)
-                    ? __builtin_amdgcn_readfirstlane(__float_as_int(cfb[b + 3][ccol(i) + 2][2]))
+                    ? __builtin_amdgcn_readfirstlane(word_slot(cfb[b + 3][ccol(i) + 2][2]))
                     : -1;
         any |= sl[i] >= 0;
         t1[i] = T(0);
@@ -1879,7 +1884,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
 #pragma unroll
       for (int i = 0; i <= NPW; ++i) {
         sl[i] = (i < NPW || w == 1 || w == 2)
-                    ? __builtin_amdgcn_readfirstlane(__float_as_int(cfb[b + 2][ccol(i) + 2][2]))
+                    ? __builtin_amdgcn_readfirstlane(word_slot(cfb[b + 2][ccol(i) + 2][2]))
                     : -1;
         any |= sl[i] >= 0;
       }
@@ -1902,7 +1907,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
       bool any = false;
 #pragma unroll
       for (int i = 0; i < NPW; ++i) {
-        sl[i] = __builtin_amdgcn_readfirstlane(__float_as_int(cfb[b + 1][ccol(i) + 2][2]));
+        sl[i] = __builtin_amdgcn_readfirstlane(word_slot(cfb[b + 1][ccol(i) + 2][2]));
         any |= sl[i] >= 0;
       }
       if (any) {
@@ -1934,7 +1939,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
       for (int i = 0; i <= NPW; ++i) {
         if (i == NPW && !has_h) break;
         const int cc = ccol(i);
-        const f4v A = cfa[b + 3][cc + 2], B = cfb[b + 3][cc + 2];
+        const v4 A = cfa[b + 3][cc + 2], B = cfb[b + 3][cc + 2];
         const T z = cheb_node_t(zA[1][i], h1[hs][cc + 4][lane], h1[hs][cc + 2][lane], zA[2][i],
                                 zA[0][i], t1[i], A[0], A[2], B[0], A[3], B[1], pA[i], rA[i],
                                 A[1], a1, a2);
@@ -1959,7 +1964,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
       for (int i = 0; i <= NPW; ++i) {
         if (i == NPW && w != 1 && w != 2) break;
         const int cc = ccol(i);
-        const f4v A = cfa[b + 2][cc + 2], B = cfb[b + 2][cc + 2];
+        const v4 A = cfa[b + 2][cc + 2], B = cfb[b + 2][cc + 2];
         const T z = cheb_node_t(z1h[1][i], h2[hs][cc + 3][lane], h2[hs][cc + 1][lane], z1n[i],
                                 z1h[0][i], t2[i], A[0], A[2], B[0], A[3], B[1], zA[0][i], rB[i],
                                 A[1], b1, b2);
@@ -1980,7 +1985,7 @@ __global__ __launch_bounds__(WG3, 4) void k_cheb3_strip(Coef<float> c, Work wk,
 #pragma unroll
       for (int i = 0; i < NPW; ++i) {
         const int jc = ccol(i);
-        const f4v A = cfa[b + 1][jc + 2], B = cfb[b + 1][jc + 2];
+        const v4 A = cfa[b + 1][jc + 2], B = cfb[b + 1][jc + 2];
         const T z = cheb_node_t(z2h[1][i], h3[hs][jc + 2][lane], h3[hs][jc][lane], z2n[i],
                                 z2h[0][i], t3[i], A[0], A[2], B[0], A[3], B[1], z1h[0][i], rC[i],
                                 A[1], c1, c2);
@@ -2700,7 +2705,7 @@ static void reduce(const SolveBuffers& b, int m0, int nmat, int len, hipStream_t
 // that forms z_1 from R itself, so that no kernel writes z_1.
 template <typename T>
 static bool cheb_folds_z1(const SolveBuffers& b) {
-  return b.resident > 0 || (sizeof(T) == 4 && b.cheb_k > 3 && b.TA != nullptr);
+  return b.resident > 0 || (b.cheb_k > 3 && b.TA != nullptr);
 }
 
 // All steps in one launch (k_cheb_resident; b.resident: nodes of the group's
@@ -2726,7 +2731,7 @@ static T* cheb_resident(const Coef<T>& c, const SolveBuffers& b, hipStream_t st,
 }
 
 // Chebyshev steps j = 1 .. cheb_k - 1 from z_1: three per pass while three
-// remain (float32), then two per pass while two remain, then one.  z_1 =
+// remain, then two per pass while two remain, then one.  z_1 =
 // D^-1 R / theta is in Za unless the first pass is a three-step pass, which
 // forms it from R (cheb_folds_z1).  A pass reads z_j, z_{j-1} and
 // writes its last two iterates (or one) to arrays that hold neither; the
@@ -2750,50 +2755,48 @@ static T* cheb_steps(const Coef<T>& c, const SolveBuffers& b, hipStream_t st, T*
   };
   const T ith = (T)b.cheb_invtheta;
   int j = 1;
-  if constexpr (sizeof(T) == 4) {
-    while (j + 2 < b.cheb_k && b.TA) {
-      const int f1 = free_slot(-1), f2 = free_slot(f1);
-      T* o2 = (j + 3 == b.cheb_k && last) ? last : buf[f2];
-      T a1, a2, b1, b2, c1, c2;
-      coef(j, a1, a2);
-      coef(j + 1, b1, b2);
-      coef(j + 2, c1, c2);
-      const T* zp = prev < 0 ? nullptr : buf[prev];
-      if (b.max_tsv_slots > 0) {
-        const int gcap = std::max(1, TSV_GRID_CAP / std::max(b.n_act, 1));
-        const dim3 ga(std::min((5 * b.max_tsv_slots + TSV_WAVES - 1) / TSV_WAVES, gcap),
-                      b.n_act);
-        const dim3 gb(std::min((b.max_tsv_slots + TSV_WAVES - 1) / TSV_WAVES, gcap), b.n_act);
-        const dim3 tb(64 * TSV_WAVES);
-        const T* zc = (const T*)buf[cur];
-        if (prev < 0) {
-          hipLaunchKernelGGL((k_cheb_tsv_a<T, false>), ga, tb, 0, st, c, b.work, b.act, zc, zp, R,
-                             (T*)b.TA, a1, a2, ith);
-          hipLaunchKernelGGL((k_cheb_tsv_b<T, false>), gb, tb, 0, st, c, b.work, b.act, zc, R,
-                             (const T*)b.TA, (T*)b.TB, b1, b2, ith);
-        } else {
-          hipLaunchKernelGGL((k_cheb_tsv_a<T, true>), ga, tb, 0, st, c, b.work, b.act, zc, zp, R,
-                             (T*)b.TA, a1, a2, ith);
-          hipLaunchKernelGGL((k_cheb_tsv_b<T, true>), gb, tb, 0, st, c, b.work, b.act, zc, R,
-                             (const T*)b.TA, (T*)b.TB, b1, b2, ith);
-        }
+  while (j + 2 < b.cheb_k && b.TA) {
+    const int f1 = free_slot(-1), f2 = free_slot(f1);
+    T* o2 = (j + 3 == b.cheb_k && last) ? last : buf[f2];
+    T a1, a2, b1, b2, c1, c2;
+    coef(j, a1, a2);
+    coef(j + 1, b1, b2);
+    coef(j + 2, c1, c2);
+    const T* zp = prev < 0 ? nullptr : buf[prev];
+    if (b.max_tsv_slots > 0) {
+      const int gcap = std::max(1, TSV_GRID_CAP / std::max(b.n_act, 1));
+      const dim3 ga(std::min((5 * b.max_tsv_slots + TSV_WAVES - 1) / TSV_WAVES, gcap),
+                    b.n_act);
+      const dim3 gb(std::min((b.max_tsv_slots + TSV_WAVES - 1) / TSV_WAVES, gcap), b.n_act);
+      const dim3 tb(64 * TSV_WAVES);
+      const T* zc = (const T*)buf[cur];
+      if (prev < 0) {
+        hipLaunchKernelGGL((k_cheb_tsv_a<T, false>), ga, tb, 0, st, c, b.work, b.act, zc, zp, R,
+                           (T*)b.TA, a1, a2, ith);
+        hipLaunchKernelGGL((k_cheb_tsv_b<T, false>), gb, tb, 0, st, c, b.work, b.act, zc, R,
+                           (const T*)b.TA, (T*)b.TB, b1, b2, ith);
+      } else {
+        hipLaunchKernelGGL((k_cheb_tsv_a<T, true>), ga, tb, 0, st, c, b.work, b.act, zc, zp, R,
+                           (T*)b.TA, a1, a2, ith);
+        hipLaunchKernelGGL((k_cheb_tsv_b<T, true>), gb, tb, 0, st, c, b.work, b.act, zc, R,
+                           (const T*)b.TA, (T*)b.TB, b1, b2, ith);
       }
-      T* o1 = j + 3 == b.cheb_k ? nullptr : buf[f1];  // the last pass's z_{j+2} is not read
-      if (prev < 0)
-        hipLaunchKernelGGL((k_cheb3_strip<false>), g, dim3(WG3), 0, st, c, b.work,
-                           (const T*)buf[cur], zp, R, (const T*)b.TA, (const T*)b.TB, o1, o2, a1,
-                           a2, b1, b2, c1, c2, ith);
-      else
-        hipLaunchKernelGGL((k_cheb3_strip<true>), g, dim3(WG3), 0, st, c, b.work,
-                           (const T*)buf[cur], zp, R, (const T*)b.TA, (const T*)b.TB, o1, o2, a1,
-                           a2, b1, b2, c1, c2, ith);
-      j += 3;
-      if (o2 == last) return last;
-      prev = f1;
-      cur = f2;
     }
+    T* o1 = j + 3 == b.cheb_k ? nullptr : buf[f1];  // the last pass's z_{j+2} is not read
+    if (prev < 0)
+      hipLaunchKernelGGL((k_cheb3_strip<T, false>), g, dim3(WG3), 0, st, c, b.work,
+                         (const T*)buf[cur], zp, R, (const T*)b.TA, (const T*)b.TB, o1, o2, a1,
+                         a2, b1, b2, c1, c2, ith);
+    else
+      hipLaunchKernelGGL((k_cheb3_strip<T, true>), g, dim3(WG3), 0, st, c, b.work,
+                         (const T*)buf[cur], zp, R, (const T*)b.TA, (const T*)b.TB, o1, o2, a1,
+                         a2, b1, b2, c1, c2, ith);
+    j += 3;
+    if (o2 == last) return last;
+    prev = f1;
+    cur = f2;
   }
-  while (j + 1 < b.cheb_k) {  // two steps per pass (float64 throughout)
+  while (j + 1 < b.cheb_k) {  // two steps per pass
     const int f1 = free_slot(-1), f2 = free_slot(f1);
     T* o2 = (j + 2 == b.cheb_k && last) ? last : buf[f2];
     T a1, a2, b1, b2;
