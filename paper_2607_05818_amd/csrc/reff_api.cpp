@@ -604,13 +604,35 @@ int64_t max_strip_rows(int64_t nx, size_t word) {
   return std::max<int64_t>(0, (int64_t(1) << 31) / (nx * S * (int64_t)word) - 8);
 }
 
+// Rows per strip for the float64 Chebyshev passes, which run one workgroup
+// per CU: a launch takes as many rounds as its strips fill the 256 CUs, and a
+// strip of H rows about H + 7 row times (four halo rows and the prologue), so
+// the height with the fewest row times in all is taken, the taller one on a tie
+// (less halo traffic), up to 64 rows so that a block that runs on alone still
+// spreads.  About 1024 strips per launch, the float32 target, meant 8-row
+// strips in four rounds at one block of 4 x 256 x 256 and 6-row strips in five
+// at four blocks of 3 x 128 x 128: a pass took 194 and 166 us, with one round
+// of 32 and 26 rows 153 and 127 us.
+int64_t fp64_strip_rows(const std::vector<PlanDesc>& plans) {
+  constexpr int64_t CUS = 256, EXTRA = 7;
+  int64_t best = 8, cost = INT64_MAX;
+  for (int64_t H = 8; H <= 64; ++H) {
+    int64_t n = 0;
+    for (const PlanDesc& p : plans)
+      n += p.n / p.plane * ((p.nx + CH - 1) / CH) * ((p.plane / p.nx + H - 1) / H);
+    const int64_t c = (n + CUS - 1) / CUS * (H + EXTRA);
+    if (c <= cost) cost = c, best = H;
+  }
+  return best;
+}
+
 // Strips for the stencil kernel of a group (float32 block variant): every
 // block's tiers are cut into CH-wide x strips and, when that gives too few
 // workgroups, into y segments, about TARGET_UNITS strips in total (and no
 // more than max_strip_rows rows each); at least `floor` per block while the
 // segments keep 64 rows or more (as for work units).
 void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
-                 size_t word, int target = TARGET_UNITS, int floor = 0) {
+                 size_t word, int target = TARGET_UNITS, int floor = 0, int64_t fixed_rows = 0) {
   int64_t rows = 0;
   for (const PlanDesc& p : plans) rows += p.n;
   if (floor > 0) {
@@ -632,7 +654,8 @@ void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
     want = std::max<int64_t>(want, std::min<int64_t>(floor, nt * nsx * std::max<int64_t>(1, ny / 64)));
     const int64_t ysegs = std::min<int64_t>(ny, std::max<int64_t>(1, (want + nt * nsx - 1) / (nt * nsx)));
     const int64_t hcap = max_strip_rows(nx, word);
-    const int64_t H = std::min<int64_t>((ny + ysegs - 1) / ysegs, std::max<int64_t>(hcap, 1));
+    const int64_t segs = fixed_rows > 0 ? (ny + fixed_rows - 1) / fixed_rows : ysegs;
+    const int64_t H = std::min<int64_t>((ny + segs - 1) / segs, std::max<int64_t>(hcap, 1));
     p.strip_begin = (int32_t)strips.size();
     for (int64_t t = 0; t < nt; ++t)
       for (int64_t y0 = 0; y0 < ny; y0 += H)
@@ -860,7 +883,11 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     nu = (int)units.size();
     strips.clear();
     const bool cheb = !o.indep && o.cheb > 1;
-    if ((fp32 || cheb) && !o.indep) make_strips(plans, strips, tsz, tc.strips, floor);
+    if ((fp32 || cheb) && !o.indep) {
+      // a tuning database's entry stands for the target of either precision
+      const int64_t fixed = fp32 || o.tune_db ? 0 : fp64_strip_rows(plans);
+      make_strips(plans, strips, tsz, tc.strips, floor, fixed);
+    }
     ns = (int)strips.size();
     // ---- buffers
     reff_status rs;
