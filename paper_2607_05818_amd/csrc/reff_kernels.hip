@@ -381,15 +381,43 @@ __global__ __launch_bounds__(WG, 4) void k_stencil_gram(Coef<T> c, Work wk,
       }
       continue;
     }
-    // All loads of the chunk first (rows past the unit's end are clamped to
-    // its last row and zeroed afterwards), so none waits behind a branch.
+    // All loads of the chunk first (clamped where they are past the block's or
+    // the unit's end, and zeroed when staged where they are no rows of the
+    // unit).  A wave's nodes are consecutive: their rows and their east and
+    // west neighbours are six rows.  The sum of stencil_row; a coupling that
+    // does not exist is 0 and multiplies a finite value, and TSV partners are
+    // read where a node has them (wave-uniform).  In float64 that fits the 128
+    // registers of two workgroups per CU: with seven rows per node 41 of them
+    // were spilled and the kernel took 382 us at 4 x 256 x 256, now 239.
+    T yw[NODES_PER_WAVE + 2], yn[NODES_PER_WAVE], ys[NODES_PER_WAVE];
     T yv[NODES_PER_WAVE], rv[NODES_PER_WAVE], qv[NODES_PER_WAVE];
+    const int64_t v0 = base + w * NODES_PER_WAVE, vend = u.pd.vbase + u.pd.n - 1;
+    const int64_t nx = u.pd.nx, cofs = u.pd.cbase - u.pd.vbase;
+#pragma unroll
+    for (int i = 0; i < NODES_PER_WAVE + 2; ++i)
+      yw[i] = Y[min(max(v0 + i - 1, u.pd.vbase), vend) * S + lane];
 #pragma unroll
     for (int i = 0; i < NODES_PER_WAVE; ++i) {
-      const int64_t v = min(base + w * NODES_PER_WAVE + i, u.end - 1);
-      yv[i] = Y[v * S + lane];
+      const int64_t v = min(v0 + i, u.end - 1);
+      yn[i] = Y[(v + nx <= vend ? v + nx : v) * S + lane];
+      ys[i] = Y[(v - nx >= u.pd.vbase ? v - nx : v) * S + lane];
       rv[i] = R[v * S + lane];
-      qv[i] = stencil_row<T, T>(c, Y, u.pd, v, lane);
+    }
+#pragma unroll
+    for (int i = 0; i < NODES_PER_WAVE; ++i) {
+      const int64_t v = min(v0 + i, u.end - 1), ci = v + cofs, lv = v - u.pd.vbase;
+      const T ce = c.cE[ci], cn = c.cN[ci];
+      const T cw = lv >= 1 ? c.cE[ci - 1] : T(0);
+      const T cs = lv >= nx ? c.cN[ci - nx] : T(0);
+      yv[i] = yw[i + 1];
+      qv[i] = c.d[ci] * yv[i] - ce * yw[i + 2] - cw * yw[i] - cn * yn[i] - cs * ys[i];
+      const int sl = c.slot[ci];
+      if (sl >= 0) {
+        const T gu = c.up[sl], gd = c.dn[sl];
+        const T yu = Y[(gu != T(0) ? v + u.pd.plane : v) * S + lane];
+        const T yd = Y[(gd != T(0) ? v - u.pd.plane : v) * S + lane];
+        qv[i] = qv[i] - gu * yu - gd * yd;
+      }
     }
 #pragma unroll
     for (int i = 0; i < NODES_PER_WAVE; ++i) {
@@ -793,8 +821,11 @@ __global__ __launch_bounds__(WG, 4) void k_update_r(Coef<T> c, Work wk,
 // preconditioner) and Y = Z - P B.  With WITH_D (block variant with ZBUF
 // only) the kernel also takes the solution update D += P A of this
 // iteration from K2: it reads P anyway, so P is read once per iteration.
+// With two S x S operands in registers that variant needs 174 VGPRs in
+// float64 and runs one workgroup per CU: at 128 it spilled 47 of them and took
+// 317 us instead of 186 (4 x 256 x 256, one block).
 template <typename T, bool DIAG, bool ZBUF = false, bool WITH_D = false>
-__global__ __launch_bounds__(WG, 4) void k_update_y(Coef<T> c, Work wk,
+__global__ __launch_bounds__(WG, sizeof(T) == 8 && WITH_D ? 2 : 4) void k_update_y(Coef<T> c, Work wk,
                                                     const T* __restrict__ delta,
                                                     const T* __restrict__ R,
                                                     const T* __restrict__ P, T* __restrict__ Y,
