@@ -2142,7 +2142,31 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ part,
 constexpr int SM_THREADS = 256;
 typedef double Mat[S][S + 1];
 
-__device__ void convergence_update(BlockState* st, const double* dpsi, double tol) {
+// Columns of a block at their sweep steps, times 1/sqrt(pivot).
+struct SweepBlock {
+  double col[S][17];
+};
+
+// A column's state before this iteration (thread k < S), read at the start of
+// the kernel so that nothing waits for it at the end.
+struct ColumnState {
+  int it;
+  double psi, ref, hist[HIST - 1];  // increments of the last HIST - 1 iterations, oldest first
+};
+
+__device__ __forceinline__ void load_column(const BlockState* st, ColumnState& c) {
+  const int k = threadIdx.x;
+  c.it = st->it;
+  if (k < S) {
+    c.psi = st->psi[k];
+    c.ref = st->ref[k];
+#pragma unroll
+    for (int h = 0; h < HIST - 1; ++h) c.hist[h] = st->hist[(c.it + 1 + h) % HIST][k];
+  }
+}
+
+__device__ void convergence_update(BlockState* st, const ColumnState& c, const double* dpsi,
+                                   double tol) {
   // Column k (thread k < S) adds its increment, keeps the last HIST
   // increments and extrapolates what is left geometrically from the sums A,
   // B of |increment| over the older and the newer half of that window:
@@ -2151,26 +2175,27 @@ __device__ void convergence_update(BlockState* st, const double* dpsi, double to
   // rather than slows down, so the geometric tail tends to over-estimate.
   __shared__ int nconv;
   const int k = threadIdx.x;
-  const int it = st->it;
+  const int it = c.it;
   if (k == 0) nconv = 0;
   __syncthreads();
   if (k < S) {
     const double d = dpsi[k];
-    const double psi = st->psi[k] + d;
+    const double psi = c.psi + d;
     st->psi[k] = psi;
     st->hist[it % HIST][k] = d;
     const int itn = it + 1;
     double est = INFINITY;
     if (itn >= HIST) {
       double A = 0.0, B = 0.0;
+#pragma unroll
       for (int h = 0; h < HIST; ++h) {
-        const double val = fabs(st->hist[(itn - HIST + h) % HIST][k]);
+        const double val = fabs(h < HIST - 1 ? c.hist[h] : d);
         if (h < HIST / 2)
           A += val;
         else
           B += val;
       }
-      const double ref = fmax(fabs(psi), st->ref[k]);
+      const double ref = fmax(fabs(psi), c.ref);
       if (B == 0.0) {
         est = 0.0;
       } else if (A > B && ref > 0.0) {
@@ -2184,7 +2209,10 @@ __device__ void convergence_update(BlockState* st, const double* dpsi, double to
   __syncthreads();
   if (k == 0) {
     st->it = it + 1;
-    if (nconv == S) st->all_conv = 1;
+    if (nconv == S) {
+      st->all_conv = 1;
+      st->frozen = 1;  // (every update after this one is skipped)
+    }
   }
 }
 
@@ -2257,68 +2285,107 @@ __device__ __forceinline__ double readlane64(double x, int l) {
   return __longlong_as_double(((int64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Symmetric sweep of the Jacobi-scaled matrix held in registers, over every
+// Guarded symmetric sweep of the Jacobi-scaled matrix in M (LDS), index by
 // index in order.  Index j is swept only if its current pivot (the Schur
 // complement with respect to the indices swept before it) is above eps;
-// otherwise it is dropped as numerically dependent.  Afterwards a holds
-// -(A_KK)^-1 on the kept set K.  If Tl is given, column j of the upper
-// triangular T = Sc (e_j - beta)/sqrt(pivot) is written to it (beta: the
+// otherwise it is dropped as numerically dependent (drop[j]).  Afterwards M
+// holds -(A_KK)^-1 on the kept set K.  With WITH_T, column j of the upper
+// triangular T = Sc (e_j - beta)/sqrt(pivot) is written to Tl (beta: the
 // coefficients of j on the kept earlier indices), so that T^T M T = I on K
 // and T has zero columns for dropped j.
-__device__ void sweep_regs(double (&a)[16], double eps, int* drop, const double* sc,
-                           Mat* Tl) {
+//
+// Four blocks of 16 columns: one wave sweeps a block on all 64 rows in
+// registers (lane r holds row r, the pivot row broadcast by v_readlane: no LDS
+// and no barrier in the 16 dependent steps), the others follow as one
+// matrix-core product, a 16-row strip per wave.  That product takes each
+// step's column as it stood at its step, scaled on both sides alike, A_ij -=
+// sum_p u_p(i) u_p(j), and the block's rows are copies of its columns: the
+// matrix stays symmetric to the last bit between blocks, and a Schur
+// complement is off by roundings of A only.  Near-dependent blocks need that:
+// with 64 neighbouring columns and precond_degree 1, the finished inverse of
+// the block as a factor, or multipliers against unscaled columns, took two to
+// three times the iterations.
+// A serial chain of 64 steps that every iteration waits for twice: with a
+// barrier and LDS broadcasts per step k_small1 and k_small3 took 48 and 40 us
+// on 2 x 32 x 32 nodes, now 40 and 33 (k_small2, products only: 9 and 6).
+template <bool WITH_T>
+__device__ void sweep_blocks(Mat& M, SweepBlock& sb, double eps, int* drop, const double* sc,
+                             Mat* Tl) {
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  __shared__ double rowb[2][S];
-  // j = 16 jw + jr with jr unrolled, so that every register index is a
-  // compile-time constant (a dynamic index would move a[] out of registers).
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cc = lane & 15, kr = lane >> 4;
+  uint64_t kept = 0;  // wave 0: swept indices
 #pragma unroll 1
-  for (int jw = 0; jw < 4; ++jw)
+  for (int b = 0; b < 4; ++b) {
+    if (wv == 0) {
+      double a[16];
 #pragma unroll
-  for (int jr = 0; jr < 16; ++jr) {
-    const int j = 16 * jw + jr;
-    // The matrix stays symmetric under the sweep, so row j (one full-wave
-    // store by the wave that holds it) also gives every wave column j.
-    double* rj = rowb[jr & 1];
-    if (w == jw) rj[lane] = a[jr];
-    __syncthreads();
-    const double piv = rj[j];
-    const double ck = rj[lane];  // M[j][lane] = M[lane][j]
-    const bool dj = !(piv > eps);
-    if (threadIdx.x == 0) drop[j] = dj ? 1 : 0;
-    if (Tl != nullptr && w == 0) {  // column j of T, one row per lane
-      const double rs = dj ? 0.0 : rsqrt64(piv);
-      double t = 0.0;
-      if (!dj) t = lane < j ? (drop[lane] ? 0.0 : -ck * rs) : (lane == j ? rs : 0.0);
-      (*Tl)[lane][j] = sc[lane] * t;
-    }
-    if (!dj) {
-      const double inv = rcp64(piv);
+      for (int c = 0; c < 16; ++c) a[c] = M[lane][16 * b + c];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = 16 * w + r;
-        const double ci = readlane64(a[r], j);  // M[i][j]
-        if (i == j)
-          a[r] = (lane == j) ? -inv : ck * inv;
-        else if (lane == j)
-          a[r] = ci * inv;
-        else
-          a[r] -= ci * ck * inv;
+      for (int p = 0; p < 16; ++p) {
+        const int q = 16 * b + p;
+        const double piv = readlane64(a[p], q);
+        const bool dj = !(piv > eps);
+        const double rs = dj ? 0.0 : rsqrt64(piv);
+        const double u = dj ? 0.0 : a[p] * rs;  // (a dropped column, NaN perhaps, changes nothing else)
+        sb.col[lane][p] = u;
+        if (WITH_T) {
+          const double t = lane < q ? ((kept >> lane) & 1 ? -u : 0.0) : (lane == q ? rs : 0.0);
+          (*Tl)[lane][q] = sc[lane] * t;
+        }
+        if (lane == 0) drop[q] = dj ? 1 : 0;
+        if (!dj) {
+          kept |= (uint64_t)1 << q;
+          const double inv = rcp64(piv);
+          const double f = a[p] * inv;
+          // row q becomes inv row q, as row q + (inv - 1) row q: pivots of the
+          // scaled matrix are at most 1 up to rounding, so nothing cancels
+          const double mult = lane == q ? inv - 1.0 : -f;
+#pragma unroll
+          for (int c = 0; c < 16; ++c) {
+            if (c == p) continue;
+            a[c] = fma(mult, readlane64(a[c], q), a[c]);
+          }
+          a[p] = lane == q ? -inv : f;
+        }
       }
+#pragma unroll
+      for (int c = 0; c < 16; ++c) M[lane][16 * b + c] = a[c];
     }
+    __syncthreads();
+    // rows of the block are its columns; the other strips take the product
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j == b) continue;
+      d4v acc;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * wv + kr + 4 * r;
+        acc[r] = wv == b ? M[16 * j + cc][i] : M[i][16 * j + cc];
+      }
+      if (wv != b) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = mma(-sb.col[16 * wv + cc][4 * ks + kr], sb.col[16 * j + cc][4 * ks + kr], acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) M[16 * wv + kr + 4 * r][16 * j + cc] = acc[r];
+    }
+    __syncthreads();
   }
-  __syncthreads();
 }
 
-// C[16w+r][lane] = sum_j A[16w+r][j] * B[j][lane] with A, B in LDS.
-__device__ __forceinline__ void mm_rows(const Mat& A, const Mat& B, double (&c)[16]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// C(i, j) = sum_k A[i][k] B[k][j] of matrices in LDS on the matrix cores; wave
+// w: rows 16 w .. 16 w + 15, entry (kr + 4 r, 16 q + cc) in c[q][r].
+__device__ __forceinline__ void mm_tiles(const Mat& A, const Mat& B, d4v (&c)[4]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) c[r] = 0.0;
-  for (int j = 0; j < S; ++j) {
-    const double b = B[j][lane];
+  for (int q = 0; q < 4; ++q) c[q] = d4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < S / 4; ++ks) {
+    const double av = A[16 * w + cc][4 * ks + kr];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) c[r] += A[16 * w + r][j] * b;
+    for (int q = 0; q < 4; ++q) c[q] = mma(av, B[4 * ks + kr][16 * q + cc], c[q]);
   }
 }
 
@@ -2335,7 +2402,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_small1(const double* __restrict_
                                                        BlockState* __restrict__ st_all,
                                                        double tol, double eps, int diag,
                                                        const int32_t* __restrict__ cnt) {
-  __shared__ Mat Wi, B, PT;
+  __shared__ Mat Wi, B, PT, M;
+  __shared__ SweepBlock sb;
   __shared__ double sc[S], dpsi[S];
   __shared__ int drop[S];
   if ((int)blockIdx.x >= cnt[2]) return;
@@ -2350,6 +2418,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_small1(const double* __restrict_
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
   const bool frozen = st->frozen != 0;
+  ColumnState col;
+  load_column(st, col);
   // outputs are written at the end so that no barrier waits on global stores
   if (diag) {
     if (tid < S) {
@@ -2361,9 +2431,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_small1(const double* __restrict_
       dpsi[tid] = v >= 0 ? a * (double)P[(vbase + v) * S + tid] : 0.0;
     }
     __syncthreads();
-    if (!frozen) convergence_update(st, dpsi, tol);
-    __syncthreads();
-    if (tid == 0 && st->all_conv) st->frozen = 1;
+    if (!frozen) convergence_update(st, col, dpsi, tol);
     return;
   }
   double a[16];
@@ -2377,41 +2445,48 @@ __global__ __launch_bounds__(SM_THREADS) void k_small1(const double* __restrict_
     PT[i][lane] = v >= 0 ? (double)P[(vbase + v) * S + lane] : 0.0;
   }
   scale_regs(a, sc, nullptr);
-  sweep_regs(a, eps, drop, sc, nullptr);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) M[16 * w + r][lane] = a[r];
+  __syncthreads();
+  sweep_blocks<false>(M, sb, eps, drop, sc, nullptr);
   const double sk = sc[lane];
   const bool dk = drop[lane] != 0;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int i = 16 * w + r;
-    Wi[i][lane] = (drop[i] || dk) ? 0.0 : -a[r] * sc[i] * sk;
+    Wi[i][lane] = (drop[i] || dk) ? 0.0 : -0.5 * (M[i][lane] + M[lane][i]) * sc[i] * sk;
   }
   __syncthreads();
-  double cc[16];
-  mm_rows(Wi, B, cc);  // alpha = W1^+ W2
+  d4v cc[4];
+  mm_tiles(Wi, B, cc);  // alpha = W1^+ W2
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < 16; ++r) B[16 * w + r][lane] = frozen ? 0.0 : cc[r];
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      B[16 * w + (lane >> 4) + 4 * r][16 * q + (lane & 15)] = frozen ? 0.0 : cc[q][r];
   __syncthreads();
   // psi_k increment: row tgt_k of P times column k of alpha.
-  if (tid < S) {
+  {
     double acc = 0.0;
-    for (int j = 0; j < S; ++j) acc += PT[tid][j] * B[j][tid];
-    dpsi[tid] = acc;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc += PT[lane][16 * w + j] * B[16 * w + j][lane];
+    sb.col[lane][w] = acc;
   }
+  __syncthreads();
+  if (tid < S) dpsi[tid] = (sb.col[tid][0] + sb.col[tid][1]) + (sb.col[tid][2] + sb.col[tid][3]);
   if (tid < 64) {
     const uint64_t m = __ballot(drop[tid] != 0);
     if (tid == 0) st->n_drop = __popcll(m);
   }
   __syncthreads();
-  if (!frozen) convergence_update(st, dpsi, tol);
+  if (!frozen) convergence_update(st, col, dpsi, tol);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int i = 16 * w + r;
     winv[i * S + lane] = Wi[i][lane];
     alpha_out[i * S + lane] = (T)B[i][lane];
   }
-  __syncthreads();
-  if (tid == 0 && st->all_conv) st->frozen = 1;
 }
 
 // Ks2: B = W1^+ W3.
@@ -2442,10 +2517,14 @@ __global__ __launch_bounds__(SM_THREADS) void k_small2(const double* __restrict_
     B[i][lane] = W3[i * S + lane];
   }
   __syncthreads();
-  double cc[16];
-  mm_rows(A, B, cc);
+  d4v cc[4];
+  mm_tiles(A, B, cc);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) delta_out[(16 * w + r) * S + lane] = frozen ? (T)0 : (T)cc[r];
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      delta_out[(16 * w + (lane >> 4) + 4 * r) * S + 16 * q + (lane & 15)] =
+          frozen ? (T)0 : (T)cc[q][r];
 }
 
 // Ks3: T from the guarded sweep of W4 = Y^T D Y, so that the kept columns
@@ -2461,6 +2540,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_small3(const double* __restrict_
                                                        double eps, double tau,
                                                        const int32_t* __restrict__ cnt) {
   __shared__ Mat tmp, Tl;
+  __shared__ SweepBlock sb;
   __shared__ double sc[S], floor_[S];
   __shared__ int drop[S];
   if ((int)blockIdx.x >= cnt[2]) return;
@@ -2478,7 +2558,10 @@ __global__ __launch_bounds__(SM_THREADS) void k_small3(const double* __restrict_
   double a[16];
   load_sym_regs(W4, tmp, a);
   scale_regs(a, sc, floor_);
-  sweep_regs(a, eps, drop, sc, &Tl);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tmp[16 * w + r][lane] = a[r];
+  __syncthreads();
+  sweep_blocks<true>(tmp, sb, eps, drop, sc, &Tl);
 #pragma unroll
   for (int r = 0; r < 16; ++r) Tg[(16 * w + r) * S + lane] = (T)Tl[16 * w + r][lane];
   if (first && threadIdx.x < S) st->scale0[threadIdx.x] = djj;
