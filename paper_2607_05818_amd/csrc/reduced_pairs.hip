@@ -25,7 +25,7 @@
 // The factorisation works on that subspace (null-space method): per
 // interface the last TSV's current is eliminated, I^a = Z u^a + g_a e_p with
 // Z = [I_{p-1}; -1^T], so H_Z = Z^T H Z ((p-1)(d-1) square, symmetric
-// positive definite) takes a block LDL^T factorisation, u = H_Z^-1 Z^T
+// positive definite) takes a blocked Cholesky factorisation, u = H_Z^-1 Z^T
 // (f - H E g), and the voltage differences follow from the last row of each
 // interface, y_a = f_(a,p-1) - (H I)_(a,p-1).  The paper decomposes C by LU
 // (its Sec. IV); the answer is the same, the symmetric positive definite
@@ -96,16 +96,19 @@ __global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, const doubl
 
 // ---- H_Z u = rhs for all right-hand sides, 64-row panels.
 //
-// With D_P = A_PP^-1 of panel P (after the panels before it), eliminating P
-// subtracts A_iP D_P [A_jP^T, b_P] from the trailing blocks A_ij and from the
-// right-hand sides b_i, and u_P = D_P (b_P - sum_{R after P} A_RP^T u_R): the
-// unscaled A_RP stays in place, and no factor is formed.  A panel is one
-// launch each way.  A workgroup recomputes its 64 x 64 operand D_P X (twice
-// the products of a kept one, against a launch per panel and a pass over it),
-// and the one that updates the next diagonal tile inverts it on the spot: the
-// serial chain is one tile inverse and two tile products per panel.  4 x 512
-// x 512 with 512 TSVs (1533 unknowns, 2176 right-hand sides): 7.2 ms as 164
-// launches of Cholesky, panel and update steps before.
+// With Q_P = L^-T, L L^T = A_PP of panel P (after the panels before it),
+// eliminating P subtracts (A_iP Q_P) (Q_P^T [A_jP^T, b_P]) from the trailing
+// blocks A_ij and from the right-hand sides b_i, and u_P = Q_P Q_P^T (b_P -
+// sum_{R after P} A_RP^T u_R): A_RP stays in place.  Products with the triangle
+// on both sides keep Cholesky's accuracy; with A_PP^-1 between them instead (a
+// product less) TSVs from 1e-6 to 1e6 ohm on one stack came out 3e-5 off,
+// against 3e-11 here.  A panel is one launch each way.  A workgroup recomputes
+// its two 64 x 64 operands (three times the products of kept ones, against a
+// launch per panel and a pass over them), and the one that updates the next
+// diagonal tile inverts its factor on the spot: the serial chain is one tile
+// sweep and three tile products per panel.  4 x 512 x 512 with 512 TSVs (1533
+// unknowns, 2176 right-hand sides): 1.8 ms, 7.2 ms as 164 launches of
+// Cholesky, panel and update steps before.
 
 // Loads the 64 x 64 tile at (i0, j0) of a row-major matrix (rows < M, columns
 // < N; zero outside) into LDS, transposed with TR.
@@ -146,34 +149,58 @@ __device__ __forceinline__ void tile_product(const double (*L)[TB + 1], const do
   }
 }
 
-// Inverts the diagonal tile at row o held in T (identity beyond nb rows)
-// into D[kt].
-__device__ __forceinline__ void finish_diagonal(double (*T)[TB + 1], double (*Cp)[17], int nb,
-                                                double* __restrict__ D, int* bad) {
-  invert_tile(T, Cp, nb, bad);
-  for (int e = threadIdx.x; e < TB * TB; e += 256) D[e] = T[e >> 6][e & 63];
+// Inverse of the Cholesky factor of the diagonal tile held in T (identity
+// beyond its rows), transposed (upper triangular), by way of X, into Q.  The
+// tile is scaled to a unit diagonal for the sweep; a pivot that is not
+// positive sets *bad.
+struct RootScratch {
+  SweepBlock sb;
+  double sc[TB];
+  int drop[TB];
+};
+__device__ __forceinline__ void finish_diagonal(double (*T)[TB + 1], double (*X)[TB + 1],
+                                                RootScratch& rs, double* __restrict__ Q, int* bad) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t < TB) rs.sc[t] = rsqrt64(T[t][t]);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) T[16 * w + r][lane] *= rs.sc[16 * w + r] * rs.sc[lane];
+  __syncthreads();
+  sweep_blocks<true>(T, rs.sb, 0.0, rs.drop, rs.sc, X);
+  if (t < TB && rs.drop[t]) atomicOr(bad, 1);
+  for (int e = t; e < TB * TB; e += 256) Q[e] = X[e >> 6][e & 63];
 }
 
-// D[0] = A_00^-1.
-__global__ __launch_bounds__(256) void k_ldl_first(int n, const double* __restrict__ A,
-                                                   double* __restrict__ D, int* bad) {
-  __shared__ double T[TB][TB + 1], Cp[TB][17];
+// Q[0] of panel 0.
+__global__ __launch_bounds__(256) void k_chol_first(int n, const double* __restrict__ A,
+                                                    double* __restrict__ Q, int* bad) {
+  __shared__ double T[TB][TB + 1], X[TB][TB + 1];
+  __shared__ RootScratch rs;
   const int nb = min(TB, n);
   for (int e = threadIdx.x; e < TB * TB; e += 256) {
     const int i = e >> 6, j = e & 63;
     T[i][j] = i < nb && j < nb ? A[(int64_t)i * n + j] : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
-  finish_diagonal(T, Cp, nb, D, bad);
+  finish_diagonal(T, X, rs, Q, bad);
+}
+
+__device__ __forceinline__ void store_tile(const d4v* acc, double (*T)[TB + 1]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) T[16 * w + kr + 4 * r][16 * q + cc] = acc[q][r];
 }
 
 // Eliminates panel kt (a full one: there are rows after it).  blockIdx.y =
 // row tile after the panel; blockIdx.x = column tile after the panel (lower
 // tiles only) or, past those, tile of the right-hand sides.
-__global__ __launch_bounds__(256, 2) void k_ldl_step(int n, int kt, int ntile, double* __restrict__ A,
-                                                     double* __restrict__ D, int ne,
-                                                     double* __restrict__ rhs, int* bad) {
-  __shared__ double S0[TB][TB + 1], S1[TB][TB + 1], Cp[TB][17];
+__global__ __launch_bounds__(256, 2) void k_chol_step(int n, int kt, int ntile, double* __restrict__ A,
+                                                      double* __restrict__ Q, int ne,
+                                                      double* __restrict__ rhs, int* bad) {
+  __shared__ double S0[TB][TB + 1], S1[TB][TB + 1];
+  __shared__ RootScratch rs;
   const int rest = ntile - 1 - kt, ti = kt + 1 + blockIdx.y;
   const bool mat = (int)blockIdx.x < rest;
   if (mat && blockIdx.x > blockIdx.y) return;
@@ -182,21 +209,23 @@ __global__ __launch_bounds__(256, 2) void k_ldl_step(int n, int kt, int ntile, d
   const int j0 = mat ? (kt + 1 + (int)blockIdx.x) * TB : ((int)blockIdx.x - rest) * TB;
   const int N = mat ? n : ne;
   double* C = mat ? A : rhs;
-  // D_P X, X = A_jP^T or b_P
-  stage_tile<false>(D + (size_t)kt * TB * TB, TB, 0, 0, TB, TB, S0);
+  const double* Qp = Q + (size_t)kt * TB * TB;
+  d4v wi[4], acc[4];
+  stage_tile<false>(A, n, i0, p0, n, n, S0);  // A_iP Q
+  stage_tile<false>(Qp, TB, 0, 0, TB, TB, S1);
+  __syncthreads();
+  tile_product(S0, S1, wi);
+  __syncthreads();
+  stage_tile<true>(Qp, TB, 0, 0, TB, TB, S0);  // Q^T X, X = A_jP^T or b_P
   if (mat)
     stage_tile<true>(A, n, j0, p0, n, n, S1);
   else
     stage_tile<false>(rhs, ne, p0, j0, n, ne, S1);
   __syncthreads();
-  d4v acc[4];
   tile_product(S0, S1, acc);
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) S1[16 * w + kr + 4 * r][16 * q + cc] = acc[q][r];
-  stage_tile<false>(A, n, i0, p0, n, n, S0);  // A_iP
+  store_tile(wi, S0);
+  store_tile(acc, S1);
   __syncthreads();
   tile_product(S0, S1, acc);
   const bool next = mat && blockIdx.x == 0 && blockIdx.y == 0;
@@ -217,32 +246,35 @@ __global__ __launch_bounds__(256, 2) void k_ldl_step(int n, int kt, int ntile, d
     }
   if (next) {
     __syncthreads();
-    finish_diagonal(S0, Cp, min(TB, n - i0), D + (size_t)(kt + 1) * TB * TB, bad);
+    finish_diagonal(S0, S1, rs, Q + (size_t)(kt + 1) * TB * TB, bad);
   }
 }
 
-// Back substitution of panel kt: u_P = D_P b_P (blockIdx.y == kt, into U),
-// b_i -= A_Pi^T u_P for the row tiles i before it; blockIdx.x = tile of the
-// right-hand sides.
-__global__ __launch_bounds__(256, 2) void k_ldl_back(int n, int kt, const double* __restrict__ A,
-                                                     const double* __restrict__ D, int ne,
-                                                     double* __restrict__ rhs,
-                                                     double* __restrict__ U) {
+// Back substitution of panel kt: u_P = Q_P Q_P^T b_P (blockIdx.y == kt, into
+// U), b_i -= A_Pi^T u_P for the row tiles i before it; blockIdx.x = tile of
+// the right-hand sides.
+__global__ __launch_bounds__(256, 2) void k_chol_back(int n, int kt, const double* __restrict__ A,
+                                                      const double* __restrict__ Q, int ne,
+                                                      double* __restrict__ rhs,
+                                                      double* __restrict__ U) {
   __shared__ double S0[TB][TB + 1], S1[TB][TB + 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
   const int p0 = kt * TB, i0 = (int)blockIdx.y * TB, j0 = (int)blockIdx.x * TB;
   const bool own = (int)blockIdx.y == kt;
-  stage_tile<false>(D + (size_t)kt * TB * TB, TB, 0, 0, TB, TB, S0);
+  const double* Qp = Q + (size_t)kt * TB * TB;
+  stage_tile<true>(Qp, TB, 0, 0, TB, TB, S0);
   stage_tile<false>(rhs, ne, p0, j0, n, ne, S1);
   __syncthreads();
   d4v acc[4];
   tile_product(S0, S1, acc);
+  __syncthreads();
+  stage_tile<false>(Qp, TB, 0, 0, TB, TB, S0);
+  store_tile(acc, S1);
+  __syncthreads();
+  tile_product(S0, S1, acc);
   if (!own) {
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) S1[16 * w + kr + 4 * r][16 * q + cc] = acc[q][r];
+    store_tile(acc, S1);
     stage_tile<true>(A, n, p0, i0, n, n, S0);  // A_Pi^T
     __syncthreads();
     tile_product(S0, S1, acc);
@@ -518,7 +550,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   double* drs = nullptr;
   char* tab = nullptr;
   double *dR = nullptr, *RT = nullptr, *rt = nullptr, *Rs1 = nullptr, *Rsd = nullptr;
-  double *HZ = nullptr, *D = nullptr, *rhs = nullptr, *U = nullptr;
+  double *HZ = nullptr, *Q = nullptr, *rhs = nullptr, *U = nullptr;
   double *Icur = nullptr, *selfv = nullptr, *cA = nullptr, *cB = nullptr, *G = nullptr;
   double* dout = nullptr;
   int* bad = nullptr;
@@ -536,7 +568,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
     mem.add(&Rs1, (size_t)m * p);
     mem.add(&Rsd, (size_t)n * p);
     mem.add(&HZ, (size_t)nz * nz);
-    mem.add(&D, (size_t)ntile * TB * TB);
+    mem.add(&Q, (size_t)ntile * TB * TB);
     mem.add(&rhs, (size_t)nz * ne);
     mem.add(&U, (size_t)nz * ne);
     mem.add(&Icur, (size_t)ne * p * (d - 1));
@@ -615,19 +647,19 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
       e = hipGetLastError();
     }
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_ldl_first, dim3(1), dim3(256), 0, st, nz, (const double*)HZ, D, bad);
+      hipLaunchKernelGGL(k_chol_first, dim3(1), dim3(256), 0, st, nz, (const double*)HZ, Q, bad);
       e = hipGetLastError();
     }
     const unsigned et = (unsigned)((ne + TB - 1) / TB);
     for (int kt = 0; kt + 1 < ntile && e == hipSuccess; ++kt) {
       const unsigned rest = (unsigned)(ntile - 1 - kt);
-      hipLaunchKernelGGL(k_ldl_step, dim3(rest + et, rest), dim3(256), 0, st, nz, kt, ntile, HZ, D,
+      hipLaunchKernelGGL(k_chol_step, dim3(rest + et, rest), dim3(256), 0, st, nz, kt, ntile, HZ, Q,
                          ne, rhs, bad);
       e = hipGetLastError();
     }
     for (int kt = ntile - 1; kt >= 0 && e == hipSuccess; --kt) {
-      hipLaunchKernelGGL(k_ldl_back, dim3(et, (unsigned)(kt + 1)), dim3(256), 0, st, nz, kt,
-                         (const double*)HZ, (const double*)D, ne, rhs, U);
+      hipLaunchKernelGGL(k_chol_back, dim3(et, (unsigned)(kt + 1)), dim3(256), 0, st, nz, kt,
+                         (const double*)HZ, (const double*)Q, ne, rhs, U);
       e = hipGetLastError();
     }
   }

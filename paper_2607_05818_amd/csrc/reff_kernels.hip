@@ -27,6 +27,7 @@
 // R_i = (G^-1)_ii and rises to it from below.  The "independent" variant
 // keeps only the diagonals: S ordinary PCGs side by side.
 #include "reff_internal.h"
+#include "tile_inverse.h"
 
 #include <math.h>
 
@@ -2142,11 +2143,6 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ part,
 constexpr int SM_THREADS = 256;
 typedef double Mat[S][S + 1];
 
-// Columns of a block at their sweep steps, times 1/sqrt(pivot).
-struct SweepBlock {
-  double col[S][17];
-};
-
 // A column's state before this iteration (thread k < S), read at the start of
 // the kernel so that nothing waits for it at the end.
 struct ColumnState {
@@ -2232,22 +2228,6 @@ __device__ __forceinline__ void load_sym_regs(const double* __restrict__ M, Mat&
   __syncthreads();
 }
 
-// 1/x and 1/sqrt(x) for x > 0 from the hardware estimates plus two Newton
-// steps each (full float64 accuracy, without the long IEEE division and
-// square-root sequences, which dominate a latency-bound sweep step).
-__device__ __forceinline__ double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ double rsqrt64(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * fma(-0.5 * x, y * y, 1.5);
-  return y * fma(-0.5 * x, y * y, 1.5);
-}
-
 // Jacobi scaling: sc[i] = 1/sqrt(M_ii) for live columns, 0 otherwise (empty,
 // non-finite, or not above floor_[i]); a is scaled in place.
 __device__ void scale_regs(double (&a)[16], double* sc, const double* floor_) {
@@ -2275,104 +2255,6 @@ __device__ void scale_regs(double (&a)[16], double* sc, const double* floor_) {
   const double sk = sc[lane];
 #pragma unroll
   for (int r = 0; r < 16; ++r) a[r] *= sc[16 * w + r] * sk;
-}
-
-// Lane l's value of x (l wave-uniform), as a scalar.
-__device__ __forceinline__ double readlane64(double x, int l) {
-  const int64_t b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((int64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-// Guarded symmetric sweep of the Jacobi-scaled matrix in M (LDS), index by
-// index in order.  Index j is swept only if its current pivot (the Schur
-// complement with respect to the indices swept before it) is above eps;
-// otherwise it is dropped as numerically dependent (drop[j]).  Afterwards M
-// holds -(A_KK)^-1 on the kept set K.  With WITH_T, column j of the upper
-// triangular T = Sc (e_j - beta)/sqrt(pivot) is written to Tl (beta: the
-// coefficients of j on the kept earlier indices), so that T^T M T = I on K
-// and T has zero columns for dropped j.
-//
-// Four blocks of 16 columns: one wave sweeps a block on all 64 rows in
-// registers (lane r holds row r, the pivot row broadcast by v_readlane: no LDS
-// and no barrier in the 16 dependent steps), the others follow as one
-// matrix-core product, a 16-row strip per wave.  That product takes each
-// step's column as it stood at its step, scaled on both sides alike, A_ij -=
-// sum_p u_p(i) u_p(j), and the block's rows are copies of its columns: the
-// matrix stays symmetric to the last bit between blocks, and a Schur
-// complement is off by roundings of A only.  Near-dependent blocks need that:
-// with 64 neighbouring columns and precond_degree 1, the finished inverse of
-// the block as a factor, or multipliers against unscaled columns, took two to
-// three times the iterations.
-// A serial chain of 64 steps that every iteration waits for twice: with a
-// barrier and LDS broadcasts per step k_small1 and k_small3 took 48 and 40 us
-// on 2 x 32 x 32 nodes, now 40 and 33 (k_small2, products only: 9 and 6).
-template <bool WITH_T>
-__device__ void sweep_blocks(Mat& M, SweepBlock& sb, double eps, int* drop, const double* sc,
-                             Mat* Tl) {
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int cc = lane & 15, kr = lane >> 4;
-  uint64_t kept = 0;  // wave 0: swept indices
-#pragma unroll 1
-  for (int b = 0; b < 4; ++b) {
-    if (wv == 0) {
-      double a[16];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) a[c] = M[lane][16 * b + c];
-#pragma unroll
-      for (int p = 0; p < 16; ++p) {
-        const int q = 16 * b + p;
-        const double piv = readlane64(a[p], q);
-        const bool dj = !(piv > eps);
-        const double rs = dj ? 0.0 : rsqrt64(piv);
-        const double u = dj ? 0.0 : a[p] * rs;  // (a dropped column, NaN perhaps, changes nothing else)
-        sb.col[lane][p] = u;
-        if (WITH_T) {
-          const double t = lane < q ? ((kept >> lane) & 1 ? -u : 0.0) : (lane == q ? rs : 0.0);
-          (*Tl)[lane][q] = sc[lane] * t;
-        }
-        if (lane == 0) drop[q] = dj ? 1 : 0;
-        if (!dj) {
-          kept |= (uint64_t)1 << q;
-          const double inv = rcp64(piv);
-          const double f = a[p] * inv;
-          // row q becomes inv row q, as row q + (inv - 1) row q: pivots of the
-          // scaled matrix are at most 1 up to rounding, so nothing cancels
-          const double mult = lane == q ? inv - 1.0 : -f;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            if (c == p) continue;
-            a[c] = fma(mult, readlane64(a[c], q), a[c]);
-          }
-          a[p] = lane == q ? -inv : f;
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 16; ++c) M[lane][16 * b + c] = a[c];
-    }
-    __syncthreads();
-    // rows of the block are its columns; the other strips take the product
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j == b) continue;
-      d4v acc;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * wv + kr + 4 * r;
-        acc[r] = wv == b ? M[16 * j + cc][i] : M[i][16 * j + cc];
-      }
-      if (wv != b) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          acc = mma(-sb.col[16 * wv + cc][4 * ks + kr], sb.col[16 * j + cc][4 * ks + kr], acc);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) M[16 * wv + kr + 4 * r][16 * j + cc] = acc[r];
-    }
-    __syncthreads();
-  }
 }
 
 // C(i, j) = sum_k A[i][k] B[k][j] of matrices in LDS on the matrix cores; wave
@@ -2561,7 +2443,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_small3(const double* __restrict_
 #pragma unroll
   for (int r = 0; r < 16; ++r) tmp[16 * w + r][lane] = a[r];
   __syncthreads();
-  sweep_blocks<true>(tmp, sb, eps, drop, sc, &Tl);
+  sweep_blocks<true>(tmp, sb, eps, drop, sc, Tl);
 #pragma unroll
   for (int r = 0; r < 16; ++r) Tg[(16 * w + r) * S + lane] = (T)Tl[16 * w + r][lane];
   if (first && threadIdx.x < S) st->scale0[threadIdx.x] = djj;

@@ -1,6 +1,7 @@
-// Inverse of one 64 x 64 symmetric positive definite tile by a workgroup of
-// four waves (device code shared by the sparse-direct fronts and the reduced
-// pair system).
+// Elimination of one 64 x 64 symmetric positive definite tile by a workgroup of
+// four waves: the plain inverse (sparse-direct fronts, whose M-matrices lose
+// nothing in it), and a guarded symmetric sweep (block solver, reduced pair
+// system).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,6 +20,22 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
   return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// 1/x and 1/sqrt(x) for x > 0 from the hardware estimates plus two Newton
+// steps each (full float64 accuracy, without the long IEEE division and
+// square-root sequences, which dominate a latency-bound sweep step).
+__device__ __forceinline__ double rcp64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+__device__ __forceinline__ double rsqrt64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * fma(-0.5 * x, y * y, 1.5);
+  return y * fma(-0.5 * x, y * y, 1.5);
 }
 
 // Inverse of the symmetric positive definite w x w matrix in T (64 x 64 in
@@ -87,6 +104,102 @@ __device__ __forceinline__ void invert_tile(double (*T)[TILE + 1], double (*Cp)[
       for (int r = 0; r < 4; ++r)
         T[16 * wv + kr + 4 * r][16 * j + cc] =
             j == b ? Cp[16 * wv + kr + 4 * r][cc] : acc[j][r];
+    __syncthreads();
+  }
+}
+
+// Columns of a block at their sweep steps, times 1/sqrt(pivot).
+struct SweepBlock {
+  double col[TILE][17];
+};
+
+// Guarded symmetric sweep of the Jacobi-scaled matrix in M (LDS), index by
+// index in order.  Index j is swept only if its current pivot (the Schur
+// complement with respect to the indices swept before it) is above eps;
+// otherwise it is dropped as numerically dependent (drop[j]).  Afterwards M
+// holds -(A_KK)^-1 on the kept set K.  With WITH_T, column j of the upper
+// triangular T = Sc (e_j - beta)/sqrt(pivot) is written to Tl (beta: the
+// coefficients of j on the kept earlier indices), so that T^T M T = I on K
+// and T has zero columns for dropped j.
+//
+// Four blocks of 16 columns: one wave sweeps a block on all 64 rows in
+// registers (lane r holds row r, the pivot row broadcast by v_readlane: no LDS
+// and no barrier in the 16 dependent steps), the others follow as one
+// matrix-core product, a 16-row strip per wave.  That product takes each
+// step's column as it stood at its step, scaled on both sides alike, A_ij -=
+// sum_p u_p(i) u_p(j), and the block's rows are copies of its columns: the
+// matrix stays symmetric to the last bit between blocks, and a Schur
+// complement is off by roundings of A only.  Near-dependent blocks need that:
+// with 64 neighbouring columns and precond_degree 1, the finished inverse of
+// the block as a factor, or multipliers against unscaled columns, took two to
+// three times the iterations.
+// A serial chain of 64 steps that every iteration waits for twice: with a
+// barrier and LDS broadcasts per step k_small1 and k_small3 took 48 and 40 us
+// on 2 x 32 x 32 nodes, now 40 and 33 (k_small2, products only: 9 and 6).
+template <bool WITH_T>
+__device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, int* drop,
+                             const double* sc, double (*Tl)[TILE + 1]) {
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cc = lane & 15, kr = lane >> 4;
+  uint64_t kept = 0;  // wave 0: swept indices
+#pragma unroll 1
+  for (int b = 0; b < 4; ++b) {
+    if (wv == 0) {
+      double a[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) a[c] = M[lane][16 * b + c];
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int q = 16 * b + p;
+        const double piv = lane_value(a[p], q);
+        const bool dj = !(piv > eps);
+        const double rs = dj ? 0.0 : rsqrt64(piv);
+        const double u = dj ? 0.0 : a[p] * rs;  // (a dropped column, NaN perhaps, changes nothing else)
+        sb.col[lane][p] = u;
+        if (WITH_T) {
+          const double t = lane < q ? ((kept >> lane) & 1 ? -u : 0.0) : (lane == q ? rs : 0.0);
+          Tl[lane][q] = sc[lane] * t;
+        }
+        if (lane == 0) drop[q] = dj ? 1 : 0;
+        if (!dj) {
+          kept |= (uint64_t)1 << q;
+          const double inv = rcp64(piv);
+          const double f = a[p] * inv;
+          // row q becomes inv row q, as row q + (inv - 1) row q: pivots of the
+          // scaled matrix are at most 1 up to rounding, so nothing cancels
+          const double mult = lane == q ? inv - 1.0 : -f;
+#pragma unroll
+          for (int c = 0; c < 16; ++c) {
+            if (c == p) continue;
+            a[c] = fma(mult, lane_value(a[c], q), a[c]);
+          }
+          a[p] = lane == q ? -inv : f;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 16; ++c) M[lane][16 * b + c] = a[c];
+    }
+    __syncthreads();
+    // rows of the block are its columns; the other strips take the product
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j == b) continue;
+      tile_d4 acc;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * wv + kr + 4 * r;
+        acc[r] = wv == b ? M[16 * j + cc][i] : M[i][16 * j + cc];
+      }
+      if (wv != b) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-sb.col[16 * wv + cc][4 * ks + kr],
+                                                     sb.col[16 * j + cc][4 * ks + kr], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) M[16 * wv + kr + 4 * r][16 * j + cc] = acc[r];
+    }
     __syncthreads();
   }
 }

@@ -4,6 +4,7 @@ stack.  Both sides are float64 direct solves of systems whose condition stays
 below 1e4 at these sizes, so the bar is 1e-10."""
 import numpy as np
 import pytest
+import scipy.sparse.linalg as spla
 
 from oracle import reff_oracle as ro
 from paper_2607_05818_amd import gen
@@ -28,3 +29,53 @@ def test_panel_and_tile_edges(d, p, m, n):
     got = reff.reff_reduced_pairs(nx, ny, r_t, s_t, st["tsv_xy"], st["tsv_r"], st["bump_xy"],
                                   st["load_xy"])
     assert np.max(np.abs(got - want) / want) <= 1e-10
+
+
+def _refined_floating_pairs(desc, q, n_bump):
+    """Pair resistances from potentials refined with extended-precision
+    residuals, edge by edge (the diagonal of the Laplacian is never rounded)."""
+    L = np.longdouble
+    u, v, w = ro.edge_list_fast(desc)
+    w = w.astype(L)
+    n = gen.n_nodes(desc)
+    lap = ro.laplacian(desc).tocsc()
+    keep = np.arange(1, n)  # node 0 at zero volts
+    lu = spla.splu(lap[keep][:, keep], permc_spec="MMD_AT_PLUS_A")
+    E = np.zeros((n, len(q)), L)
+    E[q, np.arange(len(q))] = 1
+    X = np.zeros((n, len(q)), L)
+    for _ in range(25):
+        cur = (X[u] - X[v]) * w[:, None]
+        res = E.copy()
+        np.add.at(res, u, -cur)
+        np.add.at(res, v, cur)
+        step = lu.solve(res[keep].astype(np.float64))
+        X[keep] += step
+    assert np.abs(step).max() <= 1e-17 * np.abs(X).max()
+    C = X[q]
+    own = np.diag(C)
+    return (own[:n_bump, None] + own[None, n_bump:] - C[:n_bump, n_bump:] -
+            C[n_bump:, :n_bump].T).astype(np.float64)
+
+
+@pytest.mark.parametrize("d,p", [(3, 20), (2, 70), (4, 44)])
+def test_tsv_resistances_over_twelve_decades(d, p):
+    """Neighbouring TSVs from 1e-6 to 1e6 ohm: panels whose condition is the
+    spread itself.  The bar is 1e-9, the relative bar of the float64 paths."""
+    from paper_2607_05818_amd import reff
+    nx = 40
+    rng = np.random.default_rng(d * 100 + p)
+    at = rng.choice(400, p, replace=False)
+    xy = np.stack([at % 20 + 3, at // 20 + 5], 1).astype(np.int32)
+    tr = 10.0 ** rng.uniform(-6, 6, (p, d - 1))
+    r_t, s_t = np.linspace(0.5, 2, d), np.linspace(1, 3, d)
+    bump = rng.integers(0, nx, (9, 2)).astype(np.int32)
+    load = rng.integers(0, nx, (17, 2)).astype(np.int32)
+    gx = np.concatenate([np.full(nx * (nx - 1), 1.0 / r) for r in r_t])
+    gy = np.concatenate([np.full(nx * (nx - 1), 1.0 / s) for s in s_t])
+    desc = gen.make_desc(d, nx, nx, gx, gy, xy, 1.0 / tr, [[0, 0]])
+    ids = lambda a, t: t * nx * nx + a[:, 1].astype(np.int64) * nx + a[:, 0]  # noqa: E731
+    want = _refined_floating_pairs(desc, np.concatenate([ids(bump, 0), ids(load, d - 1)]), 9)
+    print("[case] reduced twelve decades", d, p, flush=True)
+    got = reff.reff_reduced_pairs(nx, nx, r_t, s_t, xy, tr, bump, load)
+    assert np.max(np.abs(got - want)) / np.max(want) <= 1e-9
