@@ -52,48 +52,6 @@ constexpr int TB = 64;  // tile edge of the dense kernels
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-// C[M x N] = A B^T (float64, row-major, leading dimensions lda / ldb / ldc).
-// One workgroup (four waves) per 64 x 64 tile of C; wave w owns rows 16 w ..
-// 16 w + 15, as four 16 x 16 matrix-core accumulators; the K range is staged
-// through LDS 16 at a time.
-__global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, const double* __restrict__ A,
-                                                int64_t lda, const double* __restrict__ B,
-                                                int64_t ldb, double* __restrict__ Cm, int64_t ldc) {
-  const int i0 = blockIdx.y * TB, j0 = blockIdx.x * TB;
-  __shared__ double sA[TB][17], sB[16][TB + 1];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int cc = lane & 15, kr = lane >> 4;
-  d4v acc[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) acc[q] = d4v{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = t + 256 * e;  // 0 .. 1023: 64 rows x 16 k, k fastest
-      const int r = idx / 16, k = idx % 16, gk = k0 + k;
-      sA[r][k] = i0 + r < M && gk < K ? A[(int64_t)(i0 + r) * lda + gk] : 0.0;
-      sB[k][r] = j0 + r < N && gk < K ? B[(int64_t)(j0 + r) * ldb + gk] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const double a = sA[16 * w + cc][4 * ks + kr];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sB[4 * ks + kr][16 * q + cc], acc[q], 0,
-                                                      0, 0);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int gi = i0 + 16 * w + kr + 4 * r, gj = j0 + 16 * q + cc;
-      if (gi < M && gj < N) Cm[(int64_t)gi * ldc + gj] = acc[q][r];
-    }
-}
-
 // ---- H_Z u = rhs for all right-hand sides, 64-row panels.
 //
 // With Q_P = L^-T, L L^T = A_PP of panel P (after the panels before it),
@@ -449,8 +407,49 @@ __global__ __launch_bounds__(256) void k_reduced_post(int d, int p, int m, int n
   }
 }
 
-// R(i, j) = selfv[i] + selfv[m + j] - G[i][j].
-__global__ __launch_bounds__(256) void k_reduced_finish(int m, int n,
+// Cross term: G[z] = A B^T over part z of the 64-column steps of K (A m x K,
+// B n x K), one 64 x 64 tile per workgroup.  A step is one tile product, its
+// 32 loads per thread in flight together, and K is split until the launch has
+// CROSS_WORKGROUPS: 128 x 2048 pairs over K = 1024 are 64 tiles only, 200 us
+// with 16 columns at a time and one part, now 18 us.
+constexpr int CROSS_WORKGROUPS = 512;
+
+int cross_parts(int64_t m, int64_t n, int p) {
+  const int64_t tiles = ((m + TB - 1) / TB) * ((n + TB - 1) / TB);
+  const int64_t steps = (2 * (int64_t)p + TB - 1) / TB;
+  return (int)std::max<int64_t>(1, std::min(steps, CROSS_WORKGROUPS / tiles));
+}
+
+__global__ __launch_bounds__(256, 2) void k_cross(int m, int n, int K, const double* __restrict__ A,
+                                                  const double* __restrict__ B,
+                                                  double* __restrict__ G) {
+  __shared__ double S0[TB][TB + 1], S1[TB][TB + 1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cc = lane & 15, kr = lane >> 4;
+  const int i0 = blockIdx.y * TB, j0 = blockIdx.x * TB;
+  const int steps = (K + TB - 1) / TB, z = blockIdx.z, parts = gridDim.z;
+  d4v acc[4], sum[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum[q] = d4v{0.0, 0.0, 0.0, 0.0};
+  for (int k = steps * z / parts; k < steps * (z + 1) / parts; ++k) {
+    __syncthreads();
+    stage_tile<false>(A, K, i0, k * TB, m, K, S0);
+    stage_tile<true>(B, K, j0, k * TB, n, K, S1);
+    __syncthreads();
+    tile_product(S0, S1, acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q] += acc[q];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 16 * w + kr + 4 * r, j = j0 + 16 * q + cc;
+      if (i < m && j < n) G[((int64_t)z * m + i) * n + j] = sum[q][r];
+    }
+}
+
+// R(i, j) = selfv[i] + selfv[m + j] - sum of the parts of G[i][j].
+__global__ __launch_bounds__(256) void k_reduced_finish(int m, int n, int parts,
                                                         const double* __restrict__ selfv,
                                                         const double* __restrict__ G,
                                                         double* __restrict__ out) {
@@ -458,7 +457,9 @@ __global__ __launch_bounds__(256) void k_reduced_finish(int m, int n,
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total;
        x += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(x / n), j = (int)(x % n);
-    out[x] = selfv[i] + selfv[m + j] - G[x];
+    double g = G[x];
+    for (int z = 1; z < parts; ++z) g += G[z * total + x];
+    out[x] = selfv[i] + selfv[m + j] - g;
   }
 }
 
@@ -543,6 +544,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
   };
   const int q = p - 1, nz = q * (d - 1), ne = (int)(m + n);
   const int ntile = (nz + TB - 1) / TB;
+  const int parts = cross_parts(m, n, p);
   // the cosine tables of all tiers, or (few endpoints on a very large tier, or
   // no room for the tables) direct products tier by tier through a P x P array
   const size_t Pm = (size_t)std::max(P0, Pd);
@@ -575,7 +577,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
     mem.add(&selfv, (size_t)ne);
     mem.add(&cA, (size_t)m * 2 * p);
     mem.add(&cB, (size_t)n * 2 * p);
-    mem.add(&G, (size_t)m * n);
+    mem.add(&G, (size_t)parts * m * n);
     mem.add(&bad, 1);
     if (!out_on_device) mem.add(&dout, (size_t)m * n);
   };
@@ -671,13 +673,14 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_gemm64, dim3((unsigned)((n + TB - 1) / TB), (unsigned)((m + TB - 1) / TB)),
-                       dim3(256), 0, st, (int)m, (int)n, 2 * p, (const double*)cA, (int64_t)(2 * p),
-                       (const double*)cB, (int64_t)(2 * p), G, (int64_t)n);
+    hipLaunchKernelGGL(k_cross, dim3((unsigned)((n + TB - 1) / TB), (unsigned)((m + TB - 1) / TB),
+                                     (unsigned)parts),
+                       dim3(256), 0, st, (int)m, (int)n, 2 * p, (const double*)cA,
+                       (const double*)cB, G);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_reduced_finish, rgrid(m * n), dim3(256), 0, st, (int)m, (int)n,
+    hipLaunchKernelGGL(k_reduced_finish, rgrid(m * n), dim3(256), 0, st, (int)m, (int)n, parts,
                        (const double*)selfv, (const double*)G, out);
     e = hipGetLastError();
   }

@@ -79,3 +79,23 @@ def test_tsv_resistances_over_twelve_decades(d, p):
     print("[case] reduced twelve decades", d, p, flush=True)
     got = reff.reff_reduced_pairs(nx, nx, r_t, s_t, xy, tr, bump, load)
     assert np.max(np.abs(got - want)) / np.max(want) <= 1e-9
+
+
+def test_cross_term_in_one_part():
+    """24 x 24 tiles of pairs, whose cross term takes K in one part, against
+    the same pairs asked for in calls small enough to split it.  Both sum 2 p =
+    40 products of the same operands, in different order: 1e-12."""
+    from paper_2607_05818_amd import reff
+    rng = np.random.default_rng(4)
+    at = rng.choice(60 * 60, 20, replace=False)
+    xy = np.stack([at % 60, at // 60], 1).astype(np.int32)
+    tr = rng.uniform(0.5, 2, (20, 1))
+    bump = rng.integers(0, 60, (1500, 2)).astype(np.int32)
+    load = rng.integers(0, 60, (1490, 2)).astype(np.int32)
+    print("[case] cross term", flush=True)
+    got = reff.reff_reduced_pairs(60, 60, [1.0, 2.0], [1.5, 0.5], xy, tr, bump, load)
+    for b, c in [(0, 0), (700, 64), (1437, 1390)]:
+        want = reff.reff_reduced_pairs(60, 60, [1.0, 2.0], [1.5, 0.5], xy, tr, bump[b:b + 63],
+                                       load[c:c + 100])
+        part = got[b:b + 63, c:c + 100]
+        assert np.max(np.abs(part - want)) <= 1e-12 * np.max(want)
