@@ -2229,7 +2229,8 @@ __device__ __forceinline__ void load_sym_regs(const double* __restrict__ M, Mat&
 }
 
 // Jacobi scaling: sc[i] = 1/sqrt(M_ii) for live columns, 0 otherwise (empty,
-// non-finite, or not above floor_[i]); a is scaled in place.
+// non-finite, or not above floor_[i]); a is scaled in place, dead rows and
+// columns cleared.
 __device__ void scale_regs(double (&a)[16], double* sc, const double* floor_) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __shared__ double dg[S];
@@ -2254,7 +2255,10 @@ __device__ void scale_regs(double (&a)[16], double* sc, const double* floor_) {
   __syncthreads();
   const double sk = sc[lane];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) a[r] *= sc[16 * w + r] * sk;
+  for (int r = 0; r < 16; ++r) {
+    const double f = sc[16 * w + r] * sk;
+    a[r] = f != 0.0 ? a[r] * f : 0.0;  // a dead column's NaN would spread
+  }
 }
 
 // C(i, j) = sum_k A[i][k] B[k][j] of matrices in LDS on the matrix cores; wave

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void k_gather(const DFront* __restrict__ fr,
 __global__ __launch_bounds__(256) void k_tile(const DFront* __restrict__ fr,
                                               const int32_t* __restrict__ list, int nf, int jp,
                                               double* ar, int* bad) {
-  __shared__ double T[PT][PT + 1], Cp[PT][17];
+  __shared__ double T[PT][PT + 1];
   const int t = threadIdx.x;
   for (int fi = blockIdx.x; fi < nf; fi += gridDim.x) {
     const DFront f = fr[list[fi]];
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_tile(const DFront* __restrict__ fr,
       T[c][r] = v;
     }
     __syncthreads();
-    invert_tile(T, Cp, w, bad);
+    invert_tile(T, w, bad);
     for (int e = t; e < PT * PT; e += 256) {
       const int r = e & 63, c = e >> 6;
       if (r < w && c < w) a[(int64_t)c * f.F + r] = T[r][c];

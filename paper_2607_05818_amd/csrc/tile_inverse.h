@@ -52,37 +52,36 @@ __device__ __forceinline__ double rsqrt64(double x) {
 // waits for one (98 panels at 4 x 512 x 512): a step costs about 36
 // independent register instructions here, against a barrier, LDS reads, a
 // square root and a division when the four waves shared each column.  Per
-// panel of the root of the 4 x 512 x 512 stack: 25 us, where Cholesky and the
+// panel of the root of the 4 x 512 x 512 stack: 20 us, where Cholesky and the
 // triangular inverse took 101 us and their repetition in the inversion 60 us.
-__device__ __forceinline__ void invert_tile(double (*T)[TILE + 1], double (*Cp)[17], int w, int* bad) {
+// The tile is all the LDS it takes (33 KB: four workgroups per CU).
+__device__ __forceinline__ void invert_tile(double (*T)[TILE + 1], int w, int* bad) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int cc = lane & 15, kr = lane >> 4;
   for (int b = 0; 16 * b < w; ++b) {
     if (wv == 0) {
-      double a[16];
+      double a[16], own = 1.0;
 #pragma unroll
       for (int c = 0; c < 16; ++c) a[c] = T[lane][16 * b + c];
-      bool ok = true;
 #pragma unroll
       for (int p = 0; p < 16; ++p) {
         const int q = 16 * b + p;  // pivot row and column
-        const double piv = lane_value(a[p], q);
-        ok = ok && piv > 0.0 && std::isfinite(piv);
-        const double inv = 1.0 / piv;
-        // row q becomes inv * row q, row r loses (a_rp inv) * row q
-        const double mult = lane == q ? inv : -a[p] * inv;
-        const double keep = lane == q ? 0.0 : 1.0;
+        const double inv = rcp64(lane_value(a[p], q));
+        // row r loses (a_rp inv) * row q; row q is to be multiplied by inv,
+        // which waits for the end of the block (own): its later steps are
+        // linear in it, and no row reads it again
+        own = lane == q ? inv : own;
+        const double mult = lane == q ? 0.0 : -a[p] * inv;
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
           if (c == p) continue;
-          const double s = lane_value(a[c], q);
-          a[c] = fma(mult, s, a[c] * keep);
+          a[c] = fma(mult, lane_value(a[c], q), a[c]);
         }
-        a[p] = mult;
+        a[p] = lane == q ? 1.0 : mult;
       }
-      if (!ok && lane == 0) atomicOr(bad, 1);
+      if (!(own > 0.0 && std::isfinite(own))) atomicOr(bad, 1);
 #pragma unroll
-      for (int c = 0; c < 16; ++c) Cp[lane][c] = a[c];
+      for (int c = 0; c < 16; ++c) T[lane][16 * b + c] = a[c] * own;
     }
     __syncthreads();
     tile_d4 acc[4];
@@ -94,16 +93,17 @@ __device__ __forceinline__ void invert_tile(double (*T)[TILE + 1], double (*Cp)[
         acc[j][r] = wv == b ? 0.0 : T[16 * wv + kr + 4 * r][16 * j + cc];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
-        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-            Cp[16 * wv + cc][4 * ks + kr], T[16 * b + 4 * ks + kr][16 * j + cc], acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(T[16 * wv + cc][16 * b + 4 * ks + kr],
+                                                      T[16 * b + 4 * ks + kr][16 * j + cc], acc[j],
+                                                      0, 0, 0);
     }
     __syncthreads();  // every strip has read row block b
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      if (j == b) continue;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        T[16 * wv + kr + 4 * r][16 * j + cc] =
-            j == b ? Cp[16 * wv + kr + 4 * r][cc] : acc[j][r];
+      for (int r = 0; r < 4; ++r) T[16 * wv + kr + 4 * r][16 * j + cc] = acc[j][r];
+    }
     __syncthreads();
   }
 }
@@ -135,7 +135,7 @@ struct SweepBlock {
 // three times the iterations.
 // A serial chain of 64 steps that every iteration waits for twice: with a
 // barrier and LDS broadcasts per step k_small1 and k_small3 took 48 and 40 us
-// on 2 x 32 x 32 nodes, now 40 and 33 (k_small2, products only: 9 and 6).
+// on 2 x 32 x 32 nodes, now 36 and 30 (k_small2, products only: 9 and 6).
 template <bool WITH_T>
 __device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, int* drop,
                              const double* sc, double (*Tl)[TILE + 1]) {
@@ -154,28 +154,26 @@ __device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, 
         const int q = 16 * b + p;
         const double piv = lane_value(a[p], q);
         const bool dj = !(piv > eps);
-        const double rs = dj ? 0.0 : rsqrt64(piv);
-        const double u = dj ? 0.0 : a[p] * rs;  // (a dropped column, NaN perhaps, changes nothing else)
+        const double rs = rsqrt64(piv), inv = rcp64(piv);
+        // a dropped column changes nothing else (no branch: the steps' chains
+        // overlap, 40 -> 36 us)
+        const double u = dj ? 0.0 : a[p] * rs, f = dj ? 0.0 : a[p] * inv;
         sb.col[lane][p] = u;
         if (WITH_T) {
-          const double t = lane < q ? ((kept >> lane) & 1 ? -u : 0.0) : (lane == q ? rs : 0.0);
+          const double t = lane < q ? ((kept >> lane) & 1 ? -u : 0.0) : (lane == q && !dj ? rs : 0.0);
           Tl[lane][q] = sc[lane] * t;
         }
         if (lane == 0) drop[q] = dj ? 1 : 0;
-        if (!dj) {
-          kept |= (uint64_t)1 << q;
-          const double inv = rcp64(piv);
-          const double f = a[p] * inv;
-          // row q becomes inv row q, as row q + (inv - 1) row q: pivots of the
-          // scaled matrix are at most 1 up to rounding, so nothing cancels
-          const double mult = lane == q ? inv - 1.0 : -f;
+        kept |= (uint64_t)(dj ? 0 : 1) << q;
+        // row q becomes inv row q, as row q + (inv - 1) row q: pivots of the
+        // scaled matrix are at most 1 up to rounding, so nothing cancels
+        const double mult = dj ? 0.0 : lane == q ? inv - 1.0 : -f;
 #pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            if (c == p) continue;
-            a[c] = fma(mult, lane_value(a[c], q), a[c]);
-          }
-          a[p] = lane == q ? -inv : f;
+        for (int c = 0; c < 16; ++c) {
+          if (c == p) continue;
+          a[c] = fma(mult, lane_value(a[c], q), a[c]);
         }
+        a[p] = dj ? a[p] : lane == q ? -inv : f;
       }
 #pragma unroll
       for (int c = 0; c < 16; ++c) M[lane][16 * b + c] = a[c];
