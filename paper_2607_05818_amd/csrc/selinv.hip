@@ -8,13 +8,14 @@
 // level by level of the dissection tree (all fronts of one depth together).
 //
 // Factorisation (deepest level first): each front is a dense F x F
-// column-major block over [pivots, update set Q].  It is cleared, receives
-// the entries of G in its pivot columns, and the update matrices of its
-// children (extend-add, children of rank 0 then 1, so no two writers meet).
-// Its k pivot columns are then eliminated 64 at a time, right-looking, as a
+// column-major block over [pivots, update set Q].  Its lower triangle is
+// gathered from the update matrices of its children and receives the entries
+// of G in its pivot columns; what is above the diagonal is written before it
+// is read.  Its k pivot columns are then eliminated 64 at a time, right-looking, as a
 // block LDL^T: with P the panel and R every front row after it,
 //   D_P = A_PP^-1 (in place of A_PP),  Lhat = A_RP D_P (kept transposed in
 //   the unused upper block P x R),     A_RR -= Lhat A_RP^T  (lower).
+// (the update for two panels at a time, the second panel's columns between).
 // After the last panel the trailing Q x Q block is the update matrix passed
 // to the parent.  (D_P and Lhat are all that the inversion reads, so neither
 // a triangular factor of the panel nor its inverse is ever formed.)
@@ -66,7 +67,9 @@ struct DFront {
   int64_t piv;   // into piv_node[]: k node ids
   int64_t ybuf;  // offset of its F x 64 block in a K part's Y buffer
   int64_t part;  // offset of its row tiles' 64 x 64 partial products
-  int32_t F, k, pF, rank;
+  int64_t inv;   // into inv[]: pF positions within Q of its parent's rows, -1
+  int32_t F, k, pF;
+  int32_t child[2];  // -1: none
 };
 
 constexpr int KS = 32;  // K slice staged through LDS
@@ -169,39 +172,92 @@ __global__ void k_zero(double* __restrict__ p, int64_t n) {
     p[i] = 0.0;
 }
 
-// Entries of G into the cleared fronts (each position occurs once).
-__global__ void k_scatter(const int64_t* __restrict__ idx, const double* __restrict__ val,
-                          int64_t n, double* __restrict__ ar) {
+// Entries of G into the assembled fronts (each position occurs once).
+__global__ void k_scatter_add(const int64_t* __restrict__ idx, const double* __restrict__ val,
+                              int64_t n, double* __restrict__ ar) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
        e += (int64_t)gridDim.x * blockDim.x)
-    ar[idx[e]] = val[e];
+    ar[idx[e]] += val[e];
 }
 
-// Extend-add: the lower triangle of each rank-`rank` child's update matrix
-// (its trailing (F-k) x (F-k) block) into its parent at rel x rel.  One wave
-// per column b of the update matrix (four per workgroup, blockIdx.x walks
-// the columns), its lanes down the rows a >= b: the child's column is read
-// contiguously and the parent's rows rel[a] are increasing.
-__global__ __launch_bounds__(256) void k_extend_add(const DFront* __restrict__ fr,
-                                                    const int32_t* __restrict__ list, int nf,
-                                                    int rank, const int32_t* __restrict__ rel,
-                                                    double* ar) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// inv[f.inv + r] = a where rel[f.rel + a] = r, -1 for the parent's other rows.
+__global__ __launch_bounds__(256) void k_invert_rel(const DFront* __restrict__ fr, int nf,
+                                                    const int32_t* __restrict__ rel,
+                                                    int32_t* __restrict__ inv) {
+  for (int fi = blockIdx.x; fi < nf; fi += gridDim.x) {
+    const DFront f = fr[fi];
+    if (f.poff < 0) continue;
+    for (int r = threadIdx.x; r < f.pF; r += 256) inv[f.inv + r] = -1;
+    __syncthreads();
+    for (int a = threadIdx.x; a < f.F - f.k; a += 256) inv[f.inv + rel[f.rel + a]] = a;
+  }
+}
+
+// Assembly: the lower triangle of each front as the sum of its children's
+// update matrices (their trailing (F-k) x (F-k) blocks), child 0 before 1.
+// One wave per AC columns, its lanes down the rows: inv is increasing where
+// it is not -1, so the children's columns are read in order, and every entry
+// of the front is written once.  Bound by those bytes: 4 x 512 x 512 takes
+// 2.7 ms, where clearing the fronts and adding the children into them one
+// after the other read and wrote each entry up to three times (4.4 ms).
+constexpr int AC = 4;
+
+__global__ __launch_bounds__(256) void k_assemble(const DFront* __restrict__ fr,
+                                                  const int32_t* __restrict__ list, int nf,
+                                                  const int32_t* __restrict__ inv, double* ar) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int fi = blockIdx.y; fi < nf; fi += gridDim.y) {
     const DFront f = fr[list[fi]];
-    if (f.poff < 0 || f.rank != rank) continue;
-    const int q = f.F - f.k;
-    const int32_t* rl = rel + f.rel;
-    for (int b = blockIdx.x * 4 + w; b < q; b += gridDim.x * 4) {
-      const double* src = ar + f.off + (int64_t)(f.k + b) * f.F + f.k;
-      double* dst = ar + f.poff + (int64_t)rl[b] * f.pF;
-      for (int a = b + lane; a < q; a += 64) dst[rl[a]] += src[a];
+    const int32_t* im[2] = {inv, inv};
+    const double* u[2] = {ar, ar};
+    int64_t uF[2] = {0, 0};
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (f.child[c] >= 0) {
+        const DFront g = fr[f.child[c]];
+        im[c] = inv + g.inv;
+        u[c] = ar + g.off + (int64_t)g.k * g.F + g.k;
+        uF[c] = g.F;
+      }
+    const bool has[2] = {f.child[0] >= 0, f.child[1] >= 0};
+    for (int c0 = (blockIdx.x * 4 + w) * AC; c0 < f.F; c0 += gridDim.x * 4 * AC) {
+      const double* col[2][AC];
+      bool on[2][AC];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int j = 0; j < AC; ++j) {
+          const int b = has[c] ? im[c][min(c0 + j, f.F - 1)] : -1;
+          on[c][j] = b >= 0 && c0 + j < f.F;
+          col[c][j] = on[c][j] ? u[c] + b * uF[c] : u[c];
+        }
+      double* dst = ar + f.off + (int64_t)c0 * f.F;
+      for (int r = c0 + lane; r < f.F; r += 64) {
+        double v[AC];
+#pragma unroll
+        for (int j = 0; j < AC; ++j) v[j] = 0.0;
+        // Every load is made, from the child's first row where there is
+        // nothing to add: eight in flight per lane instead of a branch each.
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          if (has[c]) {
+            const int a = im[c][r];
+            double x[AC];
+#pragma unroll
+            for (int j = 0; j < AC; ++j) x[j] = col[c][j][max(a, 0)];
+#pragma unroll
+            for (int j = 0; j < AC; ++j) v[j] += a >= 0 && on[c][j] ? x[j] : 0.0;
+          }
+#pragma unroll
+        for (int j = 0; j < AC; ++j)
+          if (r >= c0 + j && c0 + j < f.F) dst[(int64_t)j * f.F + r] = v[j];
+      }
     }
   }
 }
 
 // Z_QQ of each front (full square) from its parent's finished block; one
-// wave per column as in k_extend_add.
+// wave per column (four per workgroup, blockIdx.x walks the columns).
 __global__ __launch_bounds__(256) void k_gather(const DFront* __restrict__ fr,
                                                 const int32_t* __restrict__ list, int nf,
                                                 const int32_t* __restrict__ rel, double* ar) {
@@ -258,6 +314,17 @@ __device__ __forceinline__ void lower_tile(int t, int& ti, int& tj) {
   tj = t - ti * (ti + 1) / 2;
 }
 
+// Update tiles of a front after panel jp, m rows left: the lower triangle
+// after an odd panel or the last one, with the products of the panel before
+// it too; after the others only the next panel's columns.  An update reads
+// and writes every entry of the triangle for 64 products each, which is
+// bound by those bytes: with two panels per pass the updates of
+// 4 x 512 x 512 take 5.9 ms instead of 6.8.
+__host__ __device__ inline int update_tiles(int F, int k, int jp) {
+  const int r0 = PT * (jp + 1) < k ? PT * (jp + 1) : k, ntile = (F - r0 + PT - 1) / PT;
+  return (jp & 1) == 0 && k > r0 ? ntile : ntile * (ntile + 1) / 2;
+}
+
 // The panel products of step jp for every front of a level (see the file
 // comment); blockIdx.x is the tile (for OP_Y, with its part of the K range).
 template <int OP>
@@ -281,11 +348,15 @@ __global__ __launch_bounds__(256, OP == OP_UPDATE ? 3 : 4) void k_front_gemm(con
       gemm_tile<false, false, true, false, false>(blockIdx.x * PT, 0, m, w, 0, w, 1.0, a_rp, F,
                                                   base + (int64_t)j0 * F + j0, F, lhat, F, sA, sB);
     } else if (OP == OP_UPDATE) {
-      if ((int)blockIdx.x >= ntile * (ntile + 1) / 2) continue;
-      int ti, tj;
-      lower_tile(blockIdx.x, ti, tj);
-      gemm_tile<true, true, false, true, true>(ti * PT, tj * PT, m, m, 0, w, -1.0, lhat, F, a_rp,
-                                               F, base + (int64_t)r0 * F + r0, F, sA, sB);
+      if ((int)blockIdx.x >= update_tiles(f.F, f.k, jp)) continue;
+      const bool pair = (jp & 1) == 0 && f.k > r0;  // the next panel brings the rest
+      int ti = blockIdx.x, tj = 0;
+      if (!pair) lower_tile(blockIdx.x, ti, tj);
+      const int before = jp & 1 ? PT : 0;  // columns of the panel before
+      const int n = pair ? min(PT, f.k - r0) : m;
+      gemm_tile<true, true, false, true, true>(ti * PT, tj * PT, m, n, 0, before + w, -1.0,
+                                               lhat - before, F, a_rp - before * F, F,
+                                               base + (int64_t)r0 * F + r0, F, sA, sB);
     } else {
       // Y = -Z_RR Lhat over A_RP; with ysplit > 1, the K range in ysplit
       // parts, each into its own Y buffer (summed by k_finish)
@@ -485,6 +556,8 @@ struct GroupDev {
   int64_t part = 0;      // doubles of the row tiles' partial products (else)
   int64_t maxq = 0;      // largest update set
   std::vector<int> mt;   // per panel: row tiles after it
+  std::vector<int> ut;   // per panel: update tiles
+  int maxF = 0;          // largest front
 };
 
 struct LevelDev {
@@ -561,13 +634,16 @@ std::vector<std::vector<GroupDev>> plan_groups(const SelinvPlan& P) {
         g.ylev += (int64_t)f.F * PT;
         g.part += front_tiles(f) * PT * PT;
         g.maxq = std::max<int64_t>(g.maxq, (int64_t)(f.F - f.k));
+        g.maxF = std::max(g.maxF, f.F);
       }
       g.mt.assign((size_t)g.max_panels, 0);
+      g.ut.assign((size_t)g.max_panels, 0);
       for (int j = 0; j < g.nf; ++j) {
         const SnFront& f = P.fronts[(size_t)L.fronts[b + (size_t)j]];
         for (int jp = 0; PT * jp < f.k; ++jp) {
           const int m = f.F - PT * jp - std::min(PT, f.k - PT * jp);
           g.mt[(size_t)jp] = std::max(g.mt[(size_t)jp], (m + PT - 1) / PT);
+          g.ut[(size_t)jp] = std::max(g.ut[(size_t)jp], update_tiles(f.F, f.k, jp));
         }
       }
       g.ysplit = group_ysplit(P, L.fronts.data() + b, (size_t)g.nf, g.ylev);
@@ -592,10 +668,12 @@ SelinvSizes selinv_sizes(const SelinvPlan& P) {
       z.part = std::max(z.part, g.part);
       if (g.ysplit > 1) z.ysp = std::max(z.ysp, g.ysplit * g.ylev);
     }
-  int64_t ent = 0;
+  int64_t ent = 0, inv = 0;
   for (const SelinvLevel& L : P.levels) ent += (int64_t)L.ent_idx.size();
+  for (const SnFront& f : P.fronts)
+    if (f.parent >= 0) inv += P.fronts[(size_t)f.parent].F;
   z.bytes = 8 * (P.arena + z.part + z.ysp + P.n) + 16 * ent +
-            (int64_t)sizeof(DFront) * (int64_t)P.fronts.size() + 4 * (int64_t)P.rel.size() +
+            (int64_t)sizeof(DFront) * (int64_t)P.fronts.size() + 4 * (inv + (int64_t)P.rel.size()) +
             8 * (int64_t)P.piv_node.size();
   return z;
 }
@@ -623,7 +701,7 @@ struct SelinvDevice {
   SelinvSizes sz;
   double *ar = nullptr, *part = nullptr, *Ysp = nullptr, *Rfull = nullptr, *vals = nullptr;
   int64_t *idx = nullptr, *piv = nullptr;
-  int32_t *rel = nullptr, *dl = nullptr;
+  int32_t *rel = nullptr, *inv = nullptr, *dl = nullptr;
   DFront* dF = nullptr;
   int* bad = nullptr;
   std::vector<void*> ptrs;       // own allocations
@@ -696,7 +774,7 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
   auto D = std::make_shared<SelinvDevice>();
   std::vector<DFront> dfr(P.fronts.size());
   std::vector<int32_t> lists;
-  int64_t n_ent = 0;
+  int64_t n_ent = 0, n_inv = 0;
   D->sz = selinv_sizes(P);
   auto groups = plan_groups(P);
   D->lv.resize(P.levels.size());
@@ -720,8 +798,10 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
         x.piv = f.piv;
         x.F = f.F;
         x.k = f.k;
+        x.child[0] = x.child[1] = -1;
         x.pF = f.parent >= 0 ? P.fronts[(size_t)f.parent].F : 0;
-        x.rank = f.rank;
+        x.inv = n_inv;
+        n_inv += x.pF;
         x.ybuf = yb;
         x.part = pa;
         yb += (int64_t)f.F * PT;
@@ -732,13 +812,15 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
     lists.insert(lists.end(), L.fronts.begin(), L.fronts.end());
     V.groups = std::move(groups[d]);
   }
+  for (size_t i = 0; i < P.fronts.size(); ++i)
+    if (P.fronts[i].parent >= 0) dfr[(size_t)P.fronts[i].parent].child[P.fronts[i].rank] = (int32_t)i;
   hipError_t e = hipSuccess;
   if (use_cache) {
     const SelinvSizes& z = D->sz;
     const size_t total = aligned(8 * (size_t)P.arena) + aligned(8 * (size_t)z.part) +
                          aligned(8 * (size_t)z.ysp) + aligned(8 * (size_t)P.n) + aligned(4) +
                          2 * aligned(8 * (size_t)n_ent) + aligned(8 * P.piv_node.size()) +
-                         aligned(4 * P.rel.size()) + aligned(4 * lists.size()) +
+                         aligned(4 * P.rel.size()) + aligned(4 * (size_t)n_inv) + aligned(4 * lists.size()) +
                          aligned(sizeof(DFront) * dfr.size());
     bool cached = false;
     e = D->reserve(total, cached);
@@ -765,6 +847,14 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
   if (e == hipSuccess) e = D->put(&D->rel, P.rel);
   if (e == hipSuccess) e = D->put(&D->dl, lists);
   if (e == hipSuccess) e = D->put(&D->dF, dfr);
+  if (e == hipSuccess) e = D->get(&D->inv, (size_t)n_inv);
+  if (e == hipSuccess && !dfr.empty()) {
+    hipLaunchKernelGGL(k_invert_rel, dim3((unsigned)std::min<size_t>(dfr.size(), 65536)), dim3(256),
+                       0, nullptr, (const DFront*)D->dF, (int)dfr.size(), (const int32_t*)D->rel,
+                       D->inv);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  }
   if (e != hipSuccess) {
     s = dev_status(e, "selected inversion: allocation / upload");
     return nullptr;
@@ -801,21 +891,15 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
   const int nlev = (int)P.levels.size();
   // factorisation, deepest level first
   for (int d = nlev - 1; d >= 0 && e == hipSuccess; --d) {
-    const SelinvLevel& L = P.levels[(size_t)d];
     const LevelDev& V = D.lv[(size_t)d];
     if (V.nf == 0) continue;
-    const int64_t span = L.arena_end - L.arena_begin;
-    if (span > 0) hipLaunchKernelGGL(k_zero, flat(span), dim3(256), 0, st_, ar + L.arena_begin, span);
+    for (const GroupDev& G : V.groups)
+      if (G.maxF > 0)
+        hipLaunchKernelGGL(k_assemble, dim3((unsigned)((G.maxF + 4 * AC - 1) / (4 * AC)), gy(G.nf)),
+                           dim3(256), 0, st_, dF, dl + G.list_off, G.nf, (const int32_t*)D.inv, ar);
     if (V.ent_n > 0)
-      hipLaunchKernelGGL(k_scatter, flat(V.ent_n), dim3(256), 0, st_, D.idx + V.ent_off,
+      hipLaunchKernelGGL(k_scatter_add, flat(V.ent_n), dim3(256), 0, st_, D.idx + V.ent_off,
                          D.vals + V.ent_off, V.ent_n, ar);
-    if (d + 1 < nlev)
-      for (int rank = 0; rank < 2; ++rank)
-        for (const GroupDev& C : D.lv[(size_t)d + 1].groups) {
-          const unsigned gx = (unsigned)std::max<int64_t>(1, (C.maxq + 3) / 4);
-          hipLaunchKernelGGL(k_extend_add, dim3(gx, gy(C.nf)), dim3(256), 0, st_, dF,
-                             dl + C.list_off, C.nf, rank, rel, ar);
-        }
     for (const GroupDev& G : V.groups) {
       const int32_t* l = dl + G.list_off;
       for (int jp = 0; jp < G.max_panels; ++jp) {
@@ -824,7 +908,7 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
         if (mt == 0) continue;
         hipLaunchKernelGGL(k_front_gemm<OP_LHAT>, dim3((unsigned)mt, gy(G.nf)), dim3(256), 0,
                            st_, dF, l, G.nf, jp, ar, mt, 1, Ysp, (int64_t)0);
-        hipLaunchKernelGGL(k_front_gemm<OP_UPDATE>, dim3((unsigned)(mt * (mt + 1) / 2), gy(G.nf)),
+        hipLaunchKernelGGL(k_front_gemm<OP_UPDATE>, dim3((unsigned)G.ut[(size_t)jp], gy(G.nf)),
                            dim3(256), 0, st_, dF, l, G.nf, jp, ar, mt, 1, Ysp, (int64_t)0);
       }
     }
