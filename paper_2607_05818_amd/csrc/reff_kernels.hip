@@ -2105,14 +2105,22 @@ __global__ __launch_bounds__(WG, 4) void k_cross_gram(Coef<T> c, Work wk,
 // ---------------------------------------------------------------- Kr
 // W[p][m][e] = sum over the units of block p of part[unit][m][e], for the
 // active blocks p = act[blockIdx.y], m in [m0, m0+nmat), e < len, summed in
-// a fixed order (deterministic).
-__global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ part,
-                                                double* __restrict__ W,
-                                                const PlanDesc* __restrict__ plans,
-                                                const int32_t* __restrict__ act, int m0,
-                                                int nmat, int len, int strips,
-                                                const int32_t* __restrict__ cnt) {
-  __shared__ double red[4][64];
+// a fixed order (deterministic).  64 entries per workgroup, GROUPS waves side
+// by side through the units, each with four loads in flight.  A few solve
+// blocks make few workgroups (64 per matrix), and four waves in each of them
+// leave most of the memory bandwidth unused: 512 units of one block took
+// 30 us, 14 with sixteen.  Sixteen are no help once the units are few (the
+// loads no longer fill the waves) or the solve blocks fill the chip.
+constexpr int REDUCE_UNITS = 64, REDUCE_WORKGROUPS = 512;
+
+template <int GROUPS>
+__global__ __launch_bounds__(64 * GROUPS) void k_reduce(const double* __restrict__ part,
+                                                        double* __restrict__ W,
+                                                        const PlanDesc* __restrict__ plans,
+                                                        const int32_t* __restrict__ act, int m0,
+                                                        int nmat, int len, int strips,
+                                                        const int32_t* __restrict__ cnt) {
+  __shared__ double red[GROUPS][64];
   if ((int)blockIdx.y >= cnt[2]) return;
   const int p = act[blockIdx.y];
   const int el = threadIdx.x & 63;
@@ -2126,16 +2134,22 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ part,
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   if (e < total) {
     int g = ub + grp;
-    for (; g + 12 < ue; g += 16) {
+    for (; g + 3 * GROUPS < ue; g += 4 * GROUPS) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] += part[((size_t)(g + 4 * q) * NGRAM + m) * S * S + off];
+      for (int q = 0; q < 4; ++q)
+        acc[q] += part[((size_t)(g + GROUPS * q) * NGRAM + m) * S * S + off];
     }
-    for (; g < ue; g += 4) acc[0] += part[((size_t)g * NGRAM + m) * S * S + off];
+    for (; g < ue; g += GROUPS) acc[0] += part[((size_t)g * NGRAM + m) * S * S + off];
   }
   red[grp][el] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   __syncthreads();
-  if (grp == 0 && e < total)
-    W[((size_t)p * NGRAM + m) * S * S + off] = (red[0][el] + red[1][el]) + (red[2][el] + red[3][el]);
+  if (grp == 0 && e < total) {
+    double sum = 0.0;
+#pragma unroll
+    for (int h = 0; h < GROUPS; h += 4)
+      sum += (red[h][el] + red[h + 1][el]) + (red[h + 2][el] + red[h + 3][el]);
+    W[((size_t)p * NGRAM + m) * S * S + off] = sum;
+  }
 }
 
 // ---------------------------------------------------------------- small
@@ -2697,7 +2711,10 @@ hipError_t launch_compact(const SolveBuffers& b, int nb, hipStream_t st) {
 // ---------------------------------------------------------------- launchers
 static void reduce(const SolveBuffers& b, int m0, int nmat, int len, hipStream_t st,
                    bool strips = false) {
-  hipLaunchKernelGGL(k_reduce, dim3((nmat * len + 63) / 64, b.n_act), dim3(256), 0, st, b.part,
+  const dim3 grid((nmat * len + 63) / 64, b.n_act);
+  const int per_block = (strips ? b.n_strips : b.n_units) / std::max(b.n_act, 1);
+  const bool wide = per_block >= REDUCE_UNITS && grid.x * grid.y <= REDUCE_WORKGROUPS;
+  hipLaunchKernelGGL(wide ? k_reduce<16> : k_reduce<4>, grid, dim3(wide ? 1024 : 256), 0, st, b.part,
                      b.W, b.work.plans, b.act, m0, nmat, len, strips ? 1 : 0, b.work.cnt);
 }
 
