@@ -145,6 +145,17 @@ __device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, 
   uint64_t kept = 0;  // wave 0: swept indices
 #pragma unroll 1
   for (int b = 0; b < 4; ++b) {
+    // pivots only fall: a block without one above eps now is dropped whole
+    // (a solve block of 16 columns takes a quarter of the steps)
+    if (__ballot(M[16 * b + cc][16 * b + cc] > eps) == 0) {
+      if (wv == 0) {
+        if (lane < 16) drop[16 * b + lane] = 1;
+        if (WITH_T)
+#pragma unroll
+          for (int p = 0; p < 16; ++p) Tl[lane][16 * b + p] = 0.0;
+      }
+      continue;
+    }
     if (wv == 0) {
       double a[16];
 #pragma unroll
@@ -200,6 +211,7 @@ __device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, 
     }
     __syncthreads();
   }
+  __syncthreads();  // drop and Tl of blocks dropped whole
 }
 
 }  // namespace reff
