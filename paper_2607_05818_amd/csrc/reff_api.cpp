@@ -612,11 +612,13 @@ int64_t max_strip_rows(int64_t nx, size_t word) {
 // spreads.  About 1024 strips per launch, the float32 target, meant 8-row
 // strips in four rounds at one block of 4 x 256 x 256 and 6-row strips in five
 // at four blocks of 3 x 128 x 128: a pass took 194 and 166 us, with one round
-// of 32 and 26 rows 153 and 127 us.
+// of 32 and 26 rows 153 and 127 us.  Small stacks go down to one row per strip:
+// with eight at least, 82 x 56 nodes were 21 strips and a solve of 12 columns
+// took 5.8 ms, now 4.7 (5.1 in two-step passes of about 1024 strips).
 int64_t fp64_strip_rows(const std::vector<PlanDesc>& plans) {
   constexpr int64_t CUS = 256, EXTRA = 7;
   int64_t best = 8, cost = INT64_MAX;
-  for (int64_t H = 8; H <= 64; ++H) {
+  for (int64_t H = 1; H <= 64; ++H) {
     int64_t n = 0;
     for (const PlanDesc& p : plans)
       n += p.n / p.plane * ((p.nx + CH - 1) / CH) * ((p.plane / p.nx + H - 1) / H);
