@@ -582,7 +582,7 @@ def surrogate_compare(reff, gen, log, rel_tol, n_train=512, n_test=16, per_test=
 def direct_full_map_compare(reff, log, h, n, reps=3):
     """The all-node map of the same 4 x 512 x 512 stack by sparse-direct
     selected inversion (reff_selinv_diag: nested dissection, multifrontal
-    float64 Cholesky and Takahashi recurrence, all numeric work on the GPU),
+    float64 block LDL^T and Takahashi recurrence, all numeric work on the GPU),
     checked node by node against the stored oracle map (float32 storage).
     The first call also builds the plan; then the median of `reps` calls."""
     import numpy as np

@@ -204,8 +204,8 @@ typedef struct {
  * R_i = (G^-1)_ii (Eq. 2 with all bumps merged into the grounded supply,
  * Sec. II-B / III-B) by sparse-direct selected inversion: nested dissection
  * of the stacked grid (walls of columns through every tier), a multifrontal
- * float64 Cholesky factorisation G = L L^T and the Takahashi recurrence for
- * the entries of G^-1 on the structure of L, all numeric work on the GPU.
+ * float64 block LDL^T factorisation of G and the Takahashi recurrence for the
+ * entries of G^-1 on the structure of its factor, all numeric work on the GPU.
  * The definition itself, to float64 rounding: there is no tolerance and no
  * iteration.  The cost does not depend on how many nodes are asked for, so
  * it is the method for full maps; block PCG (reff_solve_diag) is the method
@@ -218,7 +218,7 @@ typedef struct {
  *   st       nullable.
  * Errors: INVALID_ARG (bad id or option), OUT_OF_MEMORY (the fronts need
  * reff_selinv_info().device_bytes of device memory), DEVICE (HIP error, or
- * a Cholesky pivot that is not positive).
+ * a pivot that is not positive).
  */
 reff_status reff_selinv_diag(reff_pdn p, const int64_t* nodes, int64_t n_nodes,
                              double* R_out, const reff_solve_opts* opts,
@@ -441,8 +441,8 @@ reff_status reff_grid_pairs(int32_t M, int32_t N, double r, double s, const int3
  *   stream   hipStream_t to run on; NULL => default stream.  The call
  *            returns after R_out is written.
  * The call allocates and frees its own device work memory (about
- * 8 ((p-1)(d-1))^2 x 2 bytes for the reduced matrix and its factor, plus
- * the intra-die tables).  Errors: INVALID_ARG (d < 2, p < 1, counts < 0,
+ * 8 ((p-1)(d-1))^2 bytes for the reduced matrix, which is factorised in place,
+ * plus the intra-die tables).  Errors: INVALID_ARG (d < 2, p < 1, counts < 0,
  * non-positive or non-finite resistances, a point off the grid, duplicate
  * TSV columns, more than 65535 TSVs + bumps or TSVs + loads, NULL
  * pointers), OUT_OF_MEMORY, DEVICE (also when the reduced matrix is not
