@@ -143,11 +143,14 @@ __device__ void sweep_blocks(double (*M)[TILE + 1], SweepBlock& sb, double eps, 
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cc = lane & 15, kr = lane >> 4;
   uint64_t kept = 0;  // wave 0: swept indices
+  // Pivots only fall: a block without one above eps at the start is dropped
+  // whole (a solve block of 16 columns takes a quarter of the steps).  Every
+  // wave decides from the untouched diagonal, so all take the same barriers.
+  const uint64_t live = __ballot(M[lane][lane] > eps);
+  __syncthreads();
 #pragma unroll 1
   for (int b = 0; b < 4; ++b) {
-    // pivots only fall: a block without one above eps now is dropped whole
-    // (a solve block of 16 columns takes a quarter of the steps)
-    if (__ballot(M[16 * b + cc][16 * b + cc] > eps) == 0) {
+    if (((live >> (16 * b)) & 0xffff) == 0) {
       if (wv == 0) {
         if (lane < 16) drop[16 * b + lane] = 1;
         if (WITH_T)
