@@ -604,35 +604,51 @@ int64_t max_strip_rows(int64_t nx, size_t word) {
   return std::max<int64_t>(0, (int64_t(1) << 31) / (nx * S * (int64_t)word) - 8);
 }
 
-// Rows per strip for the float64 Chebyshev passes, which run one workgroup
-// per CU: a launch takes as many rounds as its strips fill the 256 CUs, and a
-// strip of H rows about H + 7 row times (four halo rows and the prologue), so
+// y segments of a tier of ny rows for strips of about H rows; 64 is the
+// tallest, and there a tier is cut only into segments of 64 rows or more.
+int64_t strip_segments(int64_t ny, int64_t H) {
+  return H >= 64 ? std::max<int64_t>(1, ny / 64) : (ny + H - 1) / H;
+}
+
+// Rows per strip of a group: a launch takes as many rounds as its strips fill
+// the chip's workgroup slots (`slots`: one per CU in float64, two in float32),
+// and a round the rows of a mean strip and `extra` more (halo rows, prologue), so
 // the height with the fewest row times in all is taken, the taller one on a tie
 // (less halo traffic), up to 64 rows so that a block that runs on alone still
-// spreads.  About 1024 strips per launch, the float32 target, meant 8-row
-// strips in four rounds at one block of 4 x 256 x 256 and 6-row strips in five
-// at four blocks of 3 x 128 x 128: a pass took 194 and 166 us, with one round
-// of 32 and 26 rows 153 and 127 us.  Small stacks go down to one row per strip:
-// with eight at least, 82 x 56 nodes were 21 strips and a solve of 12 columns
-// took 5.8 ms, now 4.7 (5.1 in two-step passes of about 1024 strips).
-int64_t fp64_strip_rows(const std::vector<PlanDesc>& plans) {
-  constexpr int64_t CUS = 256, EXTRA = 7;
-  int64_t best = 8, cost = INT64_MAX;
+// spreads.  The stacks of a batch converge at different times: there the rounds
+// of half the strips count as well.  Against about 1024 strips per launch whatever their rounds:
+// float64: 8-row strips in four rounds at one block of 4 x 256 x 256 and 6-row
+// strips in five at four blocks of 3 x 128 x 128 took 194 and 166 us a pass, one
+// round of 32 and 26 rows 153 and 127 us; stacks of 4000 to 12000 nodes take
+// one row per strip (12 columns on 82 x 56 nodes 4.7 ms, 5.8 with eight rows at
+// least).  float32: a batch of 24 plans of 30 to 233 nodes a side 2.4 rounds of
+// 64 rows, 97.9 ms, now 94.3; 91 samples of 2 x 158 x 195 8.5 -> 7.7 ms; 4 x 512 x
+// 512 keeps two rounds of 64.
+int64_t strip_rows(const std::vector<PlanDesc>& plans, int64_t slots, double extra) {
+  bool batch = false;
+  for (const PlanDesc& p : plans) batch = batch || p.cbase != plans[0].cbase;
+  int64_t best = 64;
+  double cost = INFINITY;
   for (int64_t H = 1; H <= 64; ++H) {
-    int64_t n = 0;
-    for (const PlanDesc& p : plans)
-      n += p.n / p.plane * ((p.nx + CH - 1) / CH) * ((p.plane / p.nx + H - 1) / H);
-    const int64_t c = (n + CUS - 1) / CUS * (H + EXTRA);
+    int64_t n = 0, rows = 0;
+    for (const PlanDesc& p : plans) {
+      const int64_t ny = p.plane / p.nx, across = p.n / p.plane * ((p.nx + CH - 1) / CH);
+      n += across * strip_segments(ny, H);
+      rows += across * ny;
+    }
+    const int64_t rounds = (n + slots - 1) / slots + (batch ? (n / 2 + slots - 1) / slots : 0);
+    const double c = (double)rounds * ((double)rows / (double)n + extra);
     if (c <= cost) cost = c, best = H;
   }
   return best;
 }
 
-// Strips for the stencil kernel of a group (float32 block variant): every
-// block's tiers are cut into CH-wide x strips and, when that gives too few
-// workgroups, into y segments, about TARGET_UNITS strips in total (and no
-// more than max_strip_rows rows each); at least `floor` per block while the
-// segments keep 64 rows or more (as for work units).
+// Strips for the stencil kernels of a group: every block's tiers are cut into
+// CH-wide x strips and y segments of about `fixed_rows` rows (strip_rows), or,
+// with fixed_rows = 0 (a tuning database's target), as many segments as make
+// about `target` strips in total, at least `floor` per block while the
+// segments keep 64 rows or more (as for work units); no more than
+// max_strip_rows rows each.
 void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
                  size_t word, int target = TARGET_UNITS, int floor = 0, int64_t fixed_rows = 0) {
   int64_t rows = 0;
@@ -656,7 +672,7 @@ void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
     want = std::max<int64_t>(want, std::min<int64_t>(floor, nt * nsx * std::max<int64_t>(1, ny / 64)));
     const int64_t ysegs = std::min<int64_t>(ny, std::max<int64_t>(1, (want + nt * nsx - 1) / (nt * nsx)));
     const int64_t hcap = max_strip_rows(nx, word);
-    const int64_t segs = fixed_rows > 0 ? (ny + fixed_rows - 1) / fixed_rows : ysegs;
+    const int64_t segs = fixed_rows > 0 ? strip_segments(ny, fixed_rows) : ysegs;
     const int64_t H = std::min<int64_t>((ny + segs - 1) / segs, std::max<int64_t>(hcap, 1));
     p.strip_begin = (int32_t)strips.size();
     for (int64_t t = 0; t < nt; ++t)
@@ -887,7 +903,7 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     const bool cheb = !o.indep && o.cheb > 1;
     if ((fp32 || cheb) && !o.indep) {
       // a tuning database's entry stands for the target of either precision
-      const int64_t fixed = fp32 || o.tune_db ? 0 : fp64_strip_rows(plans);
+      const int64_t fixed = o.tune_db ? 0 : fp32 ? strip_rows(plans, 512, 5) : strip_rows(plans, 256, 7);
       make_strips(plans, strips, tsz, tc.strips, floor, fixed);
     }
     ns = (int)strips.size();
