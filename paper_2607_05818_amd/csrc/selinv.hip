@@ -69,7 +69,7 @@ struct DFront {
   int64_t part;  // offset of its row tiles' 64 x 64 partial products
   int64_t inv;   // into inv[]: pF positions within Q of its parent's rows, -1
   int32_t F, k, pF;
-  int32_t child[2];  // -1: none
+  int32_t child[2];  // -1: none with an update matrix
 };
 
 constexpr int KS = 32;  // K slice staged through LDS
@@ -236,8 +236,9 @@ __global__ __launch_bounds__(256) void k_assemble(const DFront* __restrict__ fr,
         double v[AC];
 #pragma unroll
         for (int j = 0; j < AC; ++j) v[j] = 0.0;
-        // Every load is made, from the child's first row where there is
-        // nothing to add: eight in flight per lane instead of a branch each.
+        // Every load is made, from the child's first update row where there
+        // is nothing to add (a listed child has one): eight in flight per lane
+        // instead of a branch each.
 #pragma unroll
         for (int c = 0; c < 2; ++c)
           if (has[c]) {
@@ -798,7 +799,6 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
         x.piv = f.piv;
         x.F = f.F;
         x.k = f.k;
-        x.child[0] = x.child[1] = -1;
         x.pF = f.parent >= 0 ? P.fronts[(size_t)f.parent].F : 0;
         x.inv = n_inv;
         n_inv += x.pF;
@@ -812,8 +812,9 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
     lists.insert(lists.end(), L.fronts.begin(), L.fronts.end());
     V.groups = std::move(groups[d]);
   }
+  const auto kids = assembly_children(P);
   for (size_t i = 0; i < P.fronts.size(); ++i)
-    if (P.fronts[i].parent >= 0) dfr[(size_t)P.fronts[i].parent].child[P.fronts[i].rank] = (int32_t)i;
+    for (int c = 0; c < 2; ++c) dfr[i].child[c] = kids[i][(size_t)c];
   hipError_t e = hipSuccess;
   if (use_cache) {
     const SelinvSizes& z = D->sz;

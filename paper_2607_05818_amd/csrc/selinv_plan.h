@@ -23,6 +23,7 @@
 
 #include <stdint.h>
 
+#include <array>
 #include <functional>
 #include <string>
 #include <vector>
@@ -76,6 +77,12 @@ SelinvPlan merge_selinv_plans(const std::vector<SelinvPlan>& plans, std::vector<
 // *flops.  Node ids must lie in [0, n).
 std::vector<uint8_t> needed_fronts(const SelinvPlan& P, const std::vector<int64_t>& ids,
                                    double* flops);
+
+// Per front, the children whose update matrices its assembly adds (by rank;
+// -1: none).  A child without update rows (F == k: pads or the stack's edge
+// all around its box) has no update matrix: off + k F + k would lie past its
+// block, and for the last front past the arena.
+std::vector<std::array<int32_t, 2>> assembly_children(const SelinvPlan& P);
 
 // Run body(i) for i < count on up to 16 host threads.
 void selinv_parallel_for(size_t count, const std::function<void(size_t)>& body);
