@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "reff_internal.h"
+#include "strips.h"
 #include "surrogate_internal.h"
 
 using namespace reff;
@@ -596,59 +597,13 @@ void make_units(const std::vector<PlanDesc>& in, std::vector<PlanDesc>& plans,
   }
 }
 
-// Most rows of one strip for the three-step Chebyshev pass, which addresses
-// a strip's rows through unsigned 32-bit byte offsets from a base three rows
-// before it: (rows + 8) x nx x S words stay below 2^31 bytes.  0 when even
-// one row does not fit (the pass is then not used).
-int64_t max_strip_rows(int64_t nx, size_t word) {
-  return std::max<int64_t>(0, (int64_t(1) << 31) / (nx * S * (int64_t)word) - 8);
-}
-
-// y segments of a tier of ny rows for strips of about H rows; 64 is the
-// tallest, and there a tier is cut only into segments of 64 rows or more.
-int64_t strip_segments(int64_t ny, int64_t H) {
-  return H >= 64 ? std::max<int64_t>(1, ny / 64) : (ny + H - 1) / H;
-}
-
-// Rows per strip of a group: a launch takes as many rounds as its strips fill
-// the chip's workgroup slots (`slots`: one per CU in float64, two in float32),
-// and a round the rows of a mean strip and `extra` more (halo rows, prologue), so
-// the height with the fewest row times in all is taken, the taller one on a tie
-// (less halo traffic), up to 64 rows so that a block that runs on alone still
-// spreads.  The stacks of a batch converge at different times: there the rounds
-// of half the strips count as well.  Against about 1024 strips per launch whatever their rounds:
-// float64: 8-row strips in four rounds at one block of 4 x 256 x 256 and 6-row
-// strips in five at four blocks of 3 x 128 x 128 took 194 and 166 us a pass, one
-// round of 32 and 26 rows 153 and 127 us; stacks of 4000 to 12000 nodes take
-// one row per strip (12 columns on 82 x 56 nodes 4.7 ms, 5.8 with eight rows at
-// least).  float32: a batch of 24 plans of 30 to 233 nodes a side 2.4 rounds of
-// 64 rows, 97.9 ms, now 94.3; 91 samples of 2 x 158 x 195 8.5 -> 7.7 ms; 4 x 512 x
-// 512 keeps two rounds of 64.
-int64_t strip_rows(const std::vector<PlanDesc>& plans, int64_t slots, double extra) {
-  bool batch = false;
-  for (const PlanDesc& p : plans) batch = batch || p.cbase != plans[0].cbase;
-  int64_t best = 64;
-  double cost = INFINITY;
-  for (int64_t H = 1; H <= 64; ++H) {
-    int64_t n = 0, rows = 0;
-    for (const PlanDesc& p : plans) {
-      const int64_t ny = p.plane / p.nx, across = p.n / p.plane * ((p.nx + CH - 1) / CH);
-      n += across * strip_segments(ny, H);
-      rows += across * ny;
-    }
-    const int64_t rounds = (n + slots - 1) / slots + (batch ? (n / 2 + slots - 1) / slots : 0);
-    const double c = (double)rounds * ((double)rows / (double)n + extra);
-    if (c <= cost) cost = c, best = H;
-  }
-  return best;
-}
-
 // Strips for the stencil kernels of a group: every block's tiers are cut into
 // CH-wide x strips and y segments of about `fixed_rows` rows (strip_rows), or,
 // with fixed_rows = 0 (a tuning database's target), as many segments as make
 // about `target` strips in total, at least `floor` per block while the
 // segments keep 64 rows or more (as for work units); no more than
 // max_strip_rows rows each.
+static_assert(STRIP_WIDTH == CH && STRIP_COLUMNS == S, "strips.h");
 void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
                  size_t word, int target = TARGET_UNITS, int floor = 0, int64_t fixed_rows = 0) {
   int64_t rows = 0;
@@ -924,8 +879,9 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     for (const PlanDesc& p : plans) triples = triples && max_strip_rows(p.nx, tsz) >= 1;
     if (triples && (rs = ensure(ws.TA, (size_t)slot_rows * 5 * S * tsz)) != REFF_OK) return rs;
     if (triples && (rs = ensure(ws.TB, (size_t)slot_rows * S * tsz)) != REFF_OK) return rs;
-    if ((rs = ensure(ws.part, (size_t)std::max(nu, ns) * NGRAM * S * S * sizeof(double))) != REFF_OK)
-      return rs;
+    // (only the float32 strips of K1 write Gram partials)
+    const size_t npart = (size_t)(fp32 ? std::max(nu, ns) : nu);
+    if ((rs = ensure(ws.part, npart * NGRAM * S * S * sizeof(double))) != REFF_OK) return rs;
     if ((rs = ensure(ws.W, (size_t)nb * NGRAM * S * S * sizeof(double))) != REFF_OK) return rs;
     if ((rs = ensure(ws.small, (size_t)nb * 4 * S * S * sizeof(double))) != REFF_OK) return rs;
     if ((rs = ensure(ws.strips, (size_t)std::max(ns, 1) * sizeof(Strip))) != REFF_OK) return rs;
