@@ -40,7 +40,7 @@ typedef enum {
   REFF_ERR_DISCONNECTED = -2,   /* some node has no path to a pad: G singular */
   REFF_ERR_NO_CONVERGENCE = -3, /* max_iters reached; R_out holds the solver's
                                    lower bounds, stats->n_unconverged > 0    */
-  REFF_ERR_OUT_OF_MEMORY = -4,
+  REFF_ERR_OUT_OF_MEMORY = -4,  /* device or host memory, or no host threads */
   REFF_ERR_DEVICE = -5,         /* HIP runtime error; see reff_last_error();
                                    the handle stays valid for reff_free_pdn */
   REFF_ERR_UNSUPPORTED = -6

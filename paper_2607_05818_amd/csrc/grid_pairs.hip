@@ -584,7 +584,7 @@ hipError_t grid_table_call(int M, int N, double r, double s, const int32_t* xy, 
 
 extern "C" reff_status reff_grid_pairs(int32_t M, int32_t N, double r, double s,
                                        const int32_t* xy, int64_t P, double* R_out,
-                                       int32_t out_on_device, void* stream) {
+                                       int32_t out_on_device, void* stream) try {
   using namespace reff;
   const reff_status v = grid_pairs_validate(M, N, r, s, xy, P, R_out);
   if (v != REFF_OK || P == 0) return v;
@@ -632,11 +632,13 @@ extern "C" reff_status reff_grid_pairs(int32_t M, int32_t N, double r, double s,
   release();
   if (e != hipSuccess) return grid_dev_fail(e, "grid pairs");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 extern "C" reff_status reff_grid_pairs_noalloc(int32_t M, int32_t N, double r, double s,
                                                const int32_t* xy, int64_t P, double* R_out,
-                                               int32_t out_on_device, void* stream) {
+                                               int32_t out_on_device, void* stream) try {
   using namespace reff;
   const reff_status v = grid_pairs_validate(M, N, r, s, xy, P, R_out);
   if (v != REFF_OK || P == 0) return v;
@@ -692,4 +694,6 @@ extern "C" reff_status reff_grid_pairs_noalloc(int32_t M, int32_t N, double r, d
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return grid_dev_fail(e, "grid pairs (no allocation)");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }

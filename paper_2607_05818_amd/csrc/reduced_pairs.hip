@@ -503,7 +503,7 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
                                           const int32_t* tsv_xy, const double* tsv_r, int64_t m,
                                           const int32_t* bump_xy, int64_t n,
                                           const int32_t* load_xy, double* R_out,
-                                          int32_t out_on_device, void* stream) {
+                                          int32_t out_on_device, void* stream) try {
   using namespace reff;
   const int d = n_tiers;
   if (d < 2) return host_fail(REFF_ERR_INVALID_ARG, "the reduced system needs at least 2 tiers");
@@ -694,4 +694,6 @@ extern "C" reff_status reff_reduced_pairs(int32_t n_tiers, int32_t nx, int32_t n
     return host_fail(REFF_ERR_DEVICE,
                      "reduced system: a pivot of Z^T H Z was not positive");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }

@@ -9,16 +9,18 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
-#include <atomic>
+#include <memory>
 #include <new>
-#include <thread>
 #include <numeric>
 #include <random>
+#include <stdexcept>
 #include <string>
+#include <system_error>
 #include <type_traits>
 #include <vector>
 
 #include "reff_internal.h"
+#include "selinv_plan.h"
 #include "strips.h"
 #include "surrogate_internal.h"
 
@@ -97,6 +99,29 @@ reff_status validate_desc(const reff_pdn_desc* d) {
 namespace reff {
 reff_status host_fail(reff_status s, const std::string& msg) { return fail(s, msg); }
 reff_status host_validate_desc(const reff_pdn_desc* d) { return validate_desc(d); }
+reff_status host_exception() noexcept {
+  const auto say = [](reff_status s, const char* what) {
+    try {
+      g_err = what;
+    } catch (...) {
+      g_err.clear();
+    }
+    return s;
+  };
+  try {
+    throw;
+  } catch (const std::bad_alloc&) {
+    return say(REFF_ERR_OUT_OF_MEMORY, "host memory");
+  } catch (const std::length_error&) {
+    return say(REFF_ERR_OUT_OF_MEMORY, "host memory");
+  } catch (const std::system_error& e) {
+    return say(REFF_ERR_OUT_OF_MEMORY, e.what());
+  } catch (const std::exception& e) {
+    return say(REFF_ERR_DEVICE, e.what());
+  } catch (...) {
+    return say(REFF_ERR_DEVICE, "unknown exception");
+  }
+}
 // D^-1 and the float32 coefficient copies from the float64 arrays
 // (coef_prep.hip)
 hipError_t launch_coef_derived(const double* d, const double* cE, const double* cN, int64_t n,
@@ -249,29 +274,11 @@ reff_status build_host(const reff_pdn_desc* ds, const std::vector<int64_t>& gnd,
   return s == REFF_OK ? s : fail(s, msg);
 }
 
-// Run body(i) for i < count on up to 16 host threads (dynamic assignment).
-template <typename F>
-void parallel_for(size_t count, F body) {
-  const size_t hw = std::max<unsigned>(1, std::thread::hardware_concurrency());
-  const size_t nthr = std::min<size_t>({hw, (size_t)16, count});
-  if (nthr <= 1) {
-    for (size_t i = 0; i < count; ++i) body(i);
-    return;
-  }
-  std::atomic<size_t> next{0};
-  std::vector<std::thread> pool;
-  for (size_t t = 0; t < nthr; ++t)
-    pool.emplace_back([&]() {
-      for (size_t i = next++; i < count; i = next++) body(i);
-    });
-  for (auto& th : pool) th.join();
-}
-
-// Apply body(lo, hi) to [0, n) in chunks spread over parallel_for.
+// Apply body(lo, hi) to [0, n) in chunks spread over host threads.
 template <typename F>
 void parallel_chunks(size_t n, F body) {
   constexpr size_t CH = size_t(1) << 20;
-  parallel_for((n + CH - 1) / CH, [&](size_t c) { body(c * CH, std::min(n, (c + 1) * CH)); });
+  selinv_parallel_for((n + CH - 1) / CH, [&](size_t c) { body(c * CH, std::min(n, (c + 1) * CH)); });
 }
 
 template <typename T>
@@ -358,7 +365,7 @@ reff_status make_coefset_multi(const std::vector<const reff_pdn_desc*>& ds,
   }
   std::vector<reff_status> st(np, REFF_OK);
   std::vector<std::string> msg(np);
-  parallel_for(np, [&](size_t i) {
+  selinv_parallel_for(np, [&](size_t i) {
     const CoefOut o{h.d.data(), h.cE.data(), h.cN.data(), h.up.data(), h.dn.data(),
                     h.slot.data(), h.is_pad.data(), tnode.data(), off[i], soff[i]};
     st[i] = build_into(ds[i], gnds[i], o, msg[i]);
@@ -367,6 +374,7 @@ reff_status make_coefset_multi(const std::vector<const reff_pdn_desc*>& ds,
     if (st[i] != REFF_OK) return fail(st[i], "plan " + std::to_string(i) + ": " + msg[i]);
   reff_status rs = REFF_OK;
   auto& owned = extra;
+  owned.reserve(owned.size() + 16);  // every array below is owned once it is allocated
   auto upload_owned = [&](const std::vector<double>& src, double** d64, float** d32) {
     if (rs != REFF_OK) return;
     rs = upload<double>(src, d64, owned);
@@ -667,13 +675,12 @@ struct TuneDb {
   static bool ok(int v) { return v >= 64 && v <= (1 << 16); }
   void load(const char* path) {
     e.clear();
-    FILE* f = std::fopen(path, "r");
+    std::unique_ptr<FILE, int (*)(FILE*)> f(std::fopen(path, "r"), &std::fclose);
     if (!f) return;
     char key[128];
     TuneChoice c;
-    while (std::fscanf(f, "%127s %d %d", key, &c.units, &c.strips) == 3)
+    while (std::fscanf(f.get(), "%127s %d %d", key, &c.units, &c.strips) == 3)
       if (ok(c.units) && ok(c.strips)) e.emplace_back(key, c);
-    std::fclose(f);
   }
   TuneChoice get(const std::string& k) const {
     for (const auto& kv : e)
@@ -1289,7 +1296,7 @@ const char* reff_last_error(void) { return g_err.c_str(); }
 
 int64_t reff_pdn_num_nodes(reff_pdn p) { return p ? p->n : -1; }
 
-reff_status reff_build_pdn(const reff_pdn_desc* d, int32_t device, reff_pdn* out) {
+reff_status reff_build_pdn(const reff_pdn_desc* d, int32_t device, reff_pdn* out) try {
   g_err.clear();
   if (!out) return fail(REFF_ERR_INVALID_ARG, "out is NULL");
   reff_status s = validate_desc(d);
@@ -1308,8 +1315,10 @@ reff_status reff_build_pdn(const reff_pdn_desc* d, int32_t device, reff_pdn* out
   HIPCHK(hipGetDeviceCount(&ndev));
   if (device >= ndev) return fail(REFF_ERR_INVALID_ARG, "no such device");
   HIPCHK(hipSetDevice(device));
-  reff_pdn_t* p = new (std::nothrow) reff_pdn_t();
-  if (!p) return fail(REFF_ERR_OUT_OF_MEMORY, "host allocation");
+  struct Release {
+    void operator()(reff_pdn_t* q) const { reff_free_pdn(q); }
+  };
+  std::unique_ptr<reff_pdn_t, Release> p(new reff_pdn_t());
   p->device = device;
   p->nt = d->n_tiers;
   p->nx = d->nx;
@@ -1324,14 +1333,12 @@ reff_status reff_build_pdn(const reff_pdn_desc* d, int32_t device, reff_pdn* out
   if (d->n_tiers > 1 && d->n_tsv > 0)
     p->tsv_g.assign(d->tsv_g, d->tsv_g + (int64_t)d->n_tsv * (d->n_tiers - 1));
   p->pad_xy.assign(d->pad_xy, d->pad_xy + 2 * (int64_t)d->n_pads);
-  s = make_coefset(p, pads, p->gnd);
-  if (s != REFF_OK) {
-    const std::string msg = g_err;
-    reff_free_pdn(p);
-    return fail(s, msg);
-  }
-  *out = p;
+  s = make_coefset(p.get(), pads, p->gnd);
+  if (s != REFF_OK) return s;
+  *out = p.release();
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 void reff_free_pdn(reff_pdn p) {
@@ -1396,7 +1403,7 @@ static reff_status columns_of(const int64_t* nodes, int64_t count, int64_t n,
 }
 
 reff_status reff_solve_diag(reff_pdn p, const int64_t* nodes, int64_t n_nodes, double* R_out,
-                            const reff_solve_opts* opts, reff_solve_stats* st) {
+                            const reff_solve_opts* opts, reff_solve_stats* st) try {
   g_err.clear();
   const auto t0 = std::chrono::steady_clock::now();
   if (!p) return fail(REFF_ERR_INVALID_ARG, "handle is NULL");
@@ -1437,11 +1444,13 @@ reff_status reff_solve_diag(reff_pdn p, const int64_t* nodes, int64_t n_nodes, d
   if (solve_rs == REFF_ERR_NO_CONVERGENCE)
     return fail(REFF_ERR_NO_CONVERGENCE, "max_iters reached; R_out holds lower bounds");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_query_pairs(reff_pdn p, const int64_t* a, int64_t m, const int64_t* b,
                              int64_t n, reff_pair_mode mode, double* R_out,
-                             const reff_solve_opts* opts, reff_solve_stats* st) {
+                             const reff_solve_opts* opts, reff_solve_stats* st) try {
   g_err.clear();
   const auto t0 = std::chrono::steady_clock::now();
   if (!p) return fail(REFF_ERR_INVALID_ARG, "handle is NULL");
@@ -1508,6 +1517,7 @@ reff_status reff_query_pairs(reff_pdn p, const int64_t* a, int64_t m, const int6
       for (void* q : ptrs) (void)hipFree(q);
     }
     hipError_t get(void** out, size_t bytes) {
+      ptrs.reserve(ptrs.size() + 1);
       hipError_t e = hipMalloc(out, std::max<size_t>(bytes, 8));
       if (e == hipSuccess) ptrs.push_back(*out);
       return e;
@@ -1607,6 +1617,8 @@ reff_status reff_query_pairs(reff_pdn p, const int64_t* a, int64_t m, const int6
   if (solve_rs == REFF_ERR_NO_CONVERGENCE)
     return fail(REFF_ERR_NO_CONVERGENCE, "max_iters reached before the tolerance");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 // IR drop and through-bump currents by superposition of unit-load responses
@@ -1618,7 +1630,7 @@ reff_status reff_query_pairs(reff_pdn p, const int64_t* a, int64_t m, const int6
 reff_status reff_ir_drop(reff_pdn p, const int64_t* load_nodes, int64_t n_loads,
                          const double* load_amps, int32_t n_scen, const int64_t* nodes,
                          int64_t n_nodes, double* drop_out, double* pad_amps_out,
-                         const reff_solve_opts* opts, reff_solve_stats* st) {
+                         const reff_solve_opts* opts, reff_solve_stats* st) try {
   g_err.clear();
   const auto t0 = std::chrono::steady_clock::now();
   if (!p) return fail(REFF_ERR_INVALID_ARG, "handle is NULL");
@@ -1720,6 +1732,7 @@ reff_status reff_ir_drop(reff_pdn p, const int64_t* load_nodes, int64_t n_loads,
       for (void* q : ptrs) (void)hipFree(q);
     }
     hipError_t get(void** out, size_t bytes) {
+      ptrs.reserve(ptrs.size() + 1);
       hipError_t e = hipMalloc(out, std::max<size_t>(bytes, 8));
       if (e == hipSuccess) ptrs.push_back(*out);
       return e;
@@ -1810,6 +1823,8 @@ reff_status reff_ir_drop(reff_pdn p, const int64_t* load_nodes, int64_t n_loads,
   if (solve_rs == REFF_ERR_NO_CONVERGENCE)
     return fail(REFF_ERR_NO_CONVERGENCE, "max_iters reached before the tolerance");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 // Screening of a batch with the learned model: predict every plan's map,
@@ -1974,7 +1989,7 @@ static reff_status screen_plans(reff_surrogate sg, const reff_pdn_desc* plans, i
 reff_status reff_batch_plans(const reff_pdn_desc* plans, int32_t n_plans,
                              const int64_t* const* nodes, const int64_t* n_nodes,
                              double* const* R_out, const reff_batch_opts* opts,
-                             reff_solve_stats* per_plan) {
+                             reff_solve_stats* per_plan) try {
   g_err.clear();
   const auto t0 = std::chrono::steady_clock::now();
   if (n_plans < 0) return fail(REFF_ERR_INVALID_ARG, "n_plans < 0");
@@ -2012,7 +2027,7 @@ reff_status reff_batch_plans(const reff_pdn_desc* plans, int32_t n_plans,
     // descriptors checked on host threads; the first bad plan is reported
     std::vector<reff_status> vs((size_t)n_plans, REFF_OK);
     std::vector<std::string> vm((size_t)n_plans);
-    parallel_for((size_t)n_plans, [&](size_t i) {
+    selinv_parallel_for((size_t)n_plans, [&](size_t i) {
       vs[i] = validate_desc(&plans[i]);
       if (vs[i] != REFF_OK) vm[i] = g_err;  // this thread's message
     });
@@ -2121,6 +2136,8 @@ reff_status reff_batch_plans(const reff_pdn_desc* plans, int32_t n_plans,
   if (solve_rs == REFF_ERR_NO_CONVERGENCE)
     return fail(REFF_ERR_NO_CONVERGENCE, "max_iters reached; R_out holds lower bounds");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 }  // extern "C"

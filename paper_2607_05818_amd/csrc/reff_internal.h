@@ -18,6 +18,10 @@ struct SelinvDevice;  // selinv.hip
 
 // Set the calling thread's reff_last_error() text and return s.
 reff_status host_fail(reff_status s, const std::string& msg);
+// The status of the exception being handled, its text in reff_last_error():
+// every entry point ends in catch (...) { return host_exception(); }.
+// OUT_OF_MEMORY where host memory or threads could not be had.
+reff_status host_exception() noexcept;
 // The stack validation every entry point performs before device work.
 reff_status host_validate_desc(const reff_pdn_desc* d);
 // Eq. 3 on uniform M x N tiers (grid_pairs.hip).  Whether P points are served

@@ -43,6 +43,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -526,6 +527,7 @@ struct Bufs {
   template <typename T>
   hipError_t get(T** out, size_t count) {
     void* p = nullptr;
+    ptrs.reserve(ptrs.size() + 1);
     hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
     if (e == hipSuccess) ptrs.push_back(p);
     *out = (T*)p;
@@ -755,6 +757,7 @@ struct SelinvDevice {
       return hipSuccess;
     }
     void* q = nullptr;
+    ptrs.reserve(ptrs.size() + 1);
     hipError_t e = hipMalloc(&q, b);
     if (e == hipSuccess) ptrs.push_back(q);
     *out = (T*)q;
@@ -989,7 +992,7 @@ reff_status selinv_run(const SelinvPlan& P, const SelinvDevice& D, hipStream_t s
 
 extern "C" {
 
-reff_status reff_selinv_info(const reff_pdn_desc* d, reff_selinv_stats* info) {
+reff_status reff_selinv_info(const reff_pdn_desc* d, reff_selinv_stats* info) try {
   using namespace reff;
   if (!d || !info) return host_fail(REFF_ERR_INVALID_ARG, "NULL descriptor or info");
   reff_status s = host_validate_desc(d);
@@ -1009,10 +1012,12 @@ reff_status reff_selinv_info(const reff_pdn_desc* d, reff_selinv_stats* info) {
   info->flops_factor = plan.flops_factor;
   info->flops_selinv = plan.flops_selinv;
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_selinv_diag(reff_pdn p, const int64_t* nodes, int64_t n_nodes, double* R_out,
-                             const reff_solve_opts* opts, reff_selinv_stats* st) {
+                             const reff_solve_opts* opts, reff_selinv_stats* st) try {
   using namespace reff;
   const auto t0 = std::chrono::steady_clock::now();
   if (!p) return host_fail(REFF_ERR_INVALID_ARG, "handle is NULL");
@@ -1087,9 +1092,11 @@ reff_status reff_selinv_diag(reff_pdn p, const int64_t* nodes, int64_t n_nodes, 
     st->seconds_setup = std::chrono::duration<double>(t_setup - t_plan).count();
   }
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
-reff_status reff_release_cached_memory(int32_t device) {
+reff_status reff_release_cached_memory(int32_t device) try {
   using namespace reff;
   if (device < 0 || device >= 64) return host_fail(REFF_ERR_INVALID_ARG, "bad device");
   WorkspaceCache& c = g_ws[device];
@@ -1101,12 +1108,14 @@ reff_status reff_release_cached_memory(int32_t device) {
   c.bytes = 0;
   if (e != hipSuccess) return dev_status(e, "releasing cached memory");
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_selinv_batch(const reff_pdn_desc* plans, int32_t n_plans,
                               const int64_t* const* nodes, const int64_t* n_nodes,
                               double* const* R_out, const reff_solve_opts* opts,
-                              reff_selinv_stats* st) {
+                              reff_selinv_stats* st) try {
   using namespace reff;
   const auto t0 = std::chrono::steady_clock::now();
   if (st) std::memset(st, 0, sizeof(*st));
@@ -1189,6 +1198,15 @@ reff_status reff_selinv_batch(const reff_pdn_desc* plans, int32_t n_plans,
       }
     out.P = merge_selinv_plans(sp, out.base);
   };
+  // the same on a thread of its own, which must not throw
+  auto analyse_ahead = [&](size_t c, Chunk& out) {
+    try {
+      analyse(c, out);
+    } catch (...) {
+      out.s = host_exception();  // (its text stays with this thread)
+      out.err.clear();
+    }
+  };
   // requested nodes of every plan, in plan order, into one device array
   int64_t total = 0;
   std::vector<int64_t> out_at(np + 1, 0);
@@ -1211,10 +1229,16 @@ reff_status reff_selinv_batch(const reff_pdn_desc* plans, int32_t n_plans,
   hipError_t e = b.get(&dres, (size_t)total);
   if (e != hipSuccess) return dev_status(e, "selected inversion batch: output");
   for (size_t c = 0; c + 1 < cb.size(); ++c) {
-    if (cur->s != REFF_OK) return host_fail(cur->s, cur->err);
+    if (cur->s != REFF_OK)
+      return host_fail(cur->s, cur->err.empty() ? "analysis of a later chunk of plans" : cur->err);
     auto next = std::make_unique<Chunk>();
     std::thread ahead;
-    if (c + 2 < cb.size()) ahead = std::thread([&, c] { analyse(c + 1, *next); });
+    if (c + 2 < cb.size()) {
+      try {
+        ahead = std::thread([&, c] { analyse_ahead(c + 1, *next); });
+      } catch (const std::system_error&) {  // no thread to be had: analysed below
+      }
+    }
     struct Join {
       std::thread& t;
       ~Join() {
@@ -1270,7 +1294,10 @@ reff_status reff_selinv_batch(const reff_pdn_desc* plans, int32_t n_plans,
     dev_sp.reset();
     // the next chunk's analysis: whatever of it the device work did not hide
     const auto tw = std::chrono::steady_clock::now();
-    if (ahead.joinable()) ahead.join();
+    if (ahead.joinable())
+      ahead.join();
+    else if (c + 2 < cb.size())
+      analyse(c + 1, *next);
     t_plan += std::chrono::duration<double>(std::chrono::steady_clock::now() - tw).count();
     cur = std::move(next);
   }
@@ -1304,6 +1331,8 @@ reff_status reff_selinv_batch(const reff_pdn_desc* plans, int32_t n_plans,
     st->seconds_selinv = t_selinv;
   }
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 }  // extern "C"

@@ -3,10 +3,9 @@
 
 #include <algorithm>
 #include <atomic>
-#include <system_error>
-#include <mutex>
 #include <exception>
 #include <functional>
+#include <mutex>
 #include <thread>
 
 namespace reff {
@@ -437,7 +436,7 @@ void selinv_parallel_for(size_t count, const std::function<void(size_t)>& body) 
   pool.reserve(nthr - 1);
   try {
     for (size_t t = 0; t + 1 < nthr; ++t) pool.emplace_back(work);
-  } catch (const std::system_error&) {
+  } catch (const std::exception&) {  // no thread or no memory for one
   }
   work();
   for (auto& th : pool) th.join();

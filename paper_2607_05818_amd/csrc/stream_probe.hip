@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k_probe_3r2w(const f4* __restrict__ a,
 }  // namespace
 
 extern "C" reff_status reff_stream_probe(int32_t kind, const void* src, void* dst, int64_t bytes,
-                                         int32_t blocks, void* stream) {
+                                         int32_t blocks, void* stream) try {
   using namespace reff;
   if (kind < 0 || kind > 4) return host_fail(REFF_ERR_INVALID_ARG, "kind must be 0..4");
   if (bytes <= 0 || bytes % 16 != 0)
@@ -104,4 +104,6 @@ extern "C" reff_status reff_stream_probe(int32_t kind, const void* src, void* ds
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return host_fail(REFF_ERR_DEVICE, std::string("probe: ") + hipGetErrorString(e));
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }

@@ -7,7 +7,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <new>
+#include <memory>
 #include <numeric>
 #include <random>
 #include <string>
@@ -103,6 +103,7 @@ constexpr size_t PART_FLOATS = (size_t)32 << 20;  // 128 MB of partials
 constexpr int LOSS_BLOCKS = 128;
 
 reff_status dmalloc(void** p, size_t bytes, std::vector<void*>& owned) {
+  owned.reserve(owned.size() + 1);
   SGCHK(hipMalloc(p, std::max<size_t>(bytes, 256)));
   owned.push_back(*p);
   return REFF_OK;
@@ -537,8 +538,14 @@ reff_status step_grad(reff_surrogate_t* s, const reff_pdn_desc* plans, const ref
   return REFF_OK;
 }
 
-reff_status new_model(const reff_surrogate_config* cfg, int32_t device, reff_surrogate_t** out) {
-  if (!cfg || !out) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
+struct FreeModel {
+  void operator()(reff_surrogate_t* s) const { free_model(s); }
+};
+using ModelPtr = std::unique_ptr<reff_surrogate_t, FreeModel>;
+using File = std::unique_ptr<FILE, int (*)(FILE*)>;
+
+reff_status new_model(const reff_surrogate_config* cfg, int32_t device, ModelPtr& out) {
+  if (!cfg) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
   if (cfg->n_tiers < 1 || cfg->nx < 8 || cfg->ny < 8 || cfg->nx % 8 || cfg->ny % 8)
     return host_fail(REFF_ERR_INVALID_ARG, "n_tiers >= 1 and nx, ny multiples of 8 required");
   if ((int64_t)cfg->nx * cfg->ny > (1 << 22))
@@ -553,8 +560,7 @@ reff_status new_model(const reff_surrogate_config* cfg, int32_t device, reff_sur
   SGCHK(hipGetDeviceCount(&ndev));
   if (device >= ndev) return host_fail(REFF_ERR_INVALID_ARG, "no such device");
   SGCHK(hipSetDevice(device));
-  reff_surrogate_t* s = new (std::nothrow) reff_surrogate_t();
-  if (!s) return host_fail(REFF_ERR_OUT_OF_MEMORY, "host allocation");
+  ModelPtr s(new reff_surrogate_t());
   s->device = device;
   s->nt = cfg->n_tiers;
   s->nx = cfg->nx;
@@ -562,14 +568,9 @@ reff_status new_model(const reff_surrogate_config* cfg, int32_t device, reff_sur
   s->C = C;
   s->cin0 = 2 * cfg->n_tiers + 2;
   s->seed = cfg->seed;
-  build_layers(s);
-  reff_status rs = alloc_model(s);
-  if (rs != REFF_OK) {
-    const std::string msg = reff_last_error();
-    free_model(s);
-    return host_fail(rs, msg);
-  }
-  *out = s;
+  build_layers(s.get());
+  SGRET(alloc_model(s.get()));
+  out = std::move(s);
   return REFF_OK;
 }
 
@@ -613,9 +614,10 @@ reff_status predict_device(reff_surrogate s, const reff_pdn_desc* plans, int32_t
 extern "C" {
 
 reff_status reff_surrogate_create(const reff_surrogate_config* cfg, int32_t device,
-                                  reff_surrogate* out) {
-  reff_surrogate_t* s = nullptr;
-  SGRET(new_model(cfg, device, &s));
+                                  reff_surrogate* out) try {
+  if (!out) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
+  ModelPtr s;
+  SGRET(new_model(cfg, device, s));
   // He-normal weights (fan-in K*K*Cin), zero biases.
   std::vector<float> h((size_t)s->n_params, 0.f);
   std::mt19937_64 rng(cfg->seed);
@@ -623,38 +625,39 @@ reff_status reff_surrogate_create(const reff_surrogate_config* cfg, int32_t devi
     std::normal_distribution<float> nd(0.f, std::sqrt(2.f / (float)(l.k * l.k * l.cin)));
     for (int64_t i = 0; i < l.nw(); ++i) h[(size_t)(l.w_off + i)] = nd(rng);
   }
-  reff_status rs = upload_params(s, h.data());
-  if (rs != REFF_OK) {
-    const std::string msg = reff_last_error();
-    free_model(s);
-    return host_fail(rs, msg);
-  }
-  *out = s;
+  SGRET(upload_params(s.get(), h.data()));
+  *out = s.release();
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 void reff_surrogate_free(reff_surrogate s) { free_model(s); }
 
 int64_t reff_surrogate_num_params(reff_surrogate s) { return s ? s->n_params : -1; }
 
-reff_status reff_surrogate_get_params(reff_surrogate s, float* out) {
+reff_status reff_surrogate_get_params(reff_surrogate s, float* out) try {
   if (!s || !out) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
   SGCHK(hipSetDevice(s->device));
   SGCHK(hipMemcpy(out, s->p, (size_t)s->n_params * 4, hipMemcpyDeviceToHost));
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
-reff_status reff_surrogate_set_params(reff_surrogate s, const float* in) {
+reff_status reff_surrogate_set_params(reff_surrogate s, const float* in) try {
   if (!s || !in) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
   for (int64_t i = 0; i < s->n_params; ++i)
     if (!std::isfinite(in[i])) return host_fail(REFF_ERR_INVALID_ARG, "non-finite parameter");
   SGCHK(hipSetDevice(s->device));
   return upload_params(s, in);
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_surrogate_loss_grad(reff_surrogate s, const reff_pdn_desc* plans,
                                      const reff_labels* labels, int32_t n_plans, double* loss,
-                                     float* grad) {
+                                     float* grad) try {
   if (!s || !loss) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
   SGRET(check_plans(s, plans, n_plans));
   SGRET(check_labels(s, labels, n_plans));
@@ -667,11 +670,13 @@ reff_status reff_surrogate_loss_grad(reff_surrogate s, const reff_pdn_desc* plan
   if (grad) SGCHK(hipMemcpy(grad, s->g, (size_t)s->n_params * 4, hipMemcpyDeviceToHost));
   SGCHK(hipDeviceSynchronize());
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_surrogate_train(reff_surrogate s, const reff_pdn_desc* plans,
                                  const reff_labels* labels, int32_t n_plans,
-                                 const reff_train_opts* opts, double* epoch_loss) {
+                                 const reff_train_opts* opts, double* epoch_loss) try {
   if (!s) return host_fail(REFF_ERR_INVALID_ARG, "NULL model");
   reff_train_opts o{};
   if (opts) o = *opts;
@@ -709,10 +714,12 @@ reff_status reff_surrogate_train(reff_surrogate s, const reff_pdn_desc* plans,
   }
   SGCHK(hipDeviceSynchronize());
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 reff_status reff_surrogate_predict(reff_surrogate s, const reff_pdn_desc* plans, int32_t n_plans,
-                                   double* const* R_out, int32_t out_on_device) {
+                                   double* const* R_out, int32_t out_on_device) try {
   if (!s) return host_fail(REFF_ERR_INVALID_ARG, "NULL model");
   if (out_on_device != 0 && out_on_device != 1)
     return host_fail(REFF_ERR_INVALID_ARG, "out_on_device must be 0 or 1");
@@ -732,36 +739,40 @@ reff_status reff_surrogate_predict(reff_surrogate s, const reff_pdn_desc* plans,
   }
   SGCHK(hipDeviceSynchronize());
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
-reff_status reff_surrogate_save(reff_surrogate s, const char* path) {
+reff_status reff_surrogate_save(reff_surrogate s, const char* path) try {
   if (!s || !path) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
   std::vector<float> h((size_t)s->n_params);
   SGRET(reff_surrogate_get_params(s, h.data()));
-  FILE* f = std::fopen(path, "wb");
+  File f(std::fopen(path, "wb"), &std::fclose);
   if (!f) return host_fail(REFF_ERR_INVALID_ARG, std::string("cannot open ") + path);
   const char magic[8] = {'R', 'E', 'F', 'F', 'S', 'G', '0', '1'};
   const int32_t dims[4] = {s->nt, s->nx, s->ny, s->C};
   const int64_t np = s->n_params;
-  bool ok = std::fwrite(magic, 1, 8, f) == 8 && std::fwrite(dims, 4, 4, f) == 4 &&
-            std::fwrite(&s->seed, 8, 1, f) == 1 && std::fwrite(&np, 8, 1, f) == 1 &&
-            std::fwrite(h.data(), 4, h.size(), f) == h.size();
-  ok = (std::fclose(f) == 0) && ok;
+  bool ok = std::fwrite(magic, 1, 8, f.get()) == 8 && std::fwrite(dims, 4, 4, f.get()) == 4 &&
+            std::fwrite(&s->seed, 8, 1, f.get()) == 1 && std::fwrite(&np, 8, 1, f.get()) == 1 &&
+            std::fwrite(h.data(), 4, h.size(), f.get()) == h.size();
+  ok = (std::fclose(f.release()) == 0) && ok;
   if (!ok) return host_fail(REFF_ERR_INVALID_ARG, std::string("write failed: ") + path);
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
-reff_status reff_surrogate_load(const char* path, int32_t device, reff_surrogate* out) {
+reff_status reff_surrogate_load(const char* path, int32_t device, reff_surrogate* out) try {
   if (!path || !out) return host_fail(REFF_ERR_INVALID_ARG, "NULL argument");
-  FILE* f = std::fopen(path, "rb");
+  File f(std::fopen(path, "rb"), &std::fclose);
   if (!f) return host_fail(REFF_ERR_INVALID_ARG, std::string("cannot open ") + path);
   char magic[8];
   int32_t dims[4];
   uint64_t seed = 0;
   int64_t np = 0;
-  bool ok = std::fread(magic, 1, 8, f) == 8 && std::memcmp(magic, "REFFSG01", 8) == 0 &&
-            std::fread(dims, 4, 4, f) == 4 && std::fread(&seed, 8, 1, f) == 1 &&
-            std::fread(&np, 8, 1, f) == 1;
+  bool ok = std::fread(magic, 1, 8, f.get()) == 8 && std::memcmp(magic, "REFFSG01", 8) == 0 &&
+            std::fread(dims, 4, 4, f.get()) == 4 && std::fread(&seed, 8, 1, f.get()) == 1 &&
+            std::fread(&np, 8, 1, f.get()) == 1;
   reff_surrogate_config cfg{};
   if (ok) {
     cfg.n_tiers = dims[0];
@@ -770,33 +781,22 @@ reff_status reff_surrogate_load(const char* path, int32_t device, reff_surrogate
     cfg.base_channels = dims[3];
     cfg.seed = seed;
   }
-  reff_surrogate_t* s = nullptr;
+  ModelPtr s;
   if (ok) {
-    reff_status rs = new_model(&cfg, device, &s);
-    if (rs != REFF_OK) {
-      std::fclose(f);
-      return rs;
-    }
+    SGRET(new_model(&cfg, device, s));
     ok = np == s->n_params;
   }
   std::vector<float> h;
   if (ok) {
     h.resize((size_t)np);
-    ok = std::fread(h.data(), 4, h.size(), f) == h.size();
+    ok = std::fread(h.data(), 4, h.size(), f.get()) == h.size();
   }
-  std::fclose(f);
-  if (!ok) {
-    free_model(s);
-    return host_fail(REFF_ERR_INVALID_ARG, std::string("not a model file: ") + path);
-  }
-  reff_status rs = upload_params(s, h.data());
-  if (rs != REFF_OK) {
-    const std::string msg = reff_last_error();
-    free_model(s);
-    return host_fail(rs, msg);
-  }
-  *out = s;
+  if (!ok) return host_fail(REFF_ERR_INVALID_ARG, std::string("not a model file: ") + path);
+  SGRET(upload_params(s.get(), h.data()));
+  *out = s.release();
   return REFF_OK;
+} catch (...) {
+  return reff::host_exception();
 }
 
 }  // extern "C"
