@@ -363,7 +363,9 @@ typedef struct {
                               the strips per launch of the stencil passes
                               (which sets the strip height, i.e. the tile
                               shape); a class not yet in it is timed on 12
-                              candidate pairs first and added             */
+                              candidate pairs first and added.  The pair
+                              1024 1024 is the layout of a call without a
+                              database                                     */
   int32_t calibrate;       /* screened: 0 = every checked node checks the
                               prediction; 1 = the checked nodes at even
                               positions of the seeded order fit one log

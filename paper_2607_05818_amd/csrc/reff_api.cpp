@@ -607,13 +607,13 @@ void make_units(const std::vector<PlanDesc>& in, std::vector<PlanDesc>& plans,
 
 // Strips for the stencil kernels of a group: every block's tiers are cut into
 // CH-wide x strips and y segments of about `fixed_rows` rows (strip_rows), or,
-// with fixed_rows = 0 (a tuning database's target), as many segments as make
+// with fixed_rows = 0 (another target of a tuning database), as many segments as make
 // about `target` strips in total, at least `floor` per block while the
 // segments keep 64 rows or more (as for work units); no more than
 // max_strip_rows rows each.
 static_assert(STRIP_WIDTH == CH && STRIP_COLUMNS == S, "strips.h");
 void make_strips(std::vector<PlanDesc>& plans, std::vector<Strip>& strips,
-                 size_t word, int target = TARGET_UNITS, int floor = 0, int64_t fixed_rows = 0) {
+                 size_t word, int target, int floor, int64_t fixed_rows) {
   int64_t rows = 0;
   for (const PlanDesc& p : plans) rows += p.n;
   if (floor > 0) {
@@ -664,7 +664,8 @@ __global__ void k_gather_flags(const BlockState* __restrict__ st, int nb, int32_
 // Tuning database: one line "<size class> <work units> <strips>" per entry:
 // the work units per launch of the row-range kernels and the strips per
 // launch of the stencil passes (which fixes the strips' height, the tile
-// shape of those passes: CH nodes wide, H rows tall).  The size class is the
+// shape of those passes: CH nodes wide, H rows tall; DEFAULT_STRIPS is the layout
+// without a database).  The size class is the
 // precision, the Krylov variant, log2 of the rows of a launch group and the
 // number of its blocks.
 struct TuneChoice {
@@ -827,7 +828,7 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     // Work units per launch: the tuning database's entry for this size
     // class, or (new class) the fastest of a few candidates, each timed over
     // one chunk of iterations from a fresh start.
-    TuneChoice target{TARGET_UNITS, TARGET_UNITS};
+    TuneChoice target{TARGET_UNITS, DEFAULT_STRIPS};
     std::vector<TuneChoice> trials;
     std::string tkey;
     TuneDb tdb;
@@ -839,7 +840,7 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
         target = v;
       } else {
         for (int u : {512, 1024, 2048})
-          for (int sp : {256, 512, 1024, 2048}) trials.push_back(TuneChoice{u, sp});
+          for (int sp : STRIP_TARGETS) trials.push_back(TuneChoice{u, sp});
       }
     }
     std::vector<float> trial_ms;
@@ -863,11 +864,8 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     nu = (int)units.size();
     strips.clear();
     const bool cheb = !o.indep && o.cheb > 1;
-    if ((fp32 || cheb) && !o.indep) {
-      // a tuning database's entry stands for the target of either precision
-      const int64_t fixed = o.tune_db ? 0 : fp32 ? strip_rows(plans, 512, 5) : strip_rows(plans, 256, 7);
-      make_strips(plans, strips, tsz, tc.strips, floor, fixed);
-    }
+    if ((fp32 || cheb) && !o.indep)
+      make_strips(plans, strips, tsz, tc.strips, floor, target_rows(plans, fp32, tc.strips));
     ns = (int)strips.size();
     // ---- buffers
     reff_status rs;

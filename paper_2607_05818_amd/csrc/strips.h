@@ -98,4 +98,18 @@ int64_t strip_rows(const std::vector<Plan>& plans, int64_t slots, double extra) 
   return best;
 }
 
+// Strips per launch that a tuning database can name; DEFAULT_STRIPS stands for
+// the heights of strip_rows, the layout without a database, so that a tuned call
+// has it among its candidates.
+constexpr int DEFAULT_STRIPS = 1024;
+constexpr int STRIP_TARGETS[] = {256, 512, DEFAULT_STRIPS, 2048};
+
+// Rows per strip of a group for a target of strips, 0: as many segments as make
+// about that many.
+template <typename Plan>
+int64_t target_rows(const std::vector<Plan>& plans, bool fp32, int target) {
+  if (target != DEFAULT_STRIPS) return 0;
+  return fp32 ? strip_rows(plans, 512, 5) : strip_rows(plans, 256, 7);
+}
+
 }  // namespace reff

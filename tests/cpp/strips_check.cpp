@@ -31,7 +31,7 @@ static int bad = 0;
 // has.
 static void check(const char* name, const std::vector<Plan>& g, int64_t cap, int64_t lo, int64_t hi) {
   for (int fp32 = 0; fp32 < 2; ++fp32) {
-    const int64_t rows = fp32 ? strip_rows(g, 512, 5) : strip_rows(g, 256, 7), n = strips_of(g, rows);
+    const int64_t rows = target_rows(g, fp32 != 0, DEFAULT_STRIPS), n = strips_of(g, rows);
     const bool ok = n <= cap && rows >= lo && rows <= hi;
     printf("%s, %s: %lld rows, %lld strips%s\n", name, fp32 ? "float32" : "float64", (long long)rows,
            (long long)n, ok ? "" : "  FAIL");
@@ -62,6 +62,15 @@ int main() {
   check("8 x 2048 x 2048", {plan(0, 8, 2048, 2048)}, 16384, 64, 64);
   check("8 x 1000 x 1000", {plan(0, 8, 1000, 1000)}, 4096, 60, 64);
   check("82 x 56", {plan(0, 1, 82, 56)}, 168, 1, 1);
+  // a tuning database has the layout of a call without one among its candidates
+  bool found = false;
+  for (int t : STRIP_TARGETS) {
+    const std::vector<Plan> one{plan(0, 2, 158, 195)};
+    found |= target_rows(one, true, t) == strip_rows(one, 512, 5) &&
+             target_rows(one, false, t) == strip_rows(one, 256, 7);
+  }
+  if (!found) printf("the default heights are no candidate  FAIL\n");
+  bad |= !found;
   printf(bad ? "FAILED\n" : "all ok\n");
   return bad;
 }
