@@ -487,10 +487,12 @@ bool grid_use_table(int M, int N, int64_t P) {
   return table <= DIRECT_COST * direct;
 }
 
-// Tiers that share one launch: as many as 8 GiB of tables hold.
+// Tiers that share one launch: as many as 8 GiB of tables hold, and as a grid
+// has in z (65535).
 static int grid_tier_group(int M, int N, int nt) {
   const size_t nf = (size_t)(M + 1) * (N + 1);
-  return (int)std::min<size_t>(nt, std::max<size_t>(1, ((size_t)8 << 30) / (16 * nf)));
+  const size_t most = std::min<size_t>(65535, ((size_t)8 << 30) / (16 * nf));
+  return (int)std::min<size_t>(nt, std::max<size_t>(1, most));
 }
 
 size_t grid_tiers_bytes(int M, int N, int nt) {
