@@ -988,17 +988,21 @@ __global__ __launch_bounds__(WG, 4) void k_gram_ab(Coef<T> c, Work wk, const T* 
 // One Chebyshev step at one node: u + a1 (u - up) + a2 Dinv (r - (G u)_v),
 // (G u)_v = d u - cE ue - cW uw - cN un - cS us - t, where t = gU yu + gD yd
 // is the TSV term (tsv_term).  Every kernel that forms a Chebyshev iterate
-// goes through these two functions, with explicit fused multiply-adds, so a
-// value recomputed by another workgroup (a strip halo, a TSV partner) is
-// bitwise the value its owner writes.
+// goes through these two functions, with explicit fused multiply-adds and no
+// others, so a value recomputed by another workgroup (a strip halo, a TSV partner)
+// is bitwise the value its owner writes.  (Left to contract, the compiler turned
+// g - t into two fused steps where it saw how t was made, and not in the
+// three-step passes, which keep t for a row: TSV nodes differed in the last bit.)
 template <typename T>
 __device__ __forceinline__ T tsv_term(T gu, T yu, T gd, T yd) {
+#pragma clang fp contract(off)
   return fma(gu, yu, gd * yd);
 }
 
 template <typename T>
 __device__ __forceinline__ T cheb_node_t(T u, T ue, T uw, T un, T us, T t, T d, T ce, T cw, T cn,
                                          T cs, T up, T r, T dinv, T a1, T a2) {
+#pragma clang fp contract(off)
   T g = d * u;
   g = fma(-ce, ue, g);
   g = fma(-cw, uw, g);
