@@ -30,7 +30,7 @@ MFMA_PEAK_TFLOPS = {"f32": 157.3, "f64": 78.6}   # dense matrix-core peaks
 S = 64
 
 
-def cheb_passes(cheb, fp32=True):
+def cheb_passes(cheb):
     """The Chebyshev passes of one preconditioner application, in order:
     (steps, has z_{j-1}) per pass.  Steps run three per pass while three
     remain, then two, then one."""
@@ -43,7 +43,7 @@ def cheb_passes(cheb, fp32=True):
     return out
 
 
-def cheb_folds_z1(cheb, fp32=True):
+def cheb_folds_z1(cheb):
     """The first pass is a three-step pass that forms z_1 = D^-1 R / theta
     from R itself (nothing writes z_1)."""
     return cheb > 3
@@ -51,15 +51,16 @@ def cheb_folds_z1(cheb, fp32=True):
 
 def cheb_words(cheb, fp32=True):
     """S-wide vector words per node that the Chebyshev passes of one
-    application read and write, and the number of passes: a pass reads z_j,
+    application read and write, and the number of passes (the same in either
+    precision): a pass reads z_j,
     R (and z_{j-1} after the first; a first pass that forms z_1 from R reads
     R alone) and writes its last two iterates (one for a single step; a last
     three-step pass writes only its last)."""
-    passes = cheb_passes(cheb, fp32)
+    passes = cheb_passes(cheb)
     words = 0
     for n, (k, prev) in enumerate(passes):
         last = n == len(passes) - 1
-        reads = 3 if prev else (1 if cheb_folds_z1(cheb, fp32) else 2)
+        reads = 3 if prev else (1 if cheb_folds_z1(cheb) else 2)
         words += reads + (1 if k == 1 or (k == 3 and last) else 2)
     return words, len(passes)
 
@@ -84,7 +85,7 @@ def kernel_bytes(n, fp32=True, mixed_with_d=True, cheb=1):
     """
     w = 4 if fp32 else 8
     k1 = n * (4 * S * w + 3 * w + 4)
-    z1 = cheb > 1 and not cheb_folds_z1(cheb, fp32)
+    z1 = cheb > 1 and not cheb_folds_z1(cheb)
     d_in_k3 = mixed_with_d and cheb > 1
     k2 = n * ((6 if mixed_with_d and not d_in_k3 else 3) * S * w + w + (S * w if z1 else 0))
     k3 = n * ((5 if d_in_k3 else 3) * S * w + 2 * w)
@@ -191,12 +192,11 @@ def grid_pairs_compare(reff, log, M=512, N=512, P=256, reps=5):
     """Eq. 3 on one uniform tier (the intra-die step of the paper's pair
     method, Sec. III-C/D): every pair of P seeded points on an M x N grid,
     output to device memory, checked on sampled pairs against the closed form
-    summed directly in float64.  The library evaluates the double sums as
-    T = X diag(W) X^T on the float64 matrix cores: 64 x 64 blocks of T for the
-    upper block pairs, each a product over K = (M-1)(N-1), i.e.
-    2 * 64 * 64 * K flops per block pair; that issued work is the roofline
-    figure.  The direct form (6 flops per term and pair) is reported beside
-    it as an equivalent rate only."""
+    summed directly in float64.  The library takes the pairs from a cosine
+    table of the tier, two products over it on the float64 matrix cores; that
+    issued work is the roofline figure (the call's allocation and the other
+    kernels are in the time).  The direct form (6 flops per term and pair) is
+    reported beside it as an equivalent rate only."""
     import numpy as np
     import torch
     from tests import pins
@@ -219,8 +219,9 @@ def grid_pairs_compare(reff, log, M=512, N=512, P=256, reps=5):
     for i, j in [(0, 1), (7, 200), (100, 255), (31, 32)]:
         w = pins.wu_two_point(M, N, r, s, *xy[i], *xy[j])
         err = max(err, abs(R[i, j] - w) / w)
-    nb = (P + 63) // 64
-    issued = nb * (nb + 1) // 2 * 2 * 64 * 64 * (M - 1) * (N - 1)
+    # the cosine table's two products over the tier, in 32 x 32 x 32 steps
+    pad = lambda n: (n + 31) // 32 * 32  # noqa: E731
+    issued = 2 * pad(M + 1) * pad(N - 1) * (pad(M - 1) + pad(N + 1))
     tflops = issued / dt / 1e12
     direct = 6.0 * terms / dt / 1e12
     log(f"grid pairs (Eq. 3): {pairs / dt:.3g} pairs/s, {tflops:.1f} TFLOP/s issued float64 "

@@ -387,9 +387,9 @@ __global__ __launch_bounds__(WG, 4) void k_stencil_gram(Coef<T> c, Work wk,
     // unit).  A wave's nodes are consecutive: their rows and their east and
     // west neighbours are six rows.  The sum of stencil_row; a coupling that
     // does not exist is 0 and multiplies a finite value, and TSV partners are
-    // read where a node has them (wave-uniform).  In float64 that fits the 128
-    // registers of two workgroups per CU: with seven rows per node 41 of them
-    // were spilled and the kernel took 382 us at 4 x 256 x 256, now 239.
+    // read where a node has them (wave-uniform).  In float64 8 of the 128
+    // registers of two workgroups per CU are spilled: with seven rows per node it
+    // was 41 and the kernel took 382 us at 4 x 256 x 256, now 239.
     T yw[NODES_PER_WAVE + 2], yn[NODES_PER_WAVE], ys[NODES_PER_WAVE];
     T yv[NODES_PER_WAVE], rv[NODES_PER_WAVE], qv[NODES_PER_WAVE];
     const int64_t v0 = base + w * NODES_PER_WAVE, vend = u.pd.vbase + u.pd.n - 1;
@@ -1516,8 +1516,12 @@ __global__ __launch_bounds__(WG, sizeof(T) == 4 ? 4 : 2) void k_cheb2_strip(Coef
 // A strip pass costs about 15 us however small the stack (prologue of dependent
 // loads, a handful of workgroups, side-buffer launches), nine of them an
 // application at degree 19; this is one launch of 24 us (2 x 32 x 32,
-// float64).  NPT nodes per thread: float64 up to 4, float32 up to 8 (registers
-// and 128 KB of LDS), which bounds the stack (resident_nodes).
+// float64).  NPT nodes per thread, at 128 registers a thread (16 waves): float64 up
+// to 4 (116 registers), float32 up to 8 (128 and 6 spilled), 64 KB of LDS either
+// way, which bounds the stack (resident_nodes).  At that bound one launch is still
+// ahead: 64 mixed samples of 2 x 64 x 64 nodes 3.15 ms by strip passes, 2.24 here,
+// 128 such plans in one call 55 and 51 ms; of the shapes from 4200 to 8192 nodes only
+// 128 plans of 1 x 90 x 90 were slower (46.9 and 47.7 ms).
 constexpr int RES_THREADS = 1024;
 struct ChebSteps {
   double a1[MAX_CHEB], a2[MAX_CHEB];
