@@ -802,6 +802,7 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
         x.piv = f.piv;
         x.F = f.F;
         x.k = f.k;
+        x.child[0] = x.child[1] = -1;
         x.pF = f.parent >= 0 ? P.fronts[(size_t)f.parent].F : 0;
         x.inv = n_inv;
         n_inv += x.pF;
@@ -815,9 +816,8 @@ std::shared_ptr<SelinvDevice> selinv_device_build(const SelinvPlan& P, reff_stat
     lists.insert(lists.end(), L.fronts.begin(), L.fronts.end());
     V.groups = std::move(groups[d]);
   }
-  const auto kids = assembly_children(P);
   for (size_t i = 0; i < P.fronts.size(); ++i)
-    for (int c = 0; c < 2; ++c) dfr[i].child[c] = kids[i][(size_t)c];
+    if (has_update(P.fronts[i])) dfr[(size_t)P.fronts[i].parent].child[P.fronts[i].rank] = (int32_t)i;
   hipError_t e = hipSuccess;
   if (use_cache) {
     const SelinvSizes& z = D->sz;

@@ -36,15 +36,6 @@ std::vector<uint8_t> needed_fronts(const SelinvPlan& P, const std::vector<int64_
   return need;
 }
 
-std::vector<std::array<int32_t, 2>> assembly_children(const SelinvPlan& P) {
-  std::vector<std::array<int32_t, 2>> ch(P.fronts.size(), {-1, -1});
-  for (size_t i = 0; i < P.fronts.size(); ++i) {
-    const SnFront& f = P.fronts[i];
-    if (f.parent >= 0 && f.F > f.k) ch[(size_t)f.parent][(size_t)f.rank] = (int32_t)i;
-  }
-  return ch;
-}
-
 namespace {
 
 struct Builder {

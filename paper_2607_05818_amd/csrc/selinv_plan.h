@@ -23,7 +23,6 @@
 
 #include <stdint.h>
 
-#include <array>
 #include <functional>
 #include <string>
 #include <vector>
@@ -40,6 +39,12 @@ struct SnFront {
   int64_t piv = 0;       // offset into SelinvPlan::piv_node of its k node ids
   int32_t x0 = 0, x1 = 0, y0 = 0, y1 = 0;  // box
 };
+
+// Whether the assembly of a front's parent adds its update matrix.  A front
+// without update rows (F == k: pads or the stack's edge all around its box) has
+// none: off + k F + k would lie past its block, and for the last front past the
+// arena.
+inline bool has_update(const SnFront& f) { return f.parent >= 0 && f.F > f.k; }
 
 struct SelinvLevel {
   std::vector<int32_t> fronts;  // front indices at this depth
@@ -77,12 +82,6 @@ SelinvPlan merge_selinv_plans(const std::vector<SelinvPlan>& plans, std::vector<
 // *flops.  Node ids must lie in [0, n).
 std::vector<uint8_t> needed_fronts(const SelinvPlan& P, const std::vector<int64_t>& ids,
                                    double* flops);
-
-// Per front, the children whose update matrices its assembly adds (by rank;
-// -1: none).  A child without update rows (F == k: pads or the stack's edge
-// all around its box) has no update matrix: off + k F + k would lie past its
-// block, and for the last front past the arena.
-std::vector<std::array<int32_t, 2>> assembly_children(const SelinvPlan& P);
 
 // Run body(i) for i < count on up to 16 host threads.
 void selinv_parallel_for(size_t count, const std::function<void(size_t)>& body);

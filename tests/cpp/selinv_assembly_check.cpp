@@ -1,5 +1,5 @@
 // Host check of the reads of a front's assembly (k_assemble in selinv.hip):
-// for every child that assembly_children lists, the kernel reads entries (a, b),
+// for every child that has_update names, the kernel reads entries (a, b),
 // 0 <= a, b < F - k, of the matrix that starts at off + k F + k with column
 // stride F, and (0, 0) of it wherever a row or column of the parent has no
 // counterpart.  All of them have to lie inside the child's own block; no child
@@ -39,29 +39,22 @@ static SelinvPlan plan_of(int nt, int nx, int ny, const std::vector<int32_t>& pa
 
 // Returns how many fronts below a parent have no update rows.
 static int check(const SelinvPlan& P, const char* name) {
-  const auto ch = assembly_children(P);
-  chk(ch.size() == P.fronts.size(), "one entry per front", name);
-  std::vector<char> listed(P.fronts.size(), 0);
-  for (size_t i = 0; i < P.fronts.size(); ++i)
-    for (int r = 0; r < 2; ++r) {
-      const int32_t c = ch[i][(size_t)r];
-      if (c < 0) continue;
-      const SnFront& g = P.fronts[(size_t)c];
-      chk(g.parent == (int32_t)i && g.rank == r, "child of its parent", name);
-      listed[(size_t)c] = 1;
-      const int64_t first = g.off + (int64_t)g.k * g.F + g.k, q = g.F - g.k;
-      const int64_t last = first + (q > 0 ? (q - 1) * g.F + q - 1 : 0), end = g.off + (int64_t)g.F * g.F;
-      chk(first < end && last < end, "reads inside the child's block", name);
-      chk(end <= P.arena, "block inside the arena", name);
-    }
   int empty = 0;
-  for (size_t i = 0; i < P.fronts.size(); ++i) {
-    const SnFront& f = P.fronts[i];
-    if (f.parent < 0) continue;
-    if (f.F > f.k)
-      chk(listed[i], "every update matrix is added", name);
-    else
-      ++empty;
+  for (const SnFront& g : P.fronts) {
+    if (g.parent < 0) {
+      chk(!has_update(g), "a root has no parent to add to", name);
+      continue;
+    }
+    chk(g.rank == 0 || g.rank == 1, "rank", name);
+    if (g.F == g.k) ++empty;
+    if (!has_update(g)) {
+      chk(g.F == g.k, "every update matrix is added", name);
+      continue;
+    }
+    const int64_t first = g.off + (int64_t)g.k * g.F + g.k, q = g.F - g.k;
+    const int64_t last = first + (q > 0 ? (q - 1) * g.F + q - 1 : 0), end = g.off + (int64_t)g.F * g.F;
+    chk(first < end && last < end, "reads inside the child's block", name);
+    chk(end <= P.arena, "block inside the arena", name);
   }
   printf("%s: %zu fronts, %d without update rows\n", name, P.fronts.size(), empty);
   return empty;
