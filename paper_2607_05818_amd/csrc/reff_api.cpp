@@ -880,10 +880,6 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     if (cheb && (rs = ensure(ws.Zb, vec)) != REFF_OK) return rs;
     if (cheb && o.cheb > 2 && (rs = ensure(ws.Zc, vec)) != REFF_OK) return rs;
     if (cheb && o.cheb > 2 && (rs = ensure(ws.Zd, vec)) != REFF_OK) return rs;
-    bool triples = cheb && o.cheb > 3;
-    for (const PlanDesc& p : plans) triples = triples && max_strip_rows(p.nx, tsz) >= 1;
-    if (triples && (rs = ensure(ws.TA, (size_t)slot_rows * 5 * S * tsz)) != REFF_OK) return rs;
-    if (triples && (rs = ensure(ws.TB, (size_t)slot_rows * S * tsz)) != REFF_OK) return rs;
     // (only the float32 strips of K1 write Gram partials)
     const size_t npart = (size_t)(fp32 ? std::max(nu, ns) : nu);
     if ((rs = ensure(ws.part, npart * NGRAM * S * S * sizeof(double))) != REFF_OK) return rs;
@@ -900,6 +896,21 @@ reff_status run_blocks(Workspace& ws, const CoefSet& cs, const std::vector<Stack
     if ((rs = ensure(ws.act, (size_t)nb * sizeof(int32_t))) != REFF_OK) return rs;
     if ((rs = ensure(ws.flags, (size_t)nb * 2 * sizeof(int32_t))) != REFF_OK) return rs;
     if ((rs = ensure(ws.cnt, 4 * sizeof(int32_t))) != REFF_OK) return rs;
+    // The side buffers of the three-step passes come last: where the device has
+    // no room for them (6 more vectors' worth on a stack with a TSV at every
+    // node), two-step passes give the same bits.
+    bool triples = cheb && o.cheb > 3;
+    for (const PlanDesc& p : plans) triples = triples && max_strip_rows(p.nx, tsz) >= 1;
+    if (triples) {
+      rs = ensure(ws.TA, (size_t)slot_rows * 5 * S * tsz);
+      if (rs == REFF_OK) rs = ensure(ws.TB, (size_t)slot_rows * S * tsz);
+      if (rs != REFF_OK && rs != REFF_ERR_OUT_OF_MEMORY) return rs;
+      if (rs != REFF_OK) {
+        (void)hipGetLastError();
+        g_err.clear();
+        triples = false;
+      }
+    }
     // ---- tables (one pinned staging area, uploaded asynchronously)
     const size_t tab_bytes = nb * sizeof(PlanDesc) + nu * sizeof(Unit) + nb * S * 16 +
                              (nu + nb) * sizeof(int32_t) * 2 + ns * sizeof(Strip) +
